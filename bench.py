@@ -65,8 +65,8 @@ def nphi_bytes(storage, rows):
 
 
 KERNEL_SOURCES = ("device.hpp", "k_step.hip", "k_nphi.hip", "k_host.hip", "k_batch.hip",
-                  "lattice.hpp", "internal.h")
-PROFILE_KERNELS = {"k_collide_nphi": "k_phi_merge", "k_collide": "k_phi"}
+                  "k_step2d.hip", "step2d.hpp", "lattice.hpp", "internal.h")
+PROFILE_KERNELS = {"k_collide_nphi": "k_phi_merge", "k_collide": "k_phi", "k_step2d": None}
 PROFILES_DIR = os.path.join(ROOT, "profiles")
 
 
@@ -79,8 +79,8 @@ def profiled_traffic(storage, workload, kernel):
 
     if kernel not in PROFILE_KERNELS:
         return None
-    path = os.path.join(PROFILES_DIR, "%s_%s_%s_%s_hbm_bytes.md" %
-                        (kernel, PROFILE_KERNELS[kernel], workload, storage))
+    path = os.path.join(PROFILES_DIR, "%s_hbm_bytes.md" % "_".join(
+        v for v in (kernel, PROFILE_KERNELS[kernel], workload, storage) if v))
     if not os.path.exists(path):
         return None
     h = hashlib.sha256()
@@ -923,6 +923,9 @@ def main():
     if rows:
         kernel, phi_kernel = "k_collide_nphi", "k_phi_merge"
         kbytes = nphi_bytes(args.storage, rows)[0] + hist
+    elif dim == 2:
+        # one launch per step, which sums phi in its blocks
+        kernel, kbytes, phi_kernel = "k_step2d", ab["method"] - 2 * (8 if args.storage == "fp64" else 4) + hist, None
     else:
         kernel, kbytes, phi_kernel = "k_collide", ab["collide"] + hist, "k_phi"
     method_bytes = ab["method"] + hist

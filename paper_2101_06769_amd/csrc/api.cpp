@@ -260,16 +260,27 @@ struct mplb_solver {
         return mplb::NextPhi{at(L.npart), at(L.nedge),
                              mplb::nphi_rows(prm.n[0], prm.n[1], prm.storage)};
     }
+    // The step is one launch, which sums phi in its blocks and leaves the phi
+    // array alone.
+    bool one_launch() const { return mplb::step2d_ok(prm.dim, prm.storage); }
+    // The phi array of the current level for a reader of it between steps.
+    hipError_t refresh_phi(const mplb::Ctx &c) const
+    {
+        return one_launch() ? mplb::launch_phi(c) : hipSuccess;
+    }
     // The phi stage of a step: merge the partial sums the previous update
-    // wrote, or sum the pulled populations.
+    // wrote, or sum the pulled populations (nothing where the step is one
+    // launch).
     hipError_t launch_phi_stage(const mplb::Ctx &c) const
     {
+        if (one_launch()) return hipSuccess;
         if (use_nphi(c) && nphi_valid) return mplb::launch_phi_merge(c, next_phi());
         return mplb::launch_phi(c);
     }
     // The update stage; records whether it left partial sums for the next step.
     hipError_t launch_update_stage(const mplb::Ctx &c)
     {
+        if (one_launch()) return mplb::launch_step2d(c);
         nphi_valid = use_nphi(c);
         return nphi_valid ? mplb::launch_collide_nphi(c, next_phi()) : mplb::launch_collide(c);
     }
@@ -869,6 +880,12 @@ struct mplb_batch {
     int *d_ntiles;
     long long *d_tbase;
     int *d_status;  // per slot: non-zero once the phi stage met a non-finite value
+    // 2-D domains in plain storage: one launch per step over step2d tiles
+    bool one_launch() const { return mplb::step2d_ok(dim, storage); }
+    int *d_tile0;            // running tile counts, capacity + 1 (see launch_batch_step2d)
+    std::vector<int> tile0;  // host copy
+    int grid2d;              // blocks: the tile count rounded up to a bucket
+    bool kept;               // the attached populations stay in the Infinity Cache
     std::vector<mplb_solver *> slot;
     std::vector<mplb::BatchDom> doms;
     std::vector<mplb::BatchTile> tiles;
@@ -903,7 +920,7 @@ struct mplb_batch {
 namespace {
 
 size_t table_layout(int32_t capacity, int64_t max_tiles, size_t *o_doms, size_t *o_tiles,
-                    size_t *o_nt, size_t *o_tb, size_t *o_st)
+                    size_t *o_nt, size_t *o_tb, size_t *o_st, size_t *o_t0)
 {
     size_t off = 0;
     *o_doms = off;
@@ -916,6 +933,8 @@ size_t table_layout(int32_t capacity, int64_t max_tiles, size_t *o_doms, size_t 
     off += ALIGN;
     *o_st = off;
     off += up(sizeof(int) * capacity, ALIGN);
+    *o_t0 = off;
+    off += up(sizeof(int) * (size_t(capacity) + 1), ALIGN);
     return off;
 }
 
@@ -1019,6 +1038,23 @@ int upload_tables(mplb_batch *b)
     }
     if (row != b->row) drop_graph(b);  // a captured graph holds the other kernel
     b->row = row;
+    if (b->one_launch()) {
+        // the running tile counts; the launch size moves in buckets, as above
+        long long cells = 0, n = 0;
+        for (int i = 0; i < b->capacity; ++i) {
+            b->tile0[i] = int(n);
+            if (!b->slot[i]) continue;
+            cells += b->doms[i].g.np;
+            if (!b->solo[i]) n += mplb::step2d_tiles(b->doms[i].g);
+        }
+        if (n > 0x7fffffffLL - 4096) return fail(MPLB_ENOMEM, "batch tile list is full");
+        b->tile0[b->capacity] = int(n);
+        const int grid2d = int((n + 4095) / 4096 * 4096);
+        const bool kept = mplb::kept_in_cache(2, b->storage, cells);
+        if (grid2d != b->grid2d || kept != b->kept) drop_graph(b);
+        b->grid2d = grid2d;
+        b->kept = kept;
+    }
     HIPCHK(hipStreamSynchronize(b->stream));
     HIPCHK(hipMemcpyAsync(b->d_doms, b->doms.data(), sizeof(mplb::BatchDom) * b->capacity,
                           hipMemcpyHostToDevice, b->stream));
@@ -1033,6 +1069,8 @@ int upload_tables(mplb_batch *b)
     }
     HIPCHK(hipMemcpyAsync(b->d_ntiles, b->counts, sizeof(b->counts), hipMemcpyHostToDevice,
                           b->stream));
+    HIPCHK(hipMemcpyAsync(b->d_tile0, b->tile0.data(), sizeof(int) * b->tile0.size(),
+                          hipMemcpyHostToDevice, b->stream));
     HIPCHK(hipStreamSynchronize(b->stream));
     return MPLB_OK;
 }
@@ -1044,8 +1082,8 @@ extern "C" {
 size_t mplb_batch_table_bytes(int32_t capacity, int64_t max_tiles)
 {
     if (capacity < 1 || max_tiles < 1) return 0;
-    size_t a, b, c, d, e;
-    return table_layout(capacity, max_tiles, &a, &b, &c, &d, &e);
+    size_t a, b, c, d, e, f;
+    return table_layout(capacity, max_tiles, &a, &b, &c, &d, &e, &f);
 }
 
 int mplb_batch_create(int32_t dim, int32_t storage, int32_t capacity, int64_t max_tiles,
@@ -1062,8 +1100,8 @@ int mplb_batch_create(int32_t dim, int32_t storage, int32_t capacity, int64_t ma
         return fail(MPLB_EINVAL, "table memory must be non-NULL and 256-byte aligned");
     if (!hip_stream)
         return fail(MPLB_EINVAL, "a batch needs its own stream (graphs cannot capture the null stream)");
-    size_t od, ot, on, ob, os;
-    const size_t need = table_layout(capacity, max_tiles, &od, &ot, &on, &ob, &os);
+    size_t od, ot, on, ob, os, o0;
+    const size_t need = table_layout(capacity, max_tiles, &od, &ot, &on, &ob, &os, &o0);
     if (table_bytes < need) return fail(MPLB_ENOMEM, "batch table memory too small");
     mplb_batch *b = new (std::nothrow) mplb_batch();
     if (!b) return fail(MPLB_ENOMEM, "host allocation failed");
@@ -1079,6 +1117,10 @@ int mplb_batch_create(int32_t dim, int32_t storage, int32_t capacity, int64_t ma
     b->d_ntiles = reinterpret_cast<int *>(base + on);
     b->d_tbase = reinterpret_cast<long long *>(base + ob);
     b->d_status = reinterpret_cast<int *>(base + os);
+    b->d_tile0 = reinterpret_cast<int *>(base + o0);
+    b->tile0.assign(size_t(capacity) + 1, 0);
+    b->grid2d = 0;
+    b->kept = false;
     b->slot.assign(capacity, nullptr);
     b->doms.assign(capacity, mplb::BatchDom{});
     b->solo.assign(capacity, 0);
@@ -1255,6 +1297,22 @@ int mplb_batch_status(mplb_batch *b, int32_t *status)
     return closed ? upload_tables(b) : MPLB_OK;
 }
 
+namespace {
+
+// The launches of one step of the domains that share them.
+hipError_t shared_step(mplb_batch *b, int step_off)
+{
+    if (b->one_launch())
+        return mplb::launch_batch_step2d(b->storage, b->collision, b->kept, b->d_doms, b->d_tile0,
+                                         b->capacity, b->d_tbase, step_off, b->grid2d, b->d_status,
+                                         b->side);
+    return mplb::launch_batch_step(b->dim, b->storage, b->collision, b->row, b->d_doms, b->d_tiles,
+                                   b->d_ntiles, b->d_tbase, step_off, b->block, b->grid, b->d_status,
+                                   b->side);
+}
+
+}  // namespace
+
 int mplb_batch_step(mplb_batch *b, int64_t nsteps)
 {
     if (!b) return fail(MPLB_EINVAL, "batch is NULL");
@@ -1273,10 +1331,7 @@ int mplb_batch_step(mplb_batch *b, int64_t nsteps)
                 hipGraph_t graph = nullptr;
                 HIPCHK(hipStreamBeginCapture(b->side, hipStreamCaptureModeThreadLocal));
                 hipError_t e = hipSuccess;
-                for (int k = 0; k < b->chunk && e == hipSuccess; ++k)
-                    e = mplb::launch_batch_step(b->dim, b->storage, b->collision, b->row,
-                                                b->d_doms, b->d_tiles, b->d_ntiles, b->d_tbase, k,
-                                                b->block, b->grid, b->d_status, b->side);
+                for (int k = 0; k < b->chunk && e == hipSuccess; ++k) e = shared_step(b, k);
                 // always end the capture, so that a failure leaves the stream usable
                 const hipError_t e2 = hipStreamEndCapture(b->side, &graph);
                 if (e != hipSuccess || e2 != hipSuccess) {
@@ -1294,9 +1349,7 @@ int mplb_batch_step(mplb_batch *b, int64_t nsteps)
             b->t += b->chunk;
             done += b->chunk;
         } else {
-            HIPCHK(mplb::launch_batch_step(b->dim, b->storage, b->collision, b->row, b->d_doms,
-                                           b->d_tiles, b->d_ntiles, b->d_tbase, 0, b->block,
-                                           b->grid, b->d_status, b->side));
+            HIPCHK(shared_step(b, 0));
             b->t += 1;
             done += 1;
         }
@@ -1317,6 +1370,7 @@ int mplb_batch_step(mplb_batch *b, int64_t nsteps)
             const bool steady = s->hist && (!s->use_nphi(c) || s->nphi_valid);
             if (steady && hi - k >= GRAPH_STEPS) {
                 // a run of steps as the solver's step graph, its phi checked first
+                HIPCHK(s->refresh_phi(c));
                 HIPCHK(mplb::launch_flag_nonfinite(c, b->d_status + i));
                 const int rc = replay_steps(s);
                 if (rc != MPLB_OK) return rc;
@@ -1325,7 +1379,10 @@ int mplb_batch_step(mplb_batch *b, int64_t nsteps)
                 continue;
             }
             HIPCHK(s->launch_phi_stage(c));
-            if ((k - lo) % check == 0) HIPCHK(mplb::launch_flag_nonfinite(c, b->d_status + i));
+            if ((k - lo) % check == 0) {
+                HIPCHK(s->refresh_phi(c));
+                HIPCHK(mplb::launch_flag_nonfinite(c, b->d_status + i));
+            }
             HIPCHK(s->launch_update_stage(c));
             s->cur ^= 1;
             s->steps++;

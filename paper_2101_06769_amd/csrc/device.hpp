@@ -229,6 +229,64 @@ __device__ __forceinline__ T phi_at(const NbRow &n, const T *phi, int cx, int cy
     return *lane_ptr(phi, (long long)(n.ry[1 + cy] + n.rz[1 + cz]), xx);
 }
 
+// Cell of the one-launch 2-D step (step2d.hpp): the order parameter comes
+// from the block's LDS tile (lphi at the cell's own slot, rows ls slots apart)
+// and the pulled populations of both sets are already in registers.  row, x:
+// where its values are stored.
+template <typename T, bool KEPT>
+struct NbTile {
+    static constexpr bool kept = KEPT;
+    int row, x;
+    const T *lphi;
+    int ls;
+    T f[9], gp[9];
+};
+template <class NB>
+constexpr bool in_tile = false;
+template <typename T, bool KEPT>
+constexpr bool in_tile<NbTile<T, KEPT>> = true;
+
+template <typename T, bool KEPT>
+__device__ __forceinline__ T phi_at(const NbTile<T, KEPT> &n, const T *, int cx, int cy, int)
+{
+    return n.lphi[cy * n.ls + cx];
+}
+
+// Stores a post-collision value: non-temporally, or (a form whose kept is set)
+// as an ordinary store, which leaves it in the Infinity Cache for the next
+// step.
+template <class NB, typename V, typename E>
+__device__ __forceinline__ void store_out(V v, gptr<E> at)
+{
+    if constexpr (in_tile<NB>) {
+        if constexpr (NB::kept)
+            *at = v;
+        else
+            __builtin_nontemporal_store(v, at);
+    } else {
+        __builtin_nontemporal_store(v, at);
+    }
+}
+
+// Pre-collision population a of a set in plain storage, where the cell's form
+// has it: loaded, or from registers (NbTile).
+template <int D, class S, typename T, class NB>
+__device__ __forceinline__ T flow_in(const NB &n, const void *base, long long np, int a)
+{
+    if constexpr (in_tile<NB>)
+        return n.f[a];
+    else
+        return pull<D, S, T>(n, base, np, a);
+}
+template <int D, class S, typename T, class NB>
+__device__ __forceinline__ T phase_in(const NB &n, const void *base, long long np, int a)
+{
+    if constexpr (in_tile<NB>)
+        return n.gp[a];
+    else
+        return pull<D, S, T>(n, base, np, a);
+}
+
 // Parameters in the arithmetic type.
 template <typename T>
 struct Phys {
@@ -435,15 +493,15 @@ __device__ __forceinline__ void flow_moments(const NB &nb, long long np, const P
 {
     using T = typename P::T;
     constexpr int Q = Lat<D>::Q;
-    T S0 = pull<D, typename P::F, T>(nb, p.Fin, np, Q / 2);
+    T S0 = flow_in<D, typename P::F, T>(nb, p.Fin, np, Q / 2);
     if constexpr (STASH) *stash_rest = S0;
     T Sx = 0, Sy = 0, Sz = 0, Sxx = 0, Syy = 0, Szz = 0, Sxy = 0, Sxz = 0, Syz = 0;
 #pragma unroll
     for (int a = Q / 2 + 1; a < Q; ++a) {
         const int b = opposite<D>(a);
         const int cx = cx_of(a), cy = cy_of(a), cz = cz_of<D>(a);
-        const T va = pull<D, typename P::F, T>(nb, p.Fin, np, a);
-        const T vb = pull<D, typename P::F, T>(nb, p.Fin, np, b);
+        const T va = flow_in<D, typename P::F, T>(nb, p.Fin, np, a);
+        const T vb = flow_in<D, typename P::F, T>(nb, p.Fin, np, b);
         if constexpr (STASH) {
             stash[nphi_slot(a) * sstride] = va;
             stash[nphi_slot(b) * sstride] = vb;
@@ -993,7 +1051,7 @@ __device__ __forceinline__ void collide_body(const NB &nb, const Geom &g,
             } else {
                 const T v = dev + weight<D, T>(a) * c.pstar;
                 fsum += v;
-                __builtin_nontemporal_store(typename P::F::raw(v),
+                store_out<NB>(typename P::F::raw(v),
                     lane_ptr(static_cast<typename P::F::raw *>(p.Fout), (long long)a * g.np + row, xl));
             }
         };
@@ -1003,7 +1061,7 @@ __device__ __forceinline__ void collide_body(const NB &nb, const Geom &g,
             if constexpr (P::F::shifted)
                 __builtin_nontemporal_store(float(v0), lane_ptr(p.frest_out, row, xl));
             else
-                __builtin_nontemporal_store(typename P::F::raw(v0),
+                store_out<NB>(typename P::F::raw(v0),
                     lane_ptr(static_cast<typename P::F::raw *>(p.Fout), (long long)(Q / 2) * g.np + row, xl));
         };
         if constexpr ((COLL & 1) == 0) {
@@ -1123,7 +1181,7 @@ __device__ __forceinline__ void collide_body(const NB &nb, const Geom &g,
                 if constexpr (KEEP) keep[nphi_slot(a) * kstride] = dec;
             } else {
                 gsum += gout;
-                __builtin_nontemporal_store(typename P::G::raw(gout),
+                store_out<NB>(typename P::G::raw(gout),
                     lane_ptr(static_cast<typename P::G::raw *>(p.Gout), (long long)a * g.np + row, xl));
                 if constexpr (KEEP) keep[nphi_slot(a) * kstride] = gout;
             }
@@ -1141,9 +1199,9 @@ __device__ __forceinline__ void collide_body(const NB &nb, const Geom &g,
                     dz = qz - *lane_ptr(in, 2 * g.np + row, xl);
                 }
                 // non-temporal: read by the next update
-                __builtin_nontemporal_store(qx, lane_ptr(out, row, xl));
-                __builtin_nontemporal_store(qy, lane_ptr(out, g.np + row, xl));
-                __builtin_nontemporal_store(qz, lane_ptr(out, 2 * g.np + row, xl));
+                store_out<NB>(qx, lane_ptr(out, row, xl));
+                store_out<NB>(qy, lane_ptr(out, g.np + row, xl));
+                store_out<NB>(qz, lane_ptr(out, 2 * g.np + row, xl));
             }
             // the pulled values: all loads issued before the first store (the
             // compiler cannot prove the stored set apart from the pulled one,
@@ -1173,8 +1231,8 @@ __device__ __forceinline__ void collide_body(const NB &nb, const Geom &g,
                     va = pre[a];
                     vb = pre[b];
                 } else {
-                    va = pull<D, typename P::G, T>(nb, p.Gin, g.np, a);
-                    vb = pull<D, typename P::G, T>(nb, p.Gin, g.np, b);
+                    va = phase_in<D, typename P::G, T>(nb, p.Gin, g.np, a);
+                    vb = phase_in<D, typename P::G, T>(nb, p.Gin, g.np, b);
                 }
                 if constexpr (P::G::shifted) {
                     const unsigned r = gref[a - (Q / 2 + 1)];
@@ -1199,7 +1257,7 @@ __device__ __forceinline__ void collide_body(const NB &nb, const Geom &g,
             if constexpr (P::G::shifted)
                 __builtin_nontemporal_store(float(g0), lane_ptr(p.grest_out, row, xl));
             else
-                __builtin_nontemporal_store(typename P::G::raw(g0),
+                store_out<NB>(typename P::G::raw(g0),
                     lane_ptr(static_cast<typename P::G::raw *>(p.Gout), (long long)(Q / 2) * g.np + row, xl));
             if constexpr (KEEP) *keep_rest = g0;
         };

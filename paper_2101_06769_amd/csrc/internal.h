@@ -64,6 +64,14 @@ struct Ctx {
 
 hipError_t launch_phi(const Ctx &c);
 hipError_t launch_collide(const Ctx &c);
+// The whole step of a 2-D lattice in plain storage (FP64, FP32) in one launch:
+// each block sums phi for its tile and the ring of cells around it into LDS,
+// then updates its cells; the phi array is not written.  step2d_ok tells
+// whether it applies.  Its tiles (step2d_tiles of them) do not depend on the
+// context's block.
+bool step2d_ok(int dim, int storage);
+int step2d_tiles(const Geom &g);
+hipError_t launch_step2d(const Ctx &c);
 // Partial sums of the next order parameter, written by launch_collide_nphi
 // for launch_phi_merge of the following step: part [3][np], edge
 // [2][3][ny / by][nz][nx] in the arithmetic type; by = tile rows,
@@ -138,6 +146,18 @@ struct BatchDom {
 struct BatchTile {
     int dom, x0, y0, z0, z1, w;
 };
+
+// One batch step of 2-D domains in plain storage (step2d_ok) in one launch:
+// tile0[0 .. capacity] are the domains' running tile counts (step2d_tiles;
+// none for an empty slot or a domain that steps alone); blocks beyond
+// tile0[capacity] exit.  kept: the populations are stored to stay in the
+// Infinity Cache.  status as for launch_batch_step.
+hipError_t launch_batch_step2d(int storage, int collision, bool kept, const BatchDom *doms,
+                               const int *tile0, int capacity, const long long *tbase, int step_off,
+                               int grid, int *status, hipStream_t stream);
+// Whether both levels of the populations of np cells stay in the Infinity
+// Cache from one step to the next.
+bool kept_in_cache(int dim, int storage, long long np);
 
 // True when the row-form kernels apply: block a multiple of 64 wide in x,
 // x periodic, population arrays of fewer than 2^31 elements.

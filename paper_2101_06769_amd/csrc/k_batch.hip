@@ -1,6 +1,6 @@
 // Batched kernels: many independent domains in the same launches (see
 // device.hpp, "batches").
-#include "device.hpp"
+#include "step2d.hpp"
 
 namespace mplb {
 
@@ -89,6 +89,63 @@ kb_collide_nphi(const BatchDom *__restrict__ doms, const BatchTile *__restrict__
     }
 }
 
+// Batched form of the one-launch 2-D step: block b takes tile b of the running
+// counts tile0 (in eighths per XCD, as k_step2d); every wavefront finds the
+// domain with one load of 64 counts at a time.
+template <class P, int COLL, bool KEPT>
+__global__ void __launch_bounds__(STEP2D_THREADS)
+kb_step2d(const BatchDom *__restrict__ doms, const int *__restrict__ tile0, int capacity,
+          const long long *tbase, int step_off, int *status)
+{
+    using T = typename P::T;
+    __shared__ T lphi[step2d_slots()];
+    const int nt = tile0[capacity], b0 = int(blockIdx.x);
+    if (b0 >= nt) return;
+    const int per = nt >> 3;
+    const int bid = b0 < per * 8 ? (b0 & 7) * per + (b0 >> 3) : b0;
+    // the last domain whose tiles begin at or before bid: domains without
+    // tiles share their successor's count and are passed over
+    int dom = -1;
+    for (int d0 = 0; d0 < capacity; d0 += 64) {
+        const int d = d0 + int(threadIdx.x & 63);
+        const int begins = __popcll(__ballot(d < capacity && tile0[d] <= bid));
+        dom += begins;
+        if (begins < 64) break;
+    }
+    dom = __builtin_amdgcn_readfirstlane(dom);
+    const long long t = *tbase + step_off;
+    const long long first = doms[dom].first, last = doms[dom].last;
+    if (t < first || t >= last) return;  // the whole block
+    const Geom g = doms[dom].g;  // by value, see kb_step
+    const Ptrs p = batch_ptrs(doms[dom], int((t - first) & 1), t >= doms[dom].hist_from);
+    const Phys<T> ph = to_phys<T>(doms[dom].ph);
+    const int lbx = step2d_width(g.nx), by = STEP2D_THREADS >> lbx;
+    const int ntx = (g.nx + (1 << lbx) - 1) >> lbx, k = bid - tile0[dom];
+    const int x0 = (k % ntx) << lbx, y0 = (k / ntx) * by;
+    if (lbx == 6)
+        step2d_tile<P, COLL, true, KEPT>(g, ph, p, lphi, lbx, x0, y0, status + dom);
+    else
+        step2d_tile<P, COLL, false, KEPT>(g, ph, p, lphi, lbx, x0, y0, status + dom);
+}
+
+hipError_t launch_batch_step2d(int storage, int collision, bool kept, const BatchDom *doms,
+                               const int *tile0, int capacity, const long long *tbase, int step_off,
+                               int grid, int *status, hipStream_t stream)
+{
+    if (!step2d_ok(2, storage)) return hipErrorInvalidValue;
+    return with_coll(collision, [&](auto cc) {
+        constexpr int COLL = decltype(cc)::value;
+        auto go = [&](auto kernel) {
+            hipLaunchKernelGGL(kernel, dim3(grid), dim3(STEP2D_THREADS), 0, stream, doms, tile0, capacity,
+                               tbase, step_off, status);
+            return hipGetLastError();
+        };
+        if (storage == ST_FP64)
+            return kept ? go(kb_step2d<P64, COLL, true>) : go(kb_step2d<P64, COLL, false>);
+        return kept ? go(kb_step2d<P32, COLL, true>) : go(kb_step2d<P32, COLL, false>);
+    });
+}
+
 __global__ void k_set_i64(long long *ptr, long long v) { *ptr = v; }
 
 __global__ void __launch_bounds__(256) k_fill_i32(int *ptr, int n, int v)
@@ -139,24 +196,29 @@ hipError_t launch_batch_step(int dim, int storage, int collision, bool row,
     };
     // collision: the operator code (bit 0 flow collision, bit 1 first-order
     // phase-field equilibrium), shared by every domain of the batch
-    return dispatch(c, [&]<int D, class P>() {
-        hipError_t e = row ? go(kb_step<D, P, 0, true, true>, block, grid[0])
-                           : go(kb_step<D, P, 0, true, false>, block, grid[0]);
-        if (e != hipSuccess) return e;
-        return with_coll(collision, [&](auto cc) {
-            constexpr int COLL = decltype(cc)::value;
-            // dynamic LDS: single relaxation time's flow values (3-D)
-            const size_t lds = srt_lds_bytes<D, P, COLL>(block.x * block.y * block.z);
-            hipError_t e2 = row ? go(kb_step<D, P, COLL, false, true>, block, grid[1], lds)
-                                : go(kb_step<D, P, COLL, false, false>, block, grid[1], lds);
-            const bool nphi = grid[2] || grid[3] || grid[4] || grid[5] || grid[6];
-            if constexpr (D == 3) {
-                if (e2 == hipSuccess && nphi) e2 = go_nphi.template operator()<P>(cc);
-            } else {
-                if (nphi) e2 = hipErrorInvalidValue;
-            }
-            return e2;
-        });
+    return dispatch(c, [&]<int D, class P>() -> hipError_t {
+        // 2-D domains in plain storage step in one launch (launch_batch_step2d)
+        if constexpr (D == 2 && !P::F::shifted) {
+            return hipErrorInvalidValue;
+        } else {
+            hipError_t e = row ? go(kb_step<D, P, 0, true, true>, block, grid[0])
+                               : go(kb_step<D, P, 0, true, false>, block, grid[0]);
+            if (e != hipSuccess) return e;
+            return with_coll(collision, [&](auto cc) {
+                constexpr int COLL = decltype(cc)::value;
+                // dynamic LDS: single relaxation time's flow values (3-D)
+                const size_t lds = srt_lds_bytes<D, P, COLL>(block.x * block.y * block.z);
+                hipError_t e2 = row ? go(kb_step<D, P, COLL, false, true>, block, grid[1], lds)
+                                    : go(kb_step<D, P, COLL, false, false>, block, grid[1], lds);
+                const bool nphi = grid[2] || grid[3] || grid[4] || grid[5] || grid[6];
+                if constexpr (D == 3) {
+                    if (e2 == hipSuccess && nphi) e2 = go_nphi.template operator()<P>(cc);
+                } else {
+                    if (nphi) e2 = hipErrorInvalidValue;
+                }
+                return e2;
+            });
+        }
     });
 }
 

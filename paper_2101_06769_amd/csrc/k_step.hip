@@ -33,6 +33,20 @@ bool row_form_ok(int dim, const Geom &g, dim3 block)
     return block.x % 64 == 0 && g.bcx == BC_PER && Q * g.np < (1ll << 31);
 }
 
+// Whether both levels of the populations of np cells stay in the 256 MiB
+// Infinity Cache from one step to the next.  Then they are stored with
+// ordinary stores: a non-temporal store goes to HBM, and the next step reads
+// it back from there (1024 x 1024 FP32, 151 MB: 35.3 against 24.9 us a step;
+// 1792 x 1024, 264 MB: 57.0 against 41.5).  Beyond that size cached stores only
+// displace what the step has yet to read (2048 x 1024, 302 MB: 64.1 against
+// 65.0 us; 2048 x 2048: 124 against 130).
+bool kept_in_cache(int dim, int storage, long long np)
+{
+    const long long f = storage == ST_FP64 ? 8 : storage == ST_FP32 ? 4 : 2;
+    const long long gg = storage == ST_FP64 ? 8 : storage == ST_FP16S_ALL ? 2 : 4;
+    return 2 * (dim == 2 ? 9 : 27) * np * (f + gg) <= (256ll << 20);
+}
+
 hipError_t launch_phi(const Ctx &c)
 {
     return dispatch(c, [&]<int D, class P>() {
@@ -46,21 +60,26 @@ hipError_t launch_phi(const Ctx &c)
 
 hipError_t launch_collide(const Ctx &c)
 {
-    return dispatch(c, [&]<int D, class P>() {
+    return dispatch(c, [&]<int D, class P>() -> hipError_t {
         using T = typename P::T;
-        const bool row = row_form(c);
-        return with_coll(coll_code(c.ph), [&](auto cc) {
-            constexpr int COLL = decltype(cc)::value;
-            // dynamic LDS: single relaxation time's flow values (3-D)
-            const size_t lds = srt_lds_bytes<D, P, COLL>(c.block.x * c.block.y * c.block.z);
-            if (row)
-                hipLaunchKernelGGL((k_collide<D, P, COLL, true>), grid_for(c), c.block, lds,
-                                   c.stream, c.g, to_phys<T>(c.ph), c.p);
-            else
-                hipLaunchKernelGGL((k_collide<D, P, COLL, false>), grid_for(c), c.block, lds,
-                                   c.stream, c.g, to_phys<T>(c.ph), c.p);
-            return hipGetLastError();
-        });
+        // 2-D lattices in plain storage step in one launch (launch_step2d)
+        if constexpr (D == 2 && !P::F::shifted) {
+            return hipErrorInvalidValue;
+        } else {
+            const bool row = row_form(c);
+            return with_coll(coll_code(c.ph), [&](auto cc) {
+                constexpr int COLL = decltype(cc)::value;
+                // dynamic LDS: single relaxation time's flow values (3-D)
+                const size_t lds = srt_lds_bytes<D, P, COLL>(c.block.x * c.block.y * c.block.z);
+                if (row)
+                    hipLaunchKernelGGL((k_collide<D, P, COLL, true>), grid_for(c), c.block, lds,
+                                       c.stream, c.g, to_phys<T>(c.ph), c.p);
+                else
+                    hipLaunchKernelGGL((k_collide<D, P, COLL, false>), grid_for(c), c.block, lds,
+                                       c.stream, c.g, to_phys<T>(c.ph), c.p);
+                return hipGetLastError();
+            });
+        }
     });
 }
 

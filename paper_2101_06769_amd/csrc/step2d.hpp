@@ -1,0 +1,192 @@
+// The one-launch step of 2-D lattices in plain storage: a block sums phi for
+// its tile and the ring of cells around it into LDS, then updates its cells.
+// A separate phi pass costs a launch (2.6 of the 7.0 us of a 64 x 256 FP64
+// step) and reads the phase-field set twice (40 of 188 B/cell).  The sums, the
+// stencil and the update are those of k_phi and k_collide in the same order,
+// so the results are the same bits.
+//
+// Bound: launch and load latency up to about 10^5 cells, then the Infinity
+// Cache (6 TB/s of the 144 B/cell at 1024 x 1024 FP32), beyond it HBM.  Tiles
+// of 256 threads: 512 and 1024 sum fewer ring cells (148 and 164 a tile
+// against 140, for two and four times the cells) but leave a small lattice
+// fewer blocks: 4.9, 6.1 and 8.8 us on 64 x 256 FP64, 24.9, 25.4 and 26+ us on
+// 1024 x 1024 FP32.  Measured per step, before (two launches) and now:
+// 64 x 256 FP64 7.0 -> 4.9 us, 128 x 512 FP32 (single relaxation time)
+// 7.2 -> 4.8, 800 x 400 FP32 between symmetry planes 18.0 -> 10.7,
+// 1024 x 1024 FP32 38.8 -> 24.9, 4096 x 2048 FP32 272 -> 252 us.
+#pragma once
+
+#include "device.hpp"
+
+namespace mplb {
+
+// The nine values of a set that a cell pulls.  Row form (ROWU): y and the
+// rules along it are wavefront-uniform (as NbRow), so each load is a scalar
+// base plus one of three lane columns; on axes that are not periodic the
+// first and last column's lanes then load what bounced back or was mirrored,
+// behind one branch that the other wavefronts skip.  Lane form: the rules of
+// both axes as per-lane selects.
+template <bool ROWU>
+struct Pull2d {
+    int x, xm, xp;      // own, left and right column (the own one beyond a wall or symmetry plane)
+    long long r[3];     // row offsets of y - 1, y, y + 1, likewise
+    bool wy[3], sy[3];  // a wall or symmetry plane between y and y + k - 1
+    bool wx, sx;        // the lattice has walls / symmetry planes in x
+    bool lo, hi;        // first / last column of a lattice not periodic in x
+
+    __device__ __forceinline__ Pull2d(const Geom &g, int x_, int y) : x(x_)
+    {
+        const bool per = g.bcx == BC_PER;
+        wx = g.bcx == BC_WALL;
+        sx = g.bcx == BC_SYM;
+        lo = !per && x == 0;
+        hi = !per && x == g.nx - 1;
+        xm = x > 0 ? x - 1 : per ? g.nx - 1 : 0;
+        xp = x < g.nx - 1 ? x + 1 : per ? 0 : x;
+        for (int k = 0; k < 3; ++k) {
+            const int yy = y + k - 1;
+            const bool out = (unsigned)yy >= (unsigned)g.ny;
+            r[k] = (long long)(!out ? yy : g.bcy == BC_PER ? yy - (k - 1) * g.ny : y) * g.nx;
+            wy[k] = out && g.bcy == BC_WALL;
+            sy[k] = out && g.bcy == BC_SYM;
+        }
+    }
+
+    template <typename R>
+    __device__ __forceinline__ R at(const R *base, long long off, int col) const
+    {
+        if constexpr (ROWU)
+            return *lane_ptr(base, off, col);
+        else
+            return gld(base, off + col);
+    }
+
+    template <typename R>
+    __device__ __forceinline__ void load(const R *base, long long np, R (&v)[9]) const
+    {
+#pragma unroll
+        for (int a = 0; a < 9; ++a) {
+            const int cx = cx_of(a), cy = cy_of(a), k = 1 - cy;
+            const int xs = cx == 0 ? x : cx > 0 ? xm : xp;
+            if constexpr (ROWU) {
+                const int dir = wy[k] ? 8 - a : sy[k] ? a - 6 * cy : a;
+                v[a] = at(base, dir * np + r[k], wy[k] ? x : xs);
+            } else {
+                const bool ex = cx > 0 ? lo : cx < 0 ? hi : false;
+                const bool bb = wy[k] || (wx && ex);
+                const int dir = bb ? 8 - a : a - (sy[k] ? 6 * cy : 0) - (sx && ex ? 2 * cx : 0);
+                v[a] = at(base, dir * np + (bb ? r[1] : r[k]), bb ? x : xs);
+            }
+        }
+        if constexpr (ROWU) {
+            if ((wx || sx) && __any(lo || hi)) {
+#pragma unroll
+                for (int a = 0; a < 9; ++a) {
+                    const int cx = cx_of(a), cy = cy_of(a), k = 1 - cy;
+                    if (cx == 0) continue;
+                    if (!(cx > 0 ? lo : hi)) continue;
+                    const bool bb = wx || wy[k];
+                    const int b = bb ? 8 - a : a - 2 * cx - (sy[k] ? 6 * cy : 0);
+                    v[a] = at(base, b * np + (bb ? r[1] : r[k]), x);
+                }
+            }
+        }
+    }
+};
+
+// phi as k_phi sums it: the pulled values in direction order.
+template <typename T>
+__device__ __forceinline__ T phi_sum9(const T (&v)[9])
+{
+    T s = 0;
+#pragma unroll
+    for (int a = 0; a < 9; ++a) s += v[a];
+    return s;
+}
+
+// Tile: 256 threads, as wide as the lattice up to a wavefront (2^3 .. 2^6
+// cells); its slots in LDS with the ring.
+constexpr int STEP2D_THREADS = 256;
+__host__ __device__ inline int step2d_width(int nx)
+{
+    int l = 3;
+    while (l < 6 && (1 << l) < nx) ++l;
+    return l;
+}
+constexpr int step2d_slots()
+{
+    int most = 0;
+    for (int bx = 8; bx <= 64; bx *= 2) {
+        const int n = (bx + 2) * (STEP2D_THREADS / bx + 2);
+        most = n > most ? n : most;
+    }
+    return most;
+}
+
+// One tile from (x0, y0), bx = 2^lbx cells wide, 256 / bx rows high.
+// KEPT: the populations are stored to stay in the Infinity Cache (kept_in_cache).
+// flag, if given: or-ed with 1 where phi is not finite.
+// Every thread of the block calls it (it holds a barrier).  ROWU: bx = 64, a
+// wavefront per row; the rows below and above the tile are summed by the
+// first two wavefronts in row form, the columns beside it by the third.
+template <class P, int COLL, bool ROWU, bool KEPT>
+__device__ __forceinline__ void step2d_tile(const Geom &g, const Phys<typename P::T> &ph, const Ptrs &p,
+                                            typename P::T *lphi, int lbx, int x0, int y0,
+                                            int *flag = nullptr)
+{
+    using T = typename P::T;
+    const int bx = ROWU ? 64 : 1 << lbx, by = STEP2D_THREADS / bx, ls = bx + 2;
+    const int tid = int(threadIdx.x);
+    const int tx = tid & (bx - 1);
+    const int ty = ROWU ? __builtin_amdgcn_readfirstlane(tid >> 6) : tid >> lbx;
+    const int w = min(bx, g.nx - x0), h = min(by, g.ny - y0);
+    const T *F = static_cast<const T *>(p.Fin), *G = static_cast<const T *>(p.Gin);
+    // slot (i, j) of the tile, i, j from -1
+    auto slot = [&](int i, int j) { return lphi + (j + 1) * ls + i + 1; };
+    const bool active = tx < w && ty < h;
+    const int x = x0 + tx, y = y0 + ty;
+    NbTile<T, KEPT> nb;
+    if (active) {
+        const Pull2d<ROWU> c(g, x, y);
+        c.load(G, g.np, nb.gp);
+        c.load(F, g.np, nb.f);
+    }
+    // the ring: beyond walls and symmetry planes the mirrored cell's phi
+    auto ring = [&](auto rowu, int i, int j) {
+        T v[9];
+        const Pull2d<decltype(rowu)::value> c(g, stencil_coord(x0 + i, g.nx, g.bcx),
+                                              stencil_coord(y0 + j, g.ny, g.bcy));
+        c.load(G, g.np, v);
+        *slot(i, j) = phi_sum9(v);
+    };
+    if constexpr (ROWU) {
+        if (ty < 2) {
+            if (tx < w) ring(std::true_type{}, tx, ty == 0 ? -1 : h);
+        } else if (ty == 2) {
+            const int n = h + 2;
+            if (tx < 2 * n) ring(std::false_type{}, tx < n ? -1 : w, (tx < n ? tx : tx - n) - 1);
+        }
+    } else {
+        if (tid < 2 * (w + 2 + h)) {
+            const int k = tid - 2 * (w + 2);
+            if (k < 0)
+                ring(std::false_type{}, (tid < w + 2 ? tid : tid - (w + 2)) - 1, tid < w + 2 ? -1 : h);
+            else
+                ring(std::false_type{}, k < h ? -1 : w, k < h ? k : k - h);
+        }
+    }
+    if (active) {
+        const T s = phi_sum9(nb.gp);
+        *slot(tx, ty) = s;
+        if (flag && !__builtin_isfinite(s)) atomicOr(flag, 1);
+    }
+    __syncthreads();
+    if (!active) return;
+    nb.row = y * g.nx;
+    nb.x = x;
+    nb.lphi = slot(tx, ty);
+    nb.ls = ls;
+    collide_body<2, P, COLL>(nb, g, ph, p);
+}
+
+}  // namespace mplb
