@@ -148,6 +148,21 @@ __device__ __forceinline__ PullLoc pull_loc(const NbRow &n, int a)
     return l;
 }
 
+// Packed form: z as in the row form, x and y through the cell's in-plane indices.
+template <int D>
+__device__ __forceinline__ PullLoc pull_loc(const NbPack &n, int a)
+{
+    static_assert(D == 3, "3-D only");
+    const int cx = cx_of(a), cy = cy_of(a), cz = cz_of<D>(a), kz = 1 - cz;
+    const unsigned bz = cz ? 1u << (3 + kz) : 0u;
+    PullLoc l;
+    l.bb = (n.bb & bz) != 0;
+    l.dir = l.bb ? opposite<D>(a) : a - ((n.sym & bz) ? 18 * cz : 0);
+    l.rs = l.bb ? n.row : n.rz[kz];
+    l.xs = l.bb ? n.x : n.off[(1 - cx) + 3 * (1 - cy)];
+    return l;
+}
+
 // Element (plane offset + location) of a device array, global access.  NT:
 // a non-temporal load (the value is read once, by this cell).
 template <bool NT = false, typename R>
@@ -161,6 +176,15 @@ __device__ __forceinline__ R load_loc(const NbLane &, const R *base, long long p
 }
 template <bool NT = false, typename R>
 __device__ __forceinline__ R load_loc(const NbRow &, const R *base, long long plane,
+                                      const PullLoc &l)
+{
+    if constexpr (NT)
+        return __builtin_nontemporal_load(lane_ptr(base, plane + l.rs, l.xs));
+    else
+        return *lane_ptr(base, plane + l.rs, l.xs);
+}
+template <bool NT = false, typename R>
+__device__ __forceinline__ R load_loc(const NbPack &, const R *base, long long plane,
                                       const PullLoc &l)
 {
     if constexpr (NT)
@@ -210,6 +234,13 @@ __device__ __forceinline__ bool wall_out(const NbLane &n, int a)
            (D == 3 && cz_of<D>(a) && out(n.z + cz_of<D>(a), g.nz, g.bcz));
 }
 
+template <int D>
+__device__ __forceinline__ bool wall_out(const NbPack &n, int a)
+{
+    const int cz = cz_of<D>(a);
+    return cz && (n.bb & (1u << (4 + cz))) != 0;
+}
+
 // phi at the stencil neighbour (x + cx, y + cy, z + cz): periodic wrap, or the
 // mirrored first fluid layer beyond walls and symmetry planes.
 template <typename T>
@@ -229,13 +260,18 @@ __device__ __forceinline__ T phi_at(const NbRow &n, const T *phi, int cx, int cy
     return *lane_ptr(phi, (long long)(n.ry[1 + cy] + n.rz[1 + cz]), xx);
 }
 
+template <typename T>
+__device__ __forceinline__ T phi_at(const NbPack &n, const T *phi, int cx, int cy, int cz)
+{
+    return *lane_ptr(phi, (long long)n.rz[1 + cz], n.off[(1 + cx) + 3 * (1 + cy)]);
+}
+
 // Cell of the one-launch 2-D step (step2d.hpp): the order parameter comes
 // from the block's LDS tile (lphi at the cell's own slot, rows ls slots apart)
 // and the pulled populations of both sets are already in registers.  row, x:
 // where its values are stored.
 template <typename T, bool KEPT>
 struct NbTile {
-    static constexpr bool kept = KEPT;
     int row, x;
     const T *lphi;
     int ls;
@@ -252,20 +288,23 @@ __device__ __forceinline__ T phi_at(const NbTile<T, KEPT> &n, const T *, int cx,
     return n.lphi[cy * n.ls + cx];
 }
 
+template <class NB>
+constexpr bool is_kept = false;
+template <class NB>
+constexpr bool is_kept<Kept<NB>> = true;
+template <typename T>
+constexpr bool is_kept<NbTile<T, true>> = true;
+
 // Stores a post-collision value: non-temporally, or (a form whose kept is set)
 // as an ordinary store, which leaves it in the Infinity Cache for the next
-// step.
+// step (is_kept).
 template <class NB, typename V, typename E>
 __device__ __forceinline__ void store_out(V v, gptr<E> at)
 {
-    if constexpr (in_tile<NB>) {
-        if constexpr (NB::kept)
-            *at = v;
-        else
-            __builtin_nontemporal_store(v, at);
-    } else {
+    if constexpr (is_kept<NB>)
+        *at = v;
+    else
         __builtin_nontemporal_store(v, at);
-    }
 }
 
 // Pre-collision population a of a set in plain storage, where the cell's form
@@ -386,6 +425,11 @@ __device__ __forceinline__ R own_at(const NbLane &n, const R *base)
     return gld(base, n.me);
 }
 template <typename R>
+__device__ __forceinline__ R own_at(const NbPack &n, const R *base)
+{
+    return *lane_ptr(base, n.row, n.x);
+}
+template <typename R>
 __device__ __forceinline__ R own_at(const NbRow &n, const R *base)
 {
     return *lane_ptr(base, n.row, n.x);
@@ -406,7 +450,7 @@ template <bool BUF, class NB>
 __device__ __forceinline__ void store_code(const NB &, void *base, long long plane, int row, int x,
                                            unsigned short bits)
 {
-    if constexpr (BUF && std::is_same<NB, NbRow>::value) {
+    if constexpr (BUF && !std::is_base_of<NbLane, NB>::value) {
         // raw buffer (stride 0) without a range limit; word 3 as gfx9 takes it for
         // untyped accesses; cache policy 2: non-temporal
         const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(
@@ -546,7 +590,11 @@ __device__ __forceinline__ void velocity(Cell<T> &c)
 // the first store (true) or pair by pair (false).  The FP16 formats always
 // preload (measured: the FP16S update 742 -> 642 us on 128 x 128 x 512); the
 // FP32 update is faster without (697 against 715 us: the registers it
-// would hold cost occupancy).
+// would hold cost occupancy).  Lattices small enough for the Infinity Cache
+// leave a SIMD two to nine wavefronts, so the chain of loads waiting on stores
+// costs more than the registers: 32 x 32 x 128 FP32 18.2 us a step without,
+// 16.6 with, 16.1 with these loads issued first; 40 x 40 x 160 FP64 49.6, 46.9
+// and 47.2.
 constexpr bool CAC_PRELOAD = false;
 
 // Two schedules of the same pass.  paired: each pair's loads beside its
@@ -914,7 +962,7 @@ __device__ __forceinline__ void store_phi(const NB &nb, const Ptrs &p, typename 
         __builtin_nontemporal_store(make_rec(v, own_at(nb, static_cast<const unsigned *>(p.ref))),
                                     lane_ptr(static_cast<unsigned long long *>(p.phi), nb.row, nb.x));
     else
-        __builtin_nontemporal_store(v, lane_ptr(static_cast<T *>(p.phi), nb.row, nb.x));
+        store_out<NB>(v, lane_ptr(static_cast<T *>(p.phi), nb.row, nb.x));
 }
 
 template <int D, class P, class NB>
@@ -990,6 +1038,17 @@ __device__ __forceinline__ void collide_body(const NB &nb, const Geom &g,
     const int row = nb.row, xl = nb.x;
 
     Cell<T> c;
+    // the pulled phase-field values of a lattice in the Infinity Cache: loaded
+    // before the stores, in FP32 before everything else (see CAC_PRELOAD)
+    constexpr bool kept3 = is_kept<NB> && !in_tile<NB>;
+    constexpr bool early = kept3 && sizeof(T) == 4;
+    constexpr bool preload = P::F::shifted || P::G::shifted || kept3 || CAC_PRELOAD;
+    T pre[preload ? Q : 1];
+    if constexpr (early) {
+#pragma unroll
+        for (int a = 0; a < Q; ++a)
+            if (a != Q / 2) pre[a] = pull<D, typename P::G, T>(nb, p.Gin, g.np, a);
+    }
     // FP16 phase-field storage: fp16 order parameters of the cells that read
     // the phase-field values stored here (see eval_cell16_paired)
     unsigned gref[P::G::shifted ? Q / 2 : 1];
@@ -1206,9 +1265,7 @@ __device__ __forceinline__ void collide_body(const NB &nb, const Geom &g,
             // the pulled values: all loads issued before the first store (the
             // compiler cannot prove the stored set apart from the pulled one,
             // and would otherwise wait on each pair before storing it)
-            constexpr bool preload = P::F::shifted || P::G::shifted || CAC_PRELOAD;
-            T pre[preload ? Q : 1];
-            if constexpr (preload) {
+            if constexpr (preload && !early) {
 #pragma unroll
                 for (int a = 0; a < Q; ++a) {
                     if (a == Q / 2) continue;
@@ -1286,22 +1343,38 @@ __device__ __forceinline__ void collide_cell(const Geom &g, const Phys<typename 
     collide_body<D, P, COLL>(nb, g, ph, p);
 }
 
-template <bool ROW>
-using NbOf = typename std::conditional<ROW, NbRow, NbLane>::type;
+// Addressing of a launch: per lane, rows, or packed planes (3-D).
+enum { FORM_LANE, FORM_ROW, FORM_PACK };
+template <int FORM>
+using NbOf = typename std::conditional<FORM == FORM_PACK, NbPack,
+             typename std::conditional<FORM == FORM_ROW, NbRow, NbLane>::type>::type;
 
 // Thread -> cell for a block starting at (x0, y0, z0).  ROW: the block is a
 // multiple of 64 wide in x, so each wavefront lies in one x-row and y, z are
 // taken from its first lane as wavefront-uniform values.
-template <bool ROW>
+template <int FORM>
 __device__ __forceinline__ void thread_cell(int x0, int y0, int z0, int &x, int &y, int &z)
 {
     x = x0 + int(threadIdx.x);
     y = y0 + int(threadIdx.y);
     z = z0 + int(threadIdx.z);
-    if constexpr (ROW) {
+    if constexpr (FORM == FORM_ROW) {
         y = __builtin_amdgcn_readfirstlane(y);
         z = __builtin_amdgcn_readfirstlane(z);
     }
+}
+
+// Packed form: thread -> cell, PACK_THREADS consecutive cells of a plane per
+// block.  False where the block reaches past the plane.
+constexpr int PACK_THREADS = 256;
+__device__ __forceinline__ bool pack_cell(const Geom &g, int block, int &x, int &y, int &z)
+{
+    const int plane = g.nx * g.ny, per = (plane + PACK_THREADS - 1) / PACK_THREADS;
+    z = __builtin_amdgcn_readfirstlane(block / per);
+    const int c = (block - z * per) * PACK_THREADS + int(threadIdx.x);
+    y = c / g.nx;
+    x = c - y * g.nx;
+    return c < plane;
 }
 
 
@@ -1352,7 +1425,7 @@ __device__ __forceinline__ long long nphi_edge_at(const Geom &g, int ntiles, int
 // as destination (row ty of tile t, planes z - 1 .. z + 1) and, in the first
 // and last tile rows, for the neighbouring tiles' edge rows.  BX: the row
 // length nx, or 0 for a run-time one (bx_rt).
-template <class P, int BX, int B>
+template <class P, int BX, int B, class NB>
 __device__ __forceinline__ void nphi_gather(const Geom &g, const NextPhi &q,
                                             const typename P::T *lds, typename P::T rest, int x,
                                             int xm, int xp, int t, int ty, int y, int z, int bx_rt)
@@ -1397,19 +1470,19 @@ __device__ __forceinline__ void nphi_gather(const Geom &g, const NextPhi &q,
             }
         }
         // non-temporal, as the populations: the merge reads them a launch later
-        __builtin_nontemporal_store(s, lane_ptr(part, (long long)(oz + 1) * g.np + (zd * g.ny + y) * g.nx, x));
+        store_out<NB>(s, lane_ptr(part, (long long)(oz + 1) * g.np + (zd * g.ny + y) * g.nx, x));
         if (ty == 0 && (!wy || t > 0)) {
             T e = 0;
 #pragma unroll
             for (int ox = -1; ox <= 1; ++ox) e += V((ox + 1) + 9 * (oz + 1), 0, ox + 1);
-            __builtin_nontemporal_store(
+            store_out<NB>(
                 e, lane_ptr(edge, nphi_edge_at(g, ntiles, 1, oz, t > 0 ? t - 1 : ntiles - 1, zd, 0), x));
         }
         if (ty == by - 1 && (!wy || t < ntiles - 1)) {
             T e = 0;
 #pragma unroll
             for (int ox = -1; ox <= 1; ++ox) e += V((ox + 1) + 6 + 9 * (oz + 1), by - 1, ox + 1);
-            __builtin_nontemporal_store(
+            store_out<NB>(
                 e, lane_ptr(edge, nphi_edge_at(g, ntiles, 0, oz, t < ntiles - 1 ? t + 1 : 0, zd, 0), x));
         }
     }
@@ -1420,7 +1493,7 @@ __device__ __forceinline__ void nphi_gather(const Geom &g, const NextPhi &q,
 // thread (x, ty).  Every thread of the block calls it (it holds a barrier);
 // threads with active false (rows beyond the tile in a larger block) only
 // take part in the barrier.  BX as for nphi_gather.
-template <class P, int COLL, int BX>
+template <class P, int COLL, int BX, class NB = NbRow>
 __device__ __forceinline__ void nphi_tile(const Geom &g, const Phys<typename P::T> &ph,
                                           const Ptrs &p, const NextPhi &q, typename P::T *lds,
                                           int bx_rt, int t, int ty, int x, int z, bool active)
@@ -1428,7 +1501,6 @@ __device__ __forceinline__ void nphi_tile(const Geom &g, const Phys<typename P::
     using T = typename P::T;
     const int bx = BX ? BX : bx_rt, RS = 26 * bx;
     const int y = __builtin_amdgcn_readfirstlane(t * q.by + ty);
-    using NB = NbRow;
     NB nb;
     T rest = 0;
     if (active) {
@@ -1441,9 +1513,9 @@ __device__ __forceinline__ void nphi_tile(const Geom &g, const Phys<typename P::
     // the first tile row, which reads no row above): every LDS offset is a
     // non-negative constant when BX is
     if (ty == 0)
-        nphi_gather<P, BX, 0>(g, q, lds, rest, x, nb.xm, nb.xp, t, ty, y, z, bx_rt);
+        nphi_gather<P, BX, 0, NB>(g, q, lds, rest, x, nb.xm, nb.xp, t, ty, y, z, bx_rt);
     else
-        nphi_gather<P, BX, 1>(g, q, lds, rest, x, nb.xm, nb.xp, t, ty, y, z, bx_rt);
+        nphi_gather<P, BX, 1, NB>(g, q, lds, rest, x, nb.xm, nb.xp, t, ty, y, z, bx_rt);
 }
 
 // The pieces of one cell's phi in a fixed order: for source planes z + 1, z,
@@ -1567,6 +1639,26 @@ inline hipError_t dispatch(const Ctx &c, Fn &&fn)
     return hipErrorInvalidValue;
 }
 
+// Packed planes on 3-D lattices periodic in x and y whose rows are not whole
+// wavefronts, the arrays within 32-bit indices: where the populations stay in
+// the Infinity Cache, and elsewhere where rows would fill less than 3/4 of
+// their blocks (300 x 100 x 100 FP32, 59%: 534 us a step in rows, 342 packed;
+// 96 x 96 x 384, 75%: 364 and 374, a packed wavefront's loads crossing the ends
+// of rows).
+inline bool pack_form(const Ctx &c)
+{
+    if (c.dim != 3 || c.g.bcx != BC_PER || c.g.bcy != BC_PER || c.g.nx % 64 == 0 ||
+        27 * c.g.np >= (1ll << 31))
+        return false;
+    if (kept_in_cache(3, c.storage, c.g.np)) return true;
+    const int bx = int(c.block.x);
+    return bx % 64 != 0 || 4ll * c.g.nx < 3ll * ((c.g.nx + bx - 1) / bx * bx);
+}
+inline unsigned pack_blocks(const Geom &g)
+{
+    const int plane = g.nx * g.ny;
+    return unsigned((plane + PACK_THREADS - 1) / PACK_THREADS) * unsigned(g.nz);
+}
 inline bool row_form(const Ctx &c) { return row_form_ok(c.dim, c.g, c.block); }
 
 // Compile-time operator selection: bit 0 of COLL the flow collision, bit 1

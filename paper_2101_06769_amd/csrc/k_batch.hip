@@ -40,11 +40,11 @@ __attribute__((amdgpu_waves_per_eu(PHI ? 1 : collide_waves<D, P, COLL>()))) kb_s
             const T ph = (D == 3 && nby && t >= doms[tl.dom].nphi_from)
                              ? nphi_merge_cell<P>(g, p, NextPhi{doms[tl.dom].npart,
                                                                 doms[tl.dom].nedge, nby}, x, y, z)
-                             : phi_cell<D, P, NbOf<ROW>>(g, p, x, y, z);
+                             : phi_cell<D, P, NbOf<ROW ? FORM_ROW : FORM_LANE>>(g, p, x, y, z);
             if (!__builtin_isfinite(ph)) atomicOr(status + tl.dom, 1);
         } else {
             const Phys<T> ph = to_phys<T>(doms[tl.dom].ph);
-            collide_cell<D, P, COLL, NbOf<ROW>>(g, ph, p, x, y, z);
+            collide_cell<D, P, COLL, NbOf<ROW ? FORM_ROW : FORM_LANE>>(g, ph, p, x, y, z);
         }
     }
 }

@@ -18,18 +18,26 @@ int nphi_rows(int nx, int ny, int storage)
     return 1;
 }
 // BX = nx, a compile-time row length so that every LDS offset is an immediate.
-template <class P, int COLL, int BX>
+template <class P, int COLL, int BX, class NB>
 __global__ void __launch_bounds__(NPHI_THREADS) __attribute__((amdgpu_waves_per_eu(collide_waves<3, P, COLL>())))
 k_collide_nphi(Geom g, Phys<typename P::T> ph, Ptrs p, NextPhi q)
 {
     using T = typename P::T;
     extern __shared__ double nphi_lds[];
-    nphi_tile<P, COLL, BX>(g, ph, p, q, reinterpret_cast<T *>(nphi_lds), BX, int(blockIdx.y),
+    nphi_tile<P, COLL, BX, NB>(g, ph, p, q, reinterpret_cast<T *>(nphi_lds), BX, int(blockIdx.y),
                            __builtin_amdgcn_readfirstlane(int(threadIdx.y)), int(threadIdx.x),
                            __builtin_amdgcn_readfirstlane(int(blockIdx.z)), true);
 }
 
-template <class P>
+// Kept lattices (kept_in_cache) leave phi in the cache as their populations;
+// the partial sums are read once in either case, but from the cache.
+template <bool KEPT, typename T>
+__device__ __forceinline__ T merge_load(gptr<const T> at)
+{
+    return KEPT ? *at : __builtin_nontemporal_load(at);
+}
+
+template <class P, class NB>
 __global__ void __launch_bounds__(256) k_phi_merge(Geom g, Ptrs p, NextPhi q)
 {
     using T = typename P::T;
@@ -54,9 +62,9 @@ __global__ void __launch_bounds__(256) k_phi_merge(Geom g, Ptrs p, NextPhi q)
             const bool ok = z < g.nz && !(wz && (zs < 0 || zs >= g.nz));
             const long long row = (long long)(z * g.ny + y) * g.nx;
             // every partial sum and edge value is read once: non-temporal
-            v[k][oz + 1][0] = ok ? __builtin_nontemporal_load(lane_ptr(part, (oz + 1) * g.np + row, x)) : T(0);
-            v[k][oz + 1][1] = ok && first ? __builtin_nontemporal_load(lane_ptr(edge, nphi_edge_at(g, ntiles, 0, oz, t, z, 0), x)) : T(0);
-            v[k][oz + 1][2] = ok && last ? __builtin_nontemporal_load(lane_ptr(edge, nphi_edge_at(g, ntiles, 1, oz, t, z, 0), x)) : T(0);
+            v[k][oz + 1][0] = ok ? merge_load<is_kept<NB>, T>(lane_ptr(part, (oz + 1) * g.np + row, x)) : T(0);
+            v[k][oz + 1][1] = ok && first ? merge_load<is_kept<NB>, T>(lane_ptr(edge, nphi_edge_at(g, ntiles, 0, oz, t, z, 0), x)) : T(0);
+            v[k][oz + 1][2] = ok && last ? merge_load<is_kept<NB>, T>(lane_ptr(edge, nphi_edge_at(g, ntiles, 1, oz, t, z, 0), x)) : T(0);
         }
     }
 #pragma unroll
@@ -71,7 +79,7 @@ __global__ void __launch_bounds__(256) k_phi_merge(Geom g, Ptrs p, NextPhi q)
             __builtin_nontemporal_store(make_rec(s, *lane_ptr(static_cast<const unsigned *>(p.ref), row, x)),
                                         lane_ptr(static_cast<unsigned long long *>(p.phi), row, x));
         else
-            __builtin_nontemporal_store(s, lane_ptr(static_cast<T *>(p.phi), row, x));
+            store_out<NB>(s, lane_ptr(static_cast<T *>(p.phi), row, x));
     }
 }
 
@@ -106,17 +114,24 @@ hipError_t launch_collide_nphi(const Ctx &c, const NextPhi &q)
                                        c.p, q);
                     return hipGetLastError();
                 };
-                switch (c.g.nx) {
-                case 64: return go(k_collide_nphi<P, COLL, 64>);
-                case 128: return go(k_collide_nphi<P, COLL, 128>);
-                case 192: return go(k_collide_nphi<P, COLL, 192>);
-                case 256: return go(k_collide_nphi<P, COLL, 256>);
-                case 512:
-                    // one row per tile: 512 threads, FP32 arithmetic only
-                    if constexpr (sizeof(T) == 4) return go(k_collide_nphi<P, COLL, 512>);
-                    break;
+                auto by_width = [&]<class NB>() {
+                    switch (c.g.nx) {
+                    case 64: return go(k_collide_nphi<P, COLL, 64, NB>);
+                    case 128: return go(k_collide_nphi<P, COLL, 128, NB>);
+                    case 192: return go(k_collide_nphi<P, COLL, 192, NB>);
+                    case 256: return go(k_collide_nphi<P, COLL, 256, NB>);
+                    case 512:
+                        // one row per tile: 512 threads, FP32 arithmetic only
+                        if constexpr (sizeof(T) == 4) return go(k_collide_nphi<P, COLL, 512, NB>);
+                        break;
+                    }
+                    return hipErrorInvalidValue;
+                };
+                if constexpr (!P::F::shifted) {
+                    if (kept_in_cache(3, c.storage, c.g.np))
+                        return by_width.template operator()<Kept<NbRow>>();
                 }
-                return hipErrorInvalidValue;
+                return by_width.template operator()<NbRow>();
             });
         }
     });
@@ -128,9 +143,14 @@ hipError_t launch_phi_merge(const Ctx &c, const NextPhi &q)
     return dispatch(c, [&]<int D, class P>() {
         constexpr int MERGE_Z = merge_planes<P>();
         const dim3 grid(c.g.nx / 64, (c.g.ny + 3) / 4, (c.g.nz + MERGE_Z - 1) / MERGE_Z);
-        hipLaunchKernelGGL((k_phi_merge<P>), grid, dim3(64, 4, 1), 0, c.stream, c.g,
-                           c.p, q);
-        return hipGetLastError();
+        auto go = [&](auto kernel) {
+            hipLaunchKernelGGL(kernel, grid, dim3(64, 4, 1), 0, c.stream, c.g, c.p, q);
+            return hipGetLastError();
+        };
+        if constexpr (!P::F::shifted) {
+            if (kept_in_cache(3, c.storage, c.g.np)) return go(k_phi_merge<P, Kept<NbRow>>);
+        }
+        return go(k_phi_merge<P, NbRow>);
     });
 }
 

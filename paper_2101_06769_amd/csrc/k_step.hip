@@ -4,25 +4,41 @@
 
 namespace mplb {
 
-template <int D, class P, bool ROW>
+template <int FORM, bool KEPT>
+__device__ __forceinline__ bool block_cell(const Geom &g, int &x, int &y, int &z)
+{
+    if constexpr (FORM == FORM_PACK) {
+        // lattices in the Infinity Cache: XCD k takes the k-th eighth of the
+        // blocks, as k_step2d (48 x 48 x 192 FP32 46.0 -> 42.5 us a step;
+        // larger ones stream better in plain order: 96 x 96 x 384 374 -> 379)
+        int bid = int(blockIdx.x);
+        if constexpr (KEPT) {
+            const int per = int(gridDim.x) >> 3;
+            if (bid < per * 8) bid = (bid & 7) * per + (bid >> 3);
+        }
+        return pack_cell(g, bid, x, y, z);
+    } else {
+        thread_cell<FORM>(blockIdx.x * blockDim.x, blockIdx.y * blockDim.y, blockIdx.z * blockDim.z, x,
+                          y, z);
+        return x < g.nx && y < g.ny && z < g.nz;
+    }
+}
+
+template <int D, class P, class NB, int FORM>
 __global__ void __launch_bounds__(256) k_phi(Geom g, Ptrs p)
 {
     int x, y, z;
-    thread_cell<ROW>(blockIdx.x * blockDim.x, blockIdx.y * blockDim.y, blockIdx.z * blockDim.z, x,
-                     y, z);
-    if (x >= g.nx || y >= g.ny || z >= g.nz) return;
-    phi_cell<D, P, NbOf<ROW>>(g, p, x, y, z);
+    if (!block_cell<FORM, is_kept<NB>>(g, x, y, z)) return;
+    phi_cell<D, P, NB>(g, p, x, y, z);
 }
 
-template <int D, class P, int COLL, bool ROW>
+template <int D, class P, int COLL, class NB, int FORM>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(collide_waves<D, P, COLL>())))
 k_collide(Geom g, Phys<typename P::T> ph, Ptrs p)
 {
     int x, y, z;
-    thread_cell<ROW>(blockIdx.x * blockDim.x, blockIdx.y * blockDim.y, blockIdx.z * blockDim.z, x,
-                     y, z);
-    if (x >= g.nx || y >= g.ny || z >= g.nz) return;
-    collide_cell<D, P, COLL, NbOf<ROW>>(g, ph, p, x, y, z);
+    if (!block_cell<FORM, is_kept<NB>>(g, x, y, z)) return;
+    collide_cell<D, P, COLL, NB>(g, ph, p, x, y, z);
 }
 
 // Row-form addressing: every wavefront inside one x-row of the block, x
@@ -47,14 +63,32 @@ bool kept_in_cache(int dim, int storage, long long np)
     return 2 * (dim == 2 ? 9 : 27) * np * (f + gg) <= (256ll << 20);
 }
 
+// Calls fn.template operator()<NB, FORM>(grid, block) for the form of a launch
+// over the context's cells.
+template <int D, class P, class Fn>
+static hipError_t with_form(const Ctx &c, Fn &&fn)
+{
+    auto go = [&]<int FORM>(dim3 grid, dim3 block) {
+        using NB = NbOf<FORM>;
+        if constexpr (!P::F::shifted && D == 3) {
+            if (kept_in_cache(3, c.storage, c.g.np)) return fn.template operator()<Kept<NB>, FORM>(grid, block);
+        }
+        return fn.template operator()<NB, FORM>(grid, block);
+    };
+    if constexpr (D == 3) {
+        if (pack_form(c)) return go.template operator()<FORM_PACK>(dim3(pack_blocks(c.g)), dim3(PACK_THREADS));
+    }
+    return row_form(c) ? go.template operator()<FORM_ROW>(grid_for(c), c.block)
+                       : go.template operator()<FORM_LANE>(grid_for(c), c.block);
+}
+
 hipError_t launch_phi(const Ctx &c)
 {
     return dispatch(c, [&]<int D, class P>() {
-        if (row_form(c))
-            hipLaunchKernelGGL((k_phi<D, P, true>), grid_for(c), c.block, 0, c.stream, c.g, c.p);
-        else
-            hipLaunchKernelGGL((k_phi<D, P, false>), grid_for(c), c.block, 0, c.stream, c.g, c.p);
-        return hipGetLastError();
+        return with_form<D, P>(c, [&]<class NB, int FORM>(dim3 grid, dim3 block) {
+            hipLaunchKernelGGL((k_phi<D, P, NB, FORM>), grid, block, 0, c.stream, c.g, c.p);
+            return hipGetLastError();
+        });
     });
 }
 
@@ -66,22 +100,18 @@ hipError_t launch_collide(const Ctx &c)
         if constexpr (D == 2 && !P::F::shifted) {
             return hipErrorInvalidValue;
         } else {
-            const bool row = row_form(c);
             return with_coll(coll_code(c.ph), [&](auto cc) {
                 constexpr int COLL = decltype(cc)::value;
-                // dynamic LDS: single relaxation time's flow values (3-D)
-                const size_t lds = srt_lds_bytes<D, P, COLL>(c.block.x * c.block.y * c.block.z);
-                if (row)
-                    hipLaunchKernelGGL((k_collide<D, P, COLL, true>), grid_for(c), c.block, lds,
-                                       c.stream, c.g, to_phys<T>(c.ph), c.p);
-                else
-                    hipLaunchKernelGGL((k_collide<D, P, COLL, false>), grid_for(c), c.block, lds,
-                                       c.stream, c.g, to_phys<T>(c.ph), c.p);
-                return hipGetLastError();
+                return with_form<D, P>(c, [&]<class NB, int FORM>(dim3 grid, dim3 block) {
+                    // dynamic LDS: single relaxation time's flow values (3-D)
+                    const size_t lds = srt_lds_bytes<D, P, COLL>(block.x * block.y * block.z);
+                    hipLaunchKernelGGL((k_collide<D, P, COLL, NB, FORM>), grid, block, lds, c.stream, c.g,
+                                       to_phys<T>(c.ph), c.p);
+                    return hipGetLastError();
+                });
             });
         }
     });
 }
-
 
 }  // namespace mplb

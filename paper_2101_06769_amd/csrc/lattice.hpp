@@ -122,10 +122,62 @@ struct NbRow {
     unsigned bb, sym;
 };
 
+// Packed form, for 3-D lattices periodic in x and y whose population arrays
+// have fewer than 2^31 elements: a block takes consecutive cells of one plane,
+// whatever the row length, so no lane is idle but in a plane's last block.
+// z is block-uniform and its rules are taken into scalar tables as in the row
+// form; x and y differ by lane and only wrap, through nine in-plane indices
+// shared by the stencil and the pulls of both sets.  row = z nx ny is the
+// offset of the cell's plane, x its index in the plane.
+struct NbPack {
+    int x, row;
+    int off[9];  // index of (x + i - 1, y + j - 1) at i + 3 j
+    int rz[3];
+    unsigned bb, sym;  // bits 3 .. 5, as NbRow
+};
+
+// A form whose post-collision values stay in the Infinity Cache until the next
+// step reads them (see kept_in_cache): stored with ordinary stores.
+template <class NB>
+struct Kept : NB {
+    static constexpr bool kept = true;
+};
+
 __device__ __forceinline__ NbLane make_nb(const Geom &g, int x, int y, int z, NbLane *)
 {
     const int row = (z * g.ny + y) * g.nx;
     return NbLane{&g, x, y, z, row, row + x};
+}
+
+__device__ __forceinline__ NbPack make_nb(const Geom &g, int x, int y, int z, NbPack *)
+{
+    NbPack n;
+    const int nxny = g.nx * g.ny;
+    n.row = z * nxny;
+    n.x = y * g.nx + x;
+    const int xm = x == 0 ? g.nx - 1 : x - 1, xp = x == g.nx - 1 ? 0 : x + 1;
+    const int ym = (y == 0 ? g.ny - 1 : y - 1) * g.nx, yp = (y == g.ny - 1 ? 0 : y + 1) * g.nx;
+    const int yo = n.x - x;
+    n.off[0] = ym + xm; n.off[1] = ym + x; n.off[2] = ym + xp;
+    n.off[3] = yo + xm; n.off[4] = n.x;    n.off[5] = yo + xp;
+    n.off[6] = yp + xm; n.off[7] = yp + x; n.off[8] = yp + xp;
+    n.bb = 0;
+    n.sym = 0;
+#pragma unroll
+    for (int k = -1; k <= 1; ++k) {
+        const int zz = z + k;
+        const bool oz = (unsigned)zz >= (unsigned)g.nz;
+        n.rz[k + 1] = (!oz ? zz : g.bcz == BC_PER ? zz - k * g.nz : z) * nxny;
+        n.bb |= (oz && g.bcz == BC_WALL) ? 1u << (k + 4) : 0u;
+        n.sym |= (oz && g.bcz == BC_SYM) ? 1u << (k + 4) : 0u;
+    }
+    return n;
+}
+
+template <class NB>
+__device__ __forceinline__ Kept<NB> make_nb(const Geom &g, int x, int y, int z, Kept<NB> *)
+{
+    return Kept<NB>{make_nb(g, x, y, z, (NB *)nullptr)};
 }
 
 // y and z must be the same in every active lane of the wavefront.

@@ -1,0 +1,80 @@
+"""3-D lattices periodic in x and y whose rows are not whole wavefronts: the
+kernels take consecutive cells of a plane, so a wavefront spans rows and a
+plane's last block is partly empty.  One step against the FP64 oracle at the
+one-step bars (FP64 1e-12, FP32 2e-6) on rows of 1 to 130 cells, every boundary
+type in z, both collision operators, and both sides of the size up to which
+the populations are left in the Infinity Cache (256 MiB for both levels); the
+same rows beside walls in x or y, which take the general form; and lattices of
+whole wavefronts (the phi-summing update) on the small side of that size."""
+import numpy as np
+import pytest
+
+import oracle
+from paper_2101_06769_amd import inputs
+from tests.helpers import from_abi, gpu_available, rel_err
+from tests.test_gpu_degenerate import params_for
+from tests.test_gpu_parity import TOL1, gpu_solver, noisy_state
+
+pytestmark = pytest.mark.gpu
+
+if gpu_available():
+    from paper_2101_06769_amd import mplb
+
+
+def check(n, bc, storage, seed, steps=1, **kw):
+    params = params_for(3, n, bc)
+    params.update(kw)
+    phi, u, p = inputs.random_state(params, seed=seed)
+    po, f, g = noisy_state(params, phi, u, p, seed=seed + 1)
+    s = gpu_solver(params, storage, state=(f, g))
+    s.step(steps)
+    f1, g1 = oracle.step(po, f, g, steps)
+    ef = rel_err(from_abi(3, s.get_populations(0)), f1)
+    eg = rel_err(from_abi(3, s.get_populations(1)), g1)
+    assert ef < steps * TOL1[storage] and eg < steps * TOL1[storage], (n, bc, ef, eg)
+
+
+SIZES = [(1, 1, 1), (1, 3, 5), (2, 2, 2), (3, 7, 4), (16, 16, 3), (17, 15, 2), (63, 4, 3),
+         (65, 4, 2), (96, 5, 3), (100, 3, 4), (130, 2, 3)]
+
+
+@pytest.mark.parametrize("storage", ["fp64", "fp32"])
+@pytest.mark.parametrize("bcz", [0, 1, 2])
+def test_one_step_packed(storage, bcz):
+    for i, n in enumerate(SIZES):
+        check(n, (0, 0, bcz), storage, 60 + i, collision=i % 2)
+
+
+@pytest.mark.parametrize("bc", [(1, 0, 0), (0, 1, 1), (2, 0, 1), (0, 2, 0)])
+def test_one_step_beside_walls(bc):
+    for i, n in enumerate(SIZES[3:]):
+        check(n, bc, "fp64", 80 + i)
+
+
+@pytest.mark.parametrize("n", [(100, 100, 60), (100, 100, 64)])
+def test_one_step_around_the_cache_size(n):
+    # 432 B per cell in FP32: 259 MB (<= 256 MiB) and 276 MB
+    check(n, (0, 0, 1), "fp32", 7)
+
+
+@pytest.mark.parametrize("storage", ["fp64", "fp32"])
+@pytest.mark.parametrize("n,bc", [((64, 6, 5), (0, 1, 1)), ((128, 4, 3), (0, 0, 1)), ((256, 3, 4), (0, 0, 0))])
+def test_phi_summing_update_in_the_cache(storage, n, bc):
+    # the second step merges the first one's partial sums
+    check(n, bc, storage, 90, steps=2)
+
+
+def test_packed_first_order_equilibrium_equals_the_batch():
+    params = params_for(3, (36, 10, 9), (0, 0, 1))
+    params["cac_edf"] = 1
+    fields = inputs.random_state(params, seed=3)
+    a = mplb.Solver(params, storage="fp32")
+    a.init(*fields)
+    a.step(20)
+    b = mplb.Batch(3, "fp32", capacity=2, max_tiles=1 << 12)
+    s = mplb.Solver(params, storage="fp32", stream=b.stream)
+    s.init(*fields)
+    b.attach(s, 20)
+    b.step(20)
+    for w in (0, 1):
+        assert np.array_equal(a.get_populations(w), s.get_populations(w))
