@@ -14,6 +14,7 @@
 //   partials      reduction partial sums, result
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
 #include <cstring>
 #include <new>
@@ -882,25 +883,26 @@ struct mplb_batch {
     int *d_status;  // per slot: non-zero once the phi stage met a non-finite value
     // 2-D domains in plain storage: one launch per step over step2d tiles
     bool one_launch() const { return mplb::step2d_ok(dim, storage); }
-    int *d_tile0;            // running tile counts, capacity + 1 (see launch_batch_step2d)
-    std::vector<int> tile0;  // host copy
-    int grid2d;              // blocks: the tile count rounded up to a bucket
-    bool kept;               // the attached populations stay in the Infinity Cache
+    int *d_table2d;  // see launch_batch_step2d
     std::vector<mplb_solver *> slot;
     std::vector<mplb::BatchDom> doms;
     std::vector<mplb::BatchTile> tiles;
-    // tile list: [0, ntiles_host) block tiles of the domains updated by the
-    // block kernels (phi stage and update); [ntiles_host, ntiles_phi_host)
-    // block tiles of the phi-summing domains (phi stage only); then
-    // ntiles_nphi_host tiles of the phi-summing update
-    int ntiles_host, ntiles_phi_host, ntiles_nphi_host;
-    int counts[2 + 2 * mplb::NPHI_GROUPS];  // the device tile counters (see launch_batch_step)
-    int grid[2 + mplb::NPHI_GROUPS];  // blocks of the phi, update and phi-summing update
-                                      // launches: tile counts rounded up to buckets of 4096
-                                      // (0 for an empty group)
+    // The slots that share launches, in cache groups (see BATCH_GROUPS): what
+    // a group's launches need besides the device tables.
+    struct Group {
+        bool kept;  // its populations stay in the Infinity Cache
+        int grid[2 + mplb::NPHI_GROUPS];  // blocks of the phi, update and phi-summing update
+                                          // launches (0 for none); grid[0] the only one in 2-D plain
+                                          // storage: tile counts rounded up by at most an eighth,
+                                          // so that a captured graph survives most changes
+        bool operator==(const Group &) const = default;
+    };
+    std::vector<Group> groups;
+    std::vector<int> counts;  // the device tile counters, GROUP_INTS per group
+    std::vector<int> table2d;  // the device table of launch_batch_step2d
     dim3 block;
     int chunk;
-    bool row;     // row-form kernels (see row_form_ok)
+    int form;     // FORM_* of the block kernels
     long long t;  // batch steps taken
     hipGraphExec_t exec;
     bool have_graph;
@@ -919,6 +921,8 @@ struct mplb_batch {
 
 namespace {
 
+size_t table2d_ints(int32_t capacity) { return 3 * size_t(mplb::BATCH_GROUPS) + 2 * size_t(capacity); }
+
 size_t table_layout(int32_t capacity, int64_t max_tiles, size_t *o_doms, size_t *o_tiles,
                     size_t *o_nt, size_t *o_tb, size_t *o_st, size_t *o_t0)
 {
@@ -928,13 +932,13 @@ size_t table_layout(int32_t capacity, int64_t max_tiles, size_t *o_doms, size_t 
     *o_tiles = off;
     off += up(sizeof(mplb::BatchTile) * max_tiles, ALIGN);
     *o_nt = off;
-    off += ALIGN;
+    off += up(sizeof(int) * mplb::BATCH_GROUPS * mplb::GROUP_INTS, ALIGN);
     *o_tb = off;
     off += ALIGN;
     *o_st = off;
     off += up(sizeof(int) * capacity, ALIGN);
     *o_t0 = off;
-    off += up(sizeof(int) * (size_t(capacity) + 1), ALIGN);
+    off += up(sizeof(int) * table2d_ints(capacity), ALIGN);
     return off;
 }
 
@@ -944,14 +948,73 @@ void drop_graph(mplb_batch *b)
     b->have_graph = false;
 }
 
+// The sharing slots in groups whose populations (both levels) fit the Infinity
+// Cache together, as few and as even as the largest-first rule makes them.  A
+// group takes a chunk of steps while its values stay in the cache; stepped all
+// at once, every step would stream all of them from HBM.  Domains too
+// large for it share one more group, and so does everything when the groups
+// would exceed BATCH_GROUPS.  Returns, per group, whether it is kept and its
+// slots.
+struct CacheGroup {
+    bool kept;
+    std::vector<int> slots;
+    long long cells;
+};
+std::vector<CacheGroup> cache_groups(const mplb_batch *b)
+{
+    auto fits = [&](long long cells) { return mplb::kept_in_cache(b->dim, b->storage, cells); };
+    std::vector<int> small, large;
+    for (int i = 0; i < b->capacity; ++i)
+        if (b->slot[i] && !b->solo[i]) (fits(b->doms[i].g.np) ? small : large).push_back(i);
+    std::stable_sort(small.begin(), small.end(),
+                     [&](int x, int y) { return b->doms[x].g.np > b->doms[y].g.np; });
+    const size_t most = mplb::BATCH_GROUPS - (large.empty() ? 0 : 1);
+    std::vector<CacheGroup> out;
+    for (size_t n = small.empty() ? 0 : 1; n <= most; ++n) {
+        out.assign(n, CacheGroup{true, {}, 0});
+        bool ok = true;
+        for (int i : small) {
+            CacheGroup *to = &out[0];
+            for (CacheGroup &c : out)
+                if (c.cells < to->cells) to = &c;
+            to->slots.push_back(i);
+            to->cells += b->doms[i].g.np;
+            ok = ok && fits(to->cells);
+        }
+        if (ok) break;
+        if (n == most) {
+            out.clear();
+            large.insert(large.end(), small.begin(), small.end());
+        }
+    }
+    if (!large.empty()) out.push_back(CacheGroup{false, large, 0});
+    for (CacheGroup &c : out) std::sort(c.slots.begin(), c.slots.end());
+    return out;
+}
+
 // Rebuild the tile list from the attached solvers and upload it with the
 // domain table; synchronises the stream so the host copies can be reused.
 int upload_tables(mplb_batch *b)
 {
+    using mplb::NPHI_GROUPS;
     b->tiles.clear();
     // domains whose update sums the next phi, as their solver's own step
     // would
     b->nshared = 0;
+    const int threads = int(b->block.x * b->block.y * b->block.z);
+    // the block kernels' form, shared by every domain: rows (tiles as wide as
+    // the domain's row rounded up to a power of two, at least 64 where x is
+    // periodic, at most the block's width; the rest of the block's threads
+    // cover further rows), or packed planes
+    bool row = true, pack = b->dim == 3 && threads % 64 == 0, ragged = false;
+    auto width = [&](const mplb_solver *s) {
+        int w = 1;
+        while (w < s->prm.n[0]) w <<= 1;
+        if (s->prm.bc[0] == MPLB_BC_PERIODIC && w < 64) w = 64;
+        if (w > int(b->block.x)) w = int(b->block.x);
+        return w > threads ? threads : w;
+    };
+    long long listed = 0;  // tiles of the row forms, which max_tiles bounds
     for (int i = 0; i < b->capacity; ++i) {
         mplb_solver *s = b->slot[i];
         if (!s || b->solo[i]) continue;
@@ -965,111 +1028,101 @@ int upload_tables(mplb_batch *b)
         }
         d.npart = by ? s->at(s->L.npart) : nullptr;
         d.nedge = by ? s->at(s->L.nedge) : nullptr;
+        const long long nx = s->prm.n[0], ny = s->prm.n[1], nz = s->prm.n[2];
+        const int w = width(s), rows = threads / w;
+        listed += (nx + w - 1) / w * ((ny + rows - 1) / rows) * nz + (by ? ny / by * nz : 0);
+        row = row && mplb::row_form_ok(b->dim, d.g, dim3(w, rows, 1));
+        pack = pack && d.g.bcx == mplb::BC_PER && d.g.bcy == mplb::BC_PER && 27 * d.g.np < (1ll << 31);
+        ragged = ragged || (!by && nx % 64 != 0);
     }
-    // the tile list: block tiles of the other domains (phi stage and update),
-    // block tiles of the phi-summing domains (phi stage: merge), tiles of the
-    // phi-summing update (whole rows of one plane)
-    const int threads = int(b->block.x * b->block.y * b->block.z);
-    bool row = true;
-    auto push = [&](const mplb::BatchTile &tl) {
-        if ((long long)b->tiles.size() >= b->max_tiles) return false;
-        b->tiles.push_back(tl);
-        return true;
+    if (listed > b->max_tiles) return fail(MPLB_ENOMEM, "batch tile list is full");
+    const int form = pack && ragged ? mplb::FORM_PACK : row ? mplb::FORM_ROW : mplb::FORM_LANE;
+    if (form != b->form) drop_graph(b);  // a captured graph holds the other kernel
+    b->form = form;
+    // launch sizes: rounded up by at most an eighth
+    auto bucketed = [](int n) {
+        int step = 1;
+        while (step * 16 <= n) step <<= 1;
+        return (n + step - 1) / step * step;
     };
-    int seg[3] = {0, 0, 0};
-    int wstart[mplb::NPHI_GROUPS] = {}, wcount[mplb::NPHI_GROUPS] = {};  // phi-summing tiles by row length
-    for (int pass = 0; pass < 2 + mplb::NPHI_GROUPS; ++pass) {
-        const size_t before = b->tiles.size();
-        for (int i = 0; i < b->capacity; ++i) {
-            const mplb_solver *s = b->slot[i];
-            if (!s || b->solo[i]) continue;
-            const int nx = s->prm.n[0], ny = s->prm.n[1], nz = s->prm.n[2];
-            const int nby = b->doms[i].nphi_by;
-            if (pass >= 2) {
-                // one group per row length (nphi_group)
-                if (!nby || nx != mplb::nphi_group_width(pass - 2)) continue;
-                for (int z = 0; z < nz; ++z)
-                    for (int y0 = 0; y0 < ny; y0 += nby)
-                        if (!push(mplb::BatchTile{i, 0, y0, z, z + 1, nx}))
-                            return fail(MPLB_ENOMEM, "batch tile list is full");
-                continue;
+    std::vector<mplb_batch::Group> groups;
+    std::fill(b->counts.begin(), b->counts.end(), 0);
+    std::fill(b->table2d.begin(), b->table2d.end(), 0);
+    int pos = 0;
+    for (const CacheGroup &cg : cache_groups(b)) {
+        const int gi = int(groups.size());
+        mplb_batch::Group gr{};
+        gr.kept = cg.kept;
+        if (b->one_launch()) {
+            int *head = &b->table2d[2 * gi], *ids = &b->table2d[2 * mplb::BATCH_GROUPS + pos];
+            int *run = ids + b->capacity + gi;
+            head[0] = pos;
+            head[1] = int(cg.slots.size());
+            long long n = 0;
+            for (size_t k = 0; k < cg.slots.size(); ++k) {
+                ids[k] = cg.slots[k];
+                run[k] = int(n);
+                n += mplb::step2d_tiles(b->doms[cg.slots[k]].g);
+                if (n > 0x3fffffffLL) return fail(MPLB_ENOMEM, "batch tile list is full");
             }
-            if ((pass == 0) != (nby == 0)) continue;
-            // tile width: the domain's row rounded up to a power of two, at
-            // least 64 where the row form can apply (x periodic), at most the
-            // block's width; the rest of the block's threads cover further rows
-            int w = 1;
-            while (w < nx) w <<= 1;
-            const bool xper = b->doms[i].g.bcx == mplb::BC_PER;
-            if (xper && w < 64) w = 64;
-            if (w > int(b->block.x)) w = int(b->block.x);
-            if (w > threads) w = threads;
-            const int rows = threads / w;
-            row = row && mplb::row_form_ok(b->dim, b->doms[i].g, dim3(w, rows, 1));
-            for (int z0 = 0; z0 < nz; ++z0)
-                for (int y0 = 0; y0 < ny; y0 += rows)
-                    for (int x0 = 0; x0 < nx; x0 += w)
-                        if (!push(mplb::BatchTile{i, x0, y0, z0, z0 + 1, w}))
-                            return fail(MPLB_ENOMEM, "batch tile list is full");
+            run[cg.slots.size()] = int(n);
+            pos += head[1];
+            gr.grid[0] = bucketed(int(n));
+            groups.push_back(gr);
+            continue;
         }
-        if (pass < 2) {
-            seg[pass] = int(b->tiles.size() - before);
-        } else {
-            wstart[pass - 2] = int(before);
-            wcount[pass - 2] = int(b->tiles.size() - before);
-            seg[2] += wcount[pass - 2];
+        // the group's tiles: block tiles of the domains the block kernels
+        // update (phi stage and update), block tiles of the phi-summing domains
+        // (phi stage: merge), tiles of the phi-summing update (whole rows of one
+        // plane) by row length
+        int *cnt = &b->counts[size_t(gi) * mplb::GROUP_INTS];
+        cnt[0] = int(b->tiles.size());
+        for (int pass = 0; pass < 2; ++pass) {
+            for (int i : cg.slots) {
+                const mplb_solver *s = b->slot[i];
+                const int nx = s->prm.n[0], ny = s->prm.n[1], nz = s->prm.n[2];
+                if ((pass == 0) != (b->doms[i].nphi_by == 0)) continue;
+                const int w = width(s), rows = threads / w;
+                for (int z0 = 0; z0 < nz; ++z0) {
+                    if (form == mplb::FORM_PACK) {
+                        for (int c0 = 0; c0 < nx * ny; c0 += threads)
+                            b->tiles.push_back(mplb::BatchTile{i, c0, 0, z0, z0 + 1, 0});
+                        continue;
+                    }
+                    for (int y0 = 0; y0 < ny; y0 += rows)
+                        for (int x0 = 0; x0 < nx; x0 += w)
+                            b->tiles.push_back(mplb::BatchTile{i, x0, y0, z0, z0 + 1, w});
+                }
+            }
+            cnt[1 + pass] = int(b->tiles.size()) - cnt[0];
         }
-    }
-    b->ntiles_host = seg[0];
-    b->ntiles_phi_host = seg[0] + seg[1];
-    b->ntiles_nphi_host = seg[2];
-    {
-        // one block per tile, hardware-scheduled; the launch sizes move in
-        // buckets of 4096 blocks so that a captured graph survives most
-        // attach / detach events (surplus blocks find no tile and exit)
-        const int bucket = 4096;
-        auto bucketed = [&](int n, int empty) { return n ? (n + bucket - 1) / bucket * bucket : empty; };
-        constexpr int NG = 2 + mplb::NPHI_GROUPS;
-        int grid[NG] = {bucketed(b->ntiles_phi_host, bucket), bucketed(b->ntiles_host, bucket)};
-        for (int k = 0; k < mplb::NPHI_GROUPS; ++k) grid[2 + k] = bucketed(wcount[k], 0);
-        for (int k = 0; k < NG; ++k)
-            if (grid[k] != b->grid[k]) drop_graph(b);
-        for (int k = 0; k < NG; ++k) b->grid[k] = grid[k];
-    }
-    if (row != b->row) drop_graph(b);  // a captured graph holds the other kernel
-    b->row = row;
-    if (b->one_launch()) {
-        // the running tile counts; the launch size moves in buckets, as above
-        long long cells = 0, n = 0;
-        for (int i = 0; i < b->capacity; ++i) {
-            b->tile0[i] = int(n);
-            if (!b->slot[i]) continue;
-            cells += b->doms[i].g.np;
-            if (!b->solo[i]) n += mplb::step2d_tiles(b->doms[i].g);
+        gr.grid[0] = bucketed(cnt[2]);
+        gr.grid[1] = bucketed(cnt[1]);
+        for (int k = 0; k < NPHI_GROUPS; ++k) {
+            cnt[3 + 2 * k] = int(b->tiles.size());
+            for (int i : cg.slots) {
+                const int nby = b->doms[i].nphi_by;
+                if (!nby || b->doms[i].g.nx != mplb::nphi_group_width(k)) continue;
+                for (int z = 0; z < b->doms[i].g.nz; ++z)
+                    for (int y0 = 0; y0 < b->doms[i].g.ny; y0 += nby)
+                        b->tiles.push_back(mplb::BatchTile{i, 0, y0, z, z + 1, b->doms[i].g.nx});
+            }
+            cnt[4 + 2 * k] = int(b->tiles.size()) - cnt[3 + 2 * k];
+            gr.grid[2 + k] = bucketed(cnt[4 + 2 * k]);
         }
-        if (n > 0x7fffffffLL - 4096) return fail(MPLB_ENOMEM, "batch tile list is full");
-        b->tile0[b->capacity] = int(n);
-        const int grid2d = int((n + 4095) / 4096 * 4096);
-        const bool kept = mplb::kept_in_cache(2, b->storage, cells);
-        if (grid2d != b->grid2d || kept != b->kept) drop_graph(b);
-        b->grid2d = grid2d;
-        b->kept = kept;
+        groups.push_back(gr);
     }
+    if (groups != b->groups) drop_graph(b);
+    b->groups = groups;
     HIPCHK(hipStreamSynchronize(b->stream));
     HIPCHK(hipMemcpyAsync(b->d_doms, b->doms.data(), sizeof(mplb::BatchDom) * b->capacity,
                           hipMemcpyHostToDevice, b->stream));
     if (!b->tiles.empty())
         HIPCHK(hipMemcpyAsync(b->d_tiles, b->tiles.data(), sizeof(mplb::BatchTile) * b->tiles.size(),
                               hipMemcpyHostToDevice, b->stream));
-    b->counts[0] = b->ntiles_host;
-    b->counts[1] = b->ntiles_phi_host;
-    for (int k = 0; k < mplb::NPHI_GROUPS; ++k) {
-        b->counts[2 + 2 * k] = wstart[k];
-        b->counts[3 + 2 * k] = wcount[k];
-    }
-    HIPCHK(hipMemcpyAsync(b->d_ntiles, b->counts, sizeof(b->counts), hipMemcpyHostToDevice,
-                          b->stream));
-    HIPCHK(hipMemcpyAsync(b->d_tile0, b->tile0.data(), sizeof(int) * b->tile0.size(),
+    HIPCHK(hipMemcpyAsync(b->d_ntiles, b->counts.data(), sizeof(int) * b->counts.size(),
+                          hipMemcpyHostToDevice, b->stream));
+    HIPCHK(hipMemcpyAsync(b->d_table2d, b->table2d.data(), sizeof(int) * b->table2d.size(),
                           hipMemcpyHostToDevice, b->stream));
     HIPCHK(hipStreamSynchronize(b->stream));
     return MPLB_OK;
@@ -1117,10 +1170,9 @@ int mplb_batch_create(int32_t dim, int32_t storage, int32_t capacity, int64_t ma
     b->d_ntiles = reinterpret_cast<int *>(base + on);
     b->d_tbase = reinterpret_cast<long long *>(base + ob);
     b->d_status = reinterpret_cast<int *>(base + os);
-    b->d_tile0 = reinterpret_cast<int *>(base + o0);
-    b->tile0.assign(size_t(capacity) + 1, 0);
-    b->grid2d = 0;
-    b->kept = false;
+    b->d_table2d = reinterpret_cast<int *>(base + o0);
+    b->counts.assign(size_t(mplb::BATCH_GROUPS) * mplb::GROUP_INTS, 0);
+    b->table2d.assign(table2d_ints(capacity), 0);
     b->slot.assign(capacity, nullptr);
     b->doms.assign(capacity, mplb::BatchDom{});
     b->solo.assign(capacity, 0);
@@ -1138,15 +1190,11 @@ int mplb_batch_create(int32_t dim, int32_t storage, int32_t capacity, int64_t ma
         delete b;
         return fail(MPLB_EDEVICE, "hipEventCreate failed");
     }
-    b->ntiles_host = b->ntiles_phi_host = b->ntiles_nphi_host = 0;
-    // one bucket: an empty batch launches blocks that find no tile
-    b->grid[0] = b->grid[1] = 4096;
-    for (int k = 2; k < 2 + mplb::NPHI_GROUPS; ++k) b->grid[k] = 0;
     b->block = dim3(64, 4, 1);
     b->chunk = 16;
     b->t = 0;
     b->have_graph = false;
-    b->row = true;
+    b->form = mplb::FORM_ROW;
     int rc = upload_tables(b);
     if (rc == MPLB_OK && mplb::launch_fill_i32(b->d_status, capacity, 0, b->stream) != hipSuccess)
         rc = fail(MPLB_EDEVICE, "clearing the batch status flags failed");
@@ -1299,16 +1347,23 @@ int mplb_batch_status(mplb_batch *b, int32_t *status)
 
 namespace {
 
-// The launches of one step of the domains that share them.
-hipError_t shared_step(mplb_batch *b, int step_off)
+// The launches of the next n steps of the domains that share them, group by
+// group.
+hipError_t shared_steps(mplb_batch *b, int n)
 {
-    if (b->one_launch())
-        return mplb::launch_batch_step2d(b->storage, b->collision, b->kept, b->d_doms, b->d_tile0,
-                                         b->capacity, b->d_tbase, step_off, b->grid2d, b->d_status,
-                                         b->side);
-    return mplb::launch_batch_step(b->dim, b->storage, b->collision, b->row, b->d_doms, b->d_tiles,
-                                   b->d_ntiles, b->d_tbase, step_off, b->block, b->grid, b->d_status,
-                                   b->side);
+    hipError_t e = hipSuccess;
+    for (size_t gi = 0; gi < b->groups.size(); ++gi) {
+        const mplb_batch::Group &gr = b->groups[gi];
+        for (int k = 0; k < n && e == hipSuccess; ++k)
+            e = b->one_launch()
+                    ? mplb::launch_batch_step2d(b->storage, b->collision, gr.kept, b->d_doms, b->d_table2d,
+                                                b->capacity, int(gi), b->d_tbase, k, gr.grid[0],
+                                                b->d_status, b->side)
+                    : mplb::launch_batch_step(b->dim, b->storage, b->collision, b->form, gr.kept, b->d_doms,
+                                              b->d_tiles, b->d_ntiles + gi * mplb::GROUP_INTS, b->d_tbase,
+                                              k, b->block, gr.grid, b->d_status, b->side);
+    }
+    return e;
 }
 
 }  // namespace
@@ -1330,8 +1385,7 @@ int mplb_batch_step(mplb_batch *b, int64_t nsteps)
             if (!b->have_graph) {
                 hipGraph_t graph = nullptr;
                 HIPCHK(hipStreamBeginCapture(b->side, hipStreamCaptureModeThreadLocal));
-                hipError_t e = hipSuccess;
-                for (int k = 0; k < b->chunk && e == hipSuccess; ++k) e = shared_step(b, k);
+                hipError_t e = shared_steps(b, b->chunk);
                 // always end the capture, so that a failure leaves the stream usable
                 const hipError_t e2 = hipStreamEndCapture(b->side, &graph);
                 if (e != hipSuccess || e2 != hipSuccess) {
@@ -1349,9 +1403,12 @@ int mplb_batch_step(mplb_batch *b, int64_t nsteps)
             b->t += b->chunk;
             done += b->chunk;
         } else {
-            HIPCHK(shared_step(b, 0));
-            b->t += 1;
-            done += 1;
+            // direct launches: what is left of a chunk, or 16 steps at a time
+            const int direct = b->chunk > 0 ? b->chunk : 16;
+            const int n = int(left < direct ? left : direct);
+            HIPCHK(shared_steps(b, n));
+            b->t += n;
+            done += n;
         }
     }
     b->t = t0 + nsteps;

@@ -1041,7 +1041,7 @@ __device__ __forceinline__ void collide_body(const NB &nb, const Geom &g,
     // the pulled phase-field values of a lattice in the Infinity Cache: loaded
     // before the stores, in FP32 before everything else (see CAC_PRELOAD)
     constexpr bool kept3 = is_kept<NB> && !in_tile<NB>;
-    constexpr bool early = kept3 && sizeof(T) == 4;
+    constexpr bool early = kept3 && sizeof(T) == 4 && !std::is_base_of<NbLane, NB>::value;
     constexpr bool preload = P::F::shifted || P::G::shifted || kept3 || CAC_PRELOAD;
     T pre[preload ? Q : 1];
     if constexpr (early) {
@@ -1343,8 +1343,6 @@ __device__ __forceinline__ void collide_cell(const Geom &g, const Phys<typename 
     collide_body<D, P, COLL>(nb, g, ph, p);
 }
 
-// Addressing of a launch: per lane, rows, or packed planes (3-D).
-enum { FORM_LANE, FORM_ROW, FORM_PACK };
 template <int FORM>
 using NbOf = typename std::conditional<FORM == FORM_PACK, NbPack,
              typename std::conditional<FORM == FORM_ROW, NbRow, NbLane>::type>::type;
@@ -1552,7 +1550,7 @@ constexpr int merge_planes()
 }
 
 // phi of cell (x, y, z) from its pieces, loaded one by one (batched form).
-template <class P>
+template <class P, class NB>
 __device__ __forceinline__ typename P::T nphi_merge_cell(const Geom &g, const Ptrs &p,
                                                          const NextPhi &q, int x, int y, int z)
 {
@@ -1578,14 +1576,13 @@ __device__ __forceinline__ typename P::T nphi_merge_cell(const Geom &g, const Pt
         __builtin_nontemporal_store(make_rec(s, *lane_ptr(static_cast<const unsigned *>(p.ref), row, x)),
                                     lane_ptr(static_cast<unsigned long long *>(p.phi), row, x));
     else
-        __builtin_nontemporal_store(s, lane_ptr(static_cast<T *>(p.phi), row, x));
+        store_out<NB>(s, lane_ptr(static_cast<T *>(p.phi), row, x));
     return s;
 }
 
 // ------------------------------------------------------------------ batches
-// Many independent domains advance in the same launches.  Blocks stride over
-// a tile list (one block per tile when the launch has a block per tile); each
-// tile names its domain, whose geometry, parameters, buffers and active step
+// Many independent domains advance in the same launches, one block per tile
+// of a tile list; each tile names its domain, whose geometry, parameters, buffers and active step
 // window are read from the domain table.  The per-cell arithmetic is the
 // single-domain path's (phi_cell, collide_cell, nphi_merge_sum, nphi_tile),
 // so a domain's result does not depend on the batch it is in.
@@ -1607,6 +1604,18 @@ __device__ __forceinline__ Ptrs batch_ptrs(const BatchDom &d, int in, bool have_
     p.frest_out = d.frest[1 - in];
     p.grest_out = d.grest[1 - in];
     return p;
+}
+
+// Tile of block `block` among nt: in order, or (KEPT) XCD k taking the k-th
+// eighth of them, so that neighbouring tiles share an L2.
+template <bool KEPT>
+__device__ __forceinline__ int tile_of(int block, int nt)
+{
+    if constexpr (KEPT) {
+        const int per = nt >> 3;
+        if (block < per * 8) return (block & 7) * per + (block >> 3);
+    }
+    return block;
 }
 
 // --------------------------------------------------------------- launchers

@@ -142,19 +142,25 @@ struct BatchDom {
 
 // A tile of a batch: domain index, origin cell (x0, y0, z0), end of its
 // plane range z1 and width w: w cells in x by (threads per block) / w rows,
-// one plane.
+// one plane; w = 0: consecutive cells of plane z0 from in-plane index x0 (see
+// NbPack).
 struct BatchTile {
     int dom, x0, y0, z0, z1, w;
 };
 
-// One batch step of 2-D domains in plain storage (step2d_ok) in one launch:
-// tile0[0 .. capacity] are the domains' running tile counts (step2d_tiles;
-// none for an empty slot or a domain that steps alone); blocks beyond
-// tile0[capacity] exit.  kept: the populations are stored to stay in the
-// Infinity Cache.  status as for launch_batch_step.
+// The domains that share launches are advanced in cache groups: a group's
+// populations fit the Infinity Cache together (kept), and it takes a chunk of
+// steps before the next group does.  At most BATCH_GROUPS groups.
+constexpr int BATCH_GROUPS = 32;
+
+// One step of a group of 2-D domains in plain storage (step2d_ok) in one
+// launch.  table: two ints per group (first position and number of domains),
+// then the domains by position, then per group its running tile counts
+// (step2d_tiles; number of domains + 1 entries, so position + group is their
+// start).  Blocks beyond the last count exit.  status as for launch_batch_step.
 hipError_t launch_batch_step2d(int storage, int collision, bool kept, const BatchDom *doms,
-                               const int *tile0, int capacity, const long long *tbase, int step_off,
-                               int grid, int *status, hipStream_t stream);
+                               const int *table, int capacity, int group, const long long *tbase,
+                               int step_off, int grid, int *status, hipStream_t stream);
 // Whether both levels of the populations of np cells stay in the Infinity
 // Cache from one step to the next.
 bool kept_in_cache(int dim, int storage, long long np);
@@ -162,26 +168,33 @@ bool kept_in_cache(int dim, int storage, long long np);
 // True when the row-form kernels apply: block a multiple of 64 wide in x,
 // x periodic, population arrays of fewer than 2^31 elements.
 bool row_form_ok(int dim, const Geom &g, dim3 block);
-// row: every attached domain satisfies row_form_ok with this block.
-// One batch step over the tile list (*ntiles entries), batch step index
-// *tbase + step_off.  collision: operator code, bit 0 the flow collision, bit
-// 1 the first-order phase-field equilibrium (shared by all domains).  The
-// phi pass and the update run over block tiles (row: every domain takes the
-// row form).  grid blocks stride over the tiles (at least one per tile:
-// hardware scheduling).
-// Tile list: ntiles[0] block tiles of the domains the block kernels update,
-// then block tiles of the phi-summing domains up to ntiles[1] (their phi
-// stage merges partial sums), then the tiles of the phi-summing update
-// (domains with nphi_by > 0: whole rows of one plane), grouped by row length
-// (nphi_group): group k starts at ntiles[2 + 2k] and holds ntiles[3 + 2k]
-// tiles.  grid[0], grid[1]: blocks of the phi stage and the update;
-// grid[2 + k]: of group k's update (0: not launched); 2 + NPHI_GROUPS entries.
+// Addressing of a launch: per lane, rows, or packed planes (3-D).
+enum { FORM_LANE, FORM_ROW, FORM_PACK };
+// One step of a group over the tile list, batch step index *tbase + step_off.
+// collision: operator code, bit 0 the flow collision, bit 1 the first-order
+// phase-field equilibrium (shared by all domains).  form: FORM_ROW where
+// every domain the block kernels update satisfies row_form_ok with its tile
+// width, FORM_PACK where each is 3-D, periodic in x and y and within 32-bit
+// indices (tiles of w = 0).
+// ntiles, GROUP_INTS of them: the group's first tile; the number of block
+// tiles of the domains the block kernels update, which come first; that number
+// with the block tiles of the phi-summing domains (their phi stage merges
+// partial sums), which come next; then, per row length (nphi_group), start and
+// number of the tiles of the phi-summing update (domains with nphi_by > 0:
+// whole rows of one plane).  grid[0], grid[1]: blocks of the phi stage and the
+// update, at least one per tile; grid[2 + k]: of row length k's update (0: not
+// launched); 2 + NPHI_GROUPS entries.
 // status[dom] is or-ed with 1 when the phi stage finds a non-finite order
 // parameter in that domain.
-hipError_t launch_batch_step(int dim, int storage, int collision, bool row,
+constexpr int GROUP_INTS = 16;
+hipError_t launch_batch_step(int dim, int storage, int collision, int form, bool kept,
                              const BatchDom *doms, const BatchTile *tiles, const int *ntiles,
                              const long long *tbase, int step_off, dim3 block, const int *grid,
                              int *status, hipStream_t stream);
+// Its phi-summing updates (k_batch_nphi.hip).
+hipError_t launch_batch_nphi(int storage, int collision, bool kept, const BatchDom *doms,
+                             const BatchTile *tiles, const int *ntiles, const long long *tbase,
+                             int step_off, const int *grid, hipStream_t stream);
 // Threads per block of the phi-summing update for a storage format and row length.
 int nphi_block_threads(int storage, int nx);
 hipError_t launch_set_i64(long long *ptr, long long v, hipStream_t stream);

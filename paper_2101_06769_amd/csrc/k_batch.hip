@@ -4,7 +4,9 @@
 
 namespace mplb {
 
-template <int D, class P, int COLL, bool PHI, bool ROW>
+// NB: the form of the block kernels (a Kept form: the group stays in the
+// Infinity Cache).
+template <int D, class P, int COLL, bool PHI, class NB, int FORM>
 __global__ void __launch_bounds__(256)
 __attribute__((amdgpu_waves_per_eu(PHI ? 1 : collide_waves<D, P, COLL>()))) kb_step(const BatchDom *__restrict__ doms,
                                                const BatchTile *__restrict__ tiles,
@@ -17,102 +19,73 @@ __attribute__((amdgpu_waves_per_eu(PHI ? 1 : collide_waves<D, P, COLL>()))) kb_s
     // the phi stage also flags a domain whose order parameter is not finite
     // (status[dom] != 0): a non-finite population of either set reaches phi
     // within a step
-    const int nt = PHI ? ntiles[1] : ntiles[0];
-    for (int ti = blockIdx.x; ti < nt; ti += gridDim.x) {
-        const BatchTile tl = tiles[ti];
-        // the domain's record by value: read once, not re-read after every
-        // population store the compiler cannot prove to be elsewhere
-        const Geom g = doms[tl.dom].g;
-        const long long first = doms[tl.dom].first, last = doms[tl.dom].last;
-        if (t < first || t >= last) continue;
-        const Ptrs p = batch_ptrs(doms[tl.dom], int((t - first) & 1), t >= doms[tl.dom].hist_from);
+    const int nt = PHI ? ntiles[2] : ntiles[1];
+    if (int(blockIdx.x) >= nt) return;
+    const BatchTile tl = tiles[ntiles[0] + tile_of<is_kept<NB>>(int(blockIdx.x), nt)];
+    // the domain's record by value: read once, not re-read after every
+    // population store the compiler cannot prove to be elsewhere
+    const Geom g = doms[tl.dom].g;
+    const long long first = doms[tl.dom].first, last = doms[tl.dom].last;
+    if (t < first || t >= last) return;
+    const Ptrs p = batch_ptrs(doms[tl.dom], int((t - first) & 1), t >= doms[tl.dom].hist_from);
+    const int tid = int(threadIdx.x + blockDim.x * (threadIdx.y + blockDim.y * threadIdx.z));
+    int x, y;
+    const int z = tl.z0;
+    if constexpr (FORM == FORM_PACK) {
+        const int c = tl.x0 + tid;
+        if (c >= g.nx * g.ny) return;
+        y = c / g.nx;
+        x = c - y * g.nx;
+    } else {
         // the tile is tl.w cells wide in x and (block threads) / tl.w rows
         // high, one plane deep; the width is the domain's own (a multiple of
         // 64 in the row form, so that each wavefront lies in one x-row)
-        const int tid = int(threadIdx.x + blockDim.x * (threadIdx.y + blockDim.y * threadIdx.z));
-        const int x = tl.x0 + tid % tl.w;
-        int y = tl.y0 + tid / tl.w;
-        const int z = tl.z0;
-        if constexpr (ROW) y = __builtin_amdgcn_readfirstlane(y);
-        if (x >= g.nx || y >= g.ny || z >= tl.z1) continue;
-        const int nby = doms[tl.dom].nphi_by;
-        if constexpr (PHI) {
-            const T ph = (D == 3 && nby && t >= doms[tl.dom].nphi_from)
-                             ? nphi_merge_cell<P>(g, p, NextPhi{doms[tl.dom].npart,
-                                                                doms[tl.dom].nedge, nby}, x, y, z)
-                             : phi_cell<D, P, NbOf<ROW ? FORM_ROW : FORM_LANE>>(g, p, x, y, z);
-            if (!__builtin_isfinite(ph)) atomicOr(status + tl.dom, 1);
-        } else {
-            const Phys<T> ph = to_phys<T>(doms[tl.dom].ph);
-            collide_cell<D, P, COLL, NbOf<ROW ? FORM_ROW : FORM_LANE>>(g, ph, p, x, y, z);
-        }
+        x = tl.x0 + tid % tl.w;
+        y = tl.y0 + tid / tl.w;
+        if constexpr (FORM == FORM_ROW) y = __builtin_amdgcn_readfirstlane(y);
+        if (x >= g.nx || y >= g.ny || z >= tl.z1) return;
     }
-}
-
-// Batched phi-summing update for domains with rows of BX cells (64, 128,
-// 192, 256 or 512): blocks stride over the ntiles[3 + 2k] tiles from index
-// ntiles[2 + 2k], k = nphi_group(BX) (domain, rows y0 .. y0 + nphi_by - 1 of
-// plane z0), each an nphi_tile of its domain.  (A loop over several planes
-// per tile keeps the tile's pointers and parameters live across the update
-// and spills: measured slower even for one plane.)  FP32: at most 80 VGPRs (six
-// wavefronts per SIMD), so that three tiles fit a CU as in the
-// single-domain kernel.
-template <class P, int COLL>
-constexpr int kb_nphi_waves()
-{
-    return collide_waves<3, P, COLL>() == 4 ? 6 : collide_waves<3, P, COLL>();
-}
-
-template <class P, int COLL, int BX>
-__global__ void __launch_bounds__(NPHI_THREADS) __attribute__((amdgpu_waves_per_eu(kb_nphi_waves<P, COLL>())))
-kb_collide_nphi(const BatchDom *__restrict__ doms, const BatchTile *__restrict__ tiles,
-                const int *ntiles, const long long *tbase, int step_off)
-{
-    using T = typename P::T;
-    extern __shared__ double nphi_lds[];
-    constexpr int k = nphi_group(BX);
-    const long long t = *tbase + step_off;
-    const int n0 = ntiles[2 + 2 * k], nt = ntiles[3 + 2 * k];
-    for (int ti = blockIdx.x; ti < nt; ti += gridDim.x) {
-        const BatchTile tl = tiles[n0 + ti];
-        const Geom g = doms[tl.dom].g;  // by value, see kb_step
-        const long long first = doms[tl.dom].first, last = doms[tl.dom].last;
-        if (t < first || t >= last) continue;  // the whole block
-        const Ptrs p = batch_ptrs(doms[tl.dom], int((t - first) & 1), t >= doms[tl.dom].hist_from);
+    const int nby = doms[tl.dom].nphi_by;
+    if constexpr (PHI) {
+        // (packed: the rows of a phi-summing domain are whole wavefronts)
+        const int yw = FORM == FORM_PACK ? __builtin_amdgcn_readfirstlane(y) : y;
+        const T ph = (D == 3 && nby && t >= doms[tl.dom].nphi_from)
+                         ? nphi_merge_cell<P, NB>(g, p, NextPhi{doms[tl.dom].npart, doms[tl.dom].nedge, nby}, x,
+                                                  yw, z)
+                         : phi_cell<D, P, NB>(g, p, x, y, z);
+        if (!__builtin_isfinite(ph)) atomicOr(status + tl.dom, 1);
+    } else {
         const Phys<T> ph = to_phys<T>(doms[tl.dom].ph);
-        const NextPhi q{doms[tl.dom].npart, doms[tl.dom].nedge, doms[tl.dom].nphi_by};
-        const int tid = int(threadIdx.x);
-        const int ty = __builtin_amdgcn_readfirstlane(tid / BX);
-        nphi_tile<P, COLL, BX>(g, ph, p, q, reinterpret_cast<T *>(nphi_lds), BX, tl.y0 / q.by, ty,
-                               tid - ty * BX, tl.z0, ty < q.by);
-        __syncthreads();  // the next tile of this block reuses the LDS
+        collide_cell<D, P, COLL, NB>(g, ph, p, x, y, z);
     }
 }
 
-// Batched form of the one-launch 2-D step: block b takes tile b of the running
-// counts tile0 (in eighths per XCD, as k_step2d); every wavefront finds the
-// domain with one load of 64 counts at a time.
+// Batched form of the one-launch 2-D step over one cache group (see
+// launch_batch_step2d): block b takes tile b of the group's running counts (in
+// eighths per XCD, as k_step2d); every wavefront finds the domain with one load
+// of 64 counts at a time.
 template <class P, int COLL, bool KEPT>
 __global__ void __launch_bounds__(STEP2D_THREADS)
-kb_step2d(const BatchDom *__restrict__ doms, const int *__restrict__ tile0, int capacity,
+kb_step2d(const BatchDom *__restrict__ doms, const int *__restrict__ table, int capacity, int group,
           const long long *tbase, int step_off, int *status)
 {
     using T = typename P::T;
     __shared__ T lphi[step2d_slots()];
-    const int nt = tile0[capacity], b0 = int(blockIdx.x);
-    if (b0 >= nt) return;
-    const int per = nt >> 3;
-    const int bid = b0 < per * 8 ? (b0 & 7) * per + (b0 >> 3) : b0;
-    // the last domain whose tiles begin at or before bid: domains without
-    // tiles share their successor's count and are passed over
-    int dom = -1;
-    for (int d0 = 0; d0 < capacity; d0 += 64) {
+    const int pos = table[2 * group], n = table[2 * group + 1];
+    const int *ids = table + 2 * BATCH_GROUPS + pos, *tile0 = table + 2 * BATCH_GROUPS + capacity + pos + group;
+    const int nt = tile0[n];
+    if (int(blockIdx.x) >= nt) return;
+    const int bid = tile_of<true>(int(blockIdx.x), nt);
+    // the last domain whose tiles begin at or before bid
+    int at = -1;
+    for (int d0 = 0; d0 < n; d0 += 64) {
         const int d = d0 + int(threadIdx.x & 63);
-        const int begins = __popcll(__ballot(d < capacity && tile0[d] <= bid));
-        dom += begins;
+        const int begins = __popcll(__ballot(d < n && tile0[d] <= bid));
+        at += begins;
         if (begins < 64) break;
     }
-    dom = __builtin_amdgcn_readfirstlane(dom);
+    at = __builtin_amdgcn_readfirstlane(at);
+    const int dom = ids[at];
     const long long t = *tbase + step_off;
     const long long first = doms[dom].first, last = doms[dom].last;
     if (t < first || t >= last) return;  // the whole block
@@ -120,7 +93,7 @@ kb_step2d(const BatchDom *__restrict__ doms, const int *__restrict__ tile0, int 
     const Ptrs p = batch_ptrs(doms[dom], int((t - first) & 1), t >= doms[dom].hist_from);
     const Phys<T> ph = to_phys<T>(doms[dom].ph);
     const int lbx = step2d_width(g.nx), by = STEP2D_THREADS >> lbx;
-    const int ntx = (g.nx + (1 << lbx) - 1) >> lbx, k = bid - tile0[dom];
+    const int ntx = (g.nx + (1 << lbx) - 1) >> lbx, k = bid - tile0[at];
     const int x0 = (k % ntx) << lbx, y0 = (k / ntx) * by;
     if (lbx == 6)
         step2d_tile<P, COLL, true, KEPT>(g, ph, p, lphi, lbx, x0, y0, status + dom);
@@ -129,15 +102,15 @@ kb_step2d(const BatchDom *__restrict__ doms, const int *__restrict__ tile0, int 
 }
 
 hipError_t launch_batch_step2d(int storage, int collision, bool kept, const BatchDom *doms,
-                               const int *tile0, int capacity, const long long *tbase, int step_off,
-                               int grid, int *status, hipStream_t stream)
+                               const int *table, int capacity, int group, const long long *tbase,
+                               int step_off, int grid, int *status, hipStream_t stream)
 {
     if (!step2d_ok(2, storage)) return hipErrorInvalidValue;
     return with_coll(collision, [&](auto cc) {
         constexpr int COLL = decltype(cc)::value;
         auto go = [&](auto kernel) {
-            hipLaunchKernelGGL(kernel, dim3(grid), dim3(STEP2D_THREADS), 0, stream, doms, tile0, capacity,
-                               tbase, step_off, status);
+            hipLaunchKernelGGL(kernel, dim3(grid), dim3(STEP2D_THREADS), 0, stream, doms, table, capacity,
+                               group, tbase, step_off, status);
             return hipGetLastError();
         };
         if (storage == ST_FP64)
@@ -154,7 +127,7 @@ __global__ void __launch_bounds__(256) k_fill_i32(int *ptr, int n, int v)
     if (i < n) ptr[i] = v;
 }
 
-hipError_t launch_batch_step(int dim, int storage, int collision, bool row,
+hipError_t launch_batch_step(int dim, int storage, int collision, int form, bool kept,
                              const BatchDom *doms, const BatchTile *tiles, const int *ntiles,
                              const long long *tbase, int step_off, dim3 block, const int *grid,
                              int *status, hipStream_t stream)
@@ -162,62 +135,45 @@ hipError_t launch_batch_step(int dim, int storage, int collision, bool row,
     Ctx c{};
     c.dim = dim;
     c.storage = storage;
-
-    auto go = [&](auto k, dim3 blk, int nblk, size_t lds = 0) {
-        hipLaunchKernelGGL(k, dim3(nblk), blk, lds, stream, doms, tiles, ntiles, tbase, step_off,
-                           status);
-        return hipGetLastError();
+    auto step = [&]<int D, class P, class NB, int FORM>() -> hipError_t {
+        auto go = [&](auto k, int nblk, size_t lds) {
+            if (nblk == 0) return hipSuccess;
+            hipLaunchKernelGGL(k, dim3(nblk), block, lds, stream, doms, tiles, ntiles, tbase, step_off,
+                               status);
+            return hipGetLastError();
+        };
+        hipError_t e = go(kb_step<D, P, 0, true, NB, FORM>, grid[0], 0);
+        if (e != hipSuccess) return e;
+        return with_coll(collision, [&](auto cc) -> hipError_t {
+            constexpr int COLL = decltype(cc)::value;
+            // dynamic LDS: single relaxation time's flow values (3-D)
+            return go(kb_step<D, P, COLL, false, NB, FORM>, grid[1],
+                      srt_lds_bytes<D, P, COLL>(block.x * block.y * block.z));
+        });
     };
-    // the phi-summing domains' update, one launch per row length present
-    // (grid[2 + k] blocks for NPHI_WIDTHS[k])
-    auto go_nphi = [&]<class P>(auto cc) -> hipError_t {
-        constexpr int COLL = decltype(cc)::value;
-        {
-            // a group's tiles have the threads its row length takes alone
-            auto one = [&](auto kernel, int nx, int nblk) {
-                if (nblk == 0) return hipSuccess;
-                const int threads = nphi_threads(storage, nx);
-                const size_t lds = size_t(26) * threads * sizeof(typename P::T);
-                hipLaunchKernelGGL(kernel, dim3(nblk), dim3(threads), lds, stream, doms, tiles,
-                                   ntiles, tbase, step_off);
-                return hipGetLastError();
-            };
-            hipError_t e = one(kb_collide_nphi<P, COLL, 64>, 64, grid[2]);
-            if (e == hipSuccess) e = one(kb_collide_nphi<P, COLL, 128>, 128, grid[3]);
-            if (e == hipSuccess) e = one(kb_collide_nphi<P, COLL, 192>, 192, grid[4]);
-            if (e == hipSuccess) e = one(kb_collide_nphi<P, COLL, 256>, 256, grid[5]);
-            if constexpr (sizeof(typename P::T) == 4) {
-                if (e == hipSuccess) e = one(kb_collide_nphi<P, COLL, 512>, 512, grid[6]);
-            } else {
-                if (grid[6]) e = hipErrorInvalidValue;
-            }
-            return e;
-        }
-    };
-    // collision: the operator code (bit 0 flow collision, bit 1 first-order
-    // phase-field equilibrium), shared by every domain of the batch
     return dispatch(c, [&]<int D, class P>() -> hipError_t {
         // 2-D domains in plain storage step in one launch (launch_batch_step2d)
         if constexpr (D == 2 && !P::F::shifted) {
             return hipErrorInvalidValue;
         } else {
-            hipError_t e = row ? go(kb_step<D, P, 0, true, true>, block, grid[0])
-                               : go(kb_step<D, P, 0, true, false>, block, grid[0]);
-            if (e != hipSuccess) return e;
-            return with_coll(collision, [&](auto cc) {
-                constexpr int COLL = decltype(cc)::value;
-                // dynamic LDS: single relaxation time's flow values (3-D)
-                const size_t lds = srt_lds_bytes<D, P, COLL>(block.x * block.y * block.z);
-                hipError_t e2 = row ? go(kb_step<D, P, COLL, false, true>, block, grid[1], lds)
-                                    : go(kb_step<D, P, COLL, false, false>, block, grid[1], lds);
-                const bool nphi = grid[2] || grid[3] || grid[4] || grid[5] || grid[6];
-                if constexpr (D == 3) {
-                    if (e2 == hipSuccess && nphi) e2 = go_nphi.template operator()<P>(cc);
-                } else {
-                    if (nphi) e2 = hipErrorInvalidValue;
+            auto by_form = [&]<int FORM>() -> hipError_t {
+                using NB = NbOf<FORM>;
+                if constexpr (D == 3 && !P::F::shifted) {
+                    if (kept) return step.template operator()<D, P, Kept<NB>, FORM>();
                 }
-                return e2;
-            });
+                return step.template operator()<D, P, NB, FORM>();
+            };
+            hipError_t e = hipErrorInvalidValue;
+            if (form == FORM_LANE) {
+                e = by_form.template operator()<FORM_LANE>();
+            } else if (form == FORM_ROW) {
+                e = by_form.template operator()<FORM_ROW>();
+            } else if constexpr (D == 3) {
+                e = by_form.template operator()<FORM_PACK>();
+            }
+            if (e == hipSuccess && D == 3)
+                e = launch_batch_nphi(storage, collision, kept, doms, tiles, ntiles, tbase, step_off, grid, stream);
+            return e;
         }
     });
 }

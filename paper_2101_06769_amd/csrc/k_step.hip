@@ -11,12 +11,7 @@ __device__ __forceinline__ bool block_cell(const Geom &g, int &x, int &y, int &z
         // lattices in the Infinity Cache: XCD k takes the k-th eighth of the
         // blocks, as k_step2d (48 x 48 x 192 FP32 46.0 -> 42.5 us a step;
         // larger ones stream better in plain order: 96 x 96 x 384 374 -> 379)
-        int bid = int(blockIdx.x);
-        if constexpr (KEPT) {
-            const int per = int(gridDim.x) >> 3;
-            if (bid < per * 8) bid = (bid & 7) * per + (bid >> 3);
-        }
-        return pack_cell(g, bid, x, y, z);
+        return pack_cell(g, tile_of<KEPT>(int(blockIdx.x), int(gridDim.x)), x, y, z);
     } else {
         thread_cell<FORM>(blockIdx.x * blockDim.x, blockIdx.y * blockDim.y, blockIdx.z * blockDim.z, x,
                           y, z);

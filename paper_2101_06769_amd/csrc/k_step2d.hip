@@ -12,8 +12,7 @@ __global__ void __launch_bounds__(STEP2D_THREADS)
 k_step2d(Geom g, Phys<typename P::T> ph, Ptrs p, int lbx, int ntx)
 {
     __shared__ typename P::T lphi[step2d_slots()];
-    const int per = int(gridDim.x) >> 3, b0 = int(blockIdx.x);
-    const int bid = b0 < per * 8 ? (b0 & 7) * per + (b0 >> 3) : b0;
+    const int bid = tile_of<true>(int(blockIdx.x), int(gridDim.x));
     const int by = ROWU ? STEP2D_THREADS / 64 : STEP2D_THREADS >> lbx;
     step2d_tile<P, COLL, ROWU, KEPT>(g, ph, p, lphi, lbx, (bid % ntx) << lbx, (bid / ntx) * by);
 }
