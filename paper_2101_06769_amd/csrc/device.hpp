@@ -1042,12 +1042,11 @@ __device__ __forceinline__ void collide_body(const NB &nb, const Geom &g,
     // before the stores, in FP32 before everything else (see CAC_PRELOAD)
     constexpr bool kept3 = is_kept<NB> && !in_tile<NB>;
     constexpr bool early = kept3 && sizeof(T) == 4 && !std::is_base_of<NbLane, NB>::value;
-    constexpr bool preload = P::F::shifted || P::G::shifted || kept3 || CAC_PRELOAD;
-    T pre[preload ? Q : 1];
+    T first[early ? Q : 1];
     if constexpr (early) {
 #pragma unroll
         for (int a = 0; a < Q; ++a)
-            if (a != Q / 2) pre[a] = pull<D, typename P::G, T>(nb, p.Gin, g.np, a);
+            if (a != Q / 2) first[a] = pull<D, typename P::G, T>(nb, p.Gin, g.np, a);
     }
     // FP16 phase-field storage: fp16 order parameters of the cells that read
     // the phase-field values stored here (see eval_cell16_paired)
@@ -1265,11 +1264,15 @@ __device__ __forceinline__ void collide_body(const NB &nb, const Geom &g,
             // the pulled values: all loads issued before the first store (the
             // compiler cannot prove the stored set apart from the pulled one,
             // and would otherwise wait on each pair before storing it)
-            if constexpr (preload && !early) {
+            constexpr bool preload = P::F::shifted || P::G::shifted || kept3 || CAC_PRELOAD;
+            T pre[preload ? Q : 1];
+            if constexpr (preload) {
 #pragma unroll
                 for (int a = 0; a < Q; ++a) {
                     if (a == Q / 2) continue;
-                    if constexpr (P::G::shifted) {
+                    if constexpr (early) {
+                        pre[a] = first[a];
+                    } else if constexpr (P::G::shifted) {
                         const PullLoc l = pull_loc<D>(nb, a);
                         pre[a] = dec_g16(weight<D, float>(a), c.Fown,
                                          load_code<true>(nb, p.Gin, (long long)l.dir * g.np, l));
