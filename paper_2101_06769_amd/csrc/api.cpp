@@ -675,6 +675,29 @@ int mplb_sync(mplb_solver *s)
 
 int64_t mplb_steps_done(const mplb_solver *s) { return s ? s->steps : -1; }
 
+namespace {
+
+// The device address of n doubles of page-locked host memory, or null where
+// host_out is not that (pageable or managed memory, or a buffer not locked to
+// its end): the field kernel then writes over the bus itself, without the
+// staging array and the copy's launch.
+double *device_view(double *host_out, long long n)
+{
+    if (reinterpret_cast<uintptr_t>(host_out) % sizeof(double)) return nullptr;
+    hipPointerAttribute_t a{}, z{};
+    if (hipPointerGetAttributes(&a, host_out) != hipSuccess ||
+        hipPointerGetAttributes(&z, host_out + n - 1) != hipSuccess) {
+        (void)hipGetLastError();  // pageable memory: the query's error is not the next launch's
+        return nullptr;
+    }
+    if (a.type != hipMemoryTypeHost || z.type != hipMemoryTypeHost || !a.devicePointer || !z.devicePointer)
+        return nullptr;
+    double *first = static_cast<double *>(a.devicePointer);
+    return static_cast<double *>(z.devicePointer) == first + (n - 1) ? first : nullptr;
+}
+
+}  // namespace
+
 int mplb_read(mplb_solver *s, int32_t field, double *host_out)
 {
     if (!s || !host_out) return fail(MPLB_EINVAL, "solver and host_out are required");
@@ -685,10 +708,13 @@ int mplb_read(mplb_solver *s, int32_t field, double *host_out)
         return MPLB_OK;
     }
     const mplb::Ctx c = s->ctx(s->cur);
-    double *st = s->staging(1 - s->cur);
-    HIPCHK(mplb::launch_phi(c));
-    HIPCHK(mplb::launch_field(c, field, st));
-    HIPCHK(hipMemcpyAsync(host_out, st, s->L.N * sizeof(double), hipMemcpyDeviceToHost, s->stream));
+    if (double *direct = device_view(host_out, s->L.N)) {
+        HIPCHK(mplb::launch_field(c, field, direct));
+    } else {
+        double *st = s->staging(1 - s->cur);
+        HIPCHK(mplb::launch_field(c, field, st));
+        HIPCHK(hipMemcpyAsync(host_out, st, s->L.N * sizeof(double), hipMemcpyDeviceToHost, s->stream));
+    }
     HIPCHK(hipStreamSynchronize(s->stream));
     return MPLB_OK;
 }

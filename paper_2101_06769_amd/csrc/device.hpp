@@ -966,7 +966,7 @@ __device__ __forceinline__ void store_phi(const NB &nb, const Ptrs &p, typename 
 }
 
 template <int D, class P, class NB>
-__device__ __forceinline__ typename P::T phi_body(const NB &nb, long long np, const Ptrs &p)
+__device__ __forceinline__ typename P::T phi_value(const NB &nb, long long np, const Ptrs &p)
 {
     using T = typename P::T;
     constexpr int Q = Lat<D>::Q;
@@ -991,7 +991,6 @@ __device__ __forceinline__ typename P::T phi_body(const NB &nb, long long np, co
 #pragma unroll
         for (int a = 0; a < Q; ++a) s += pull<D, typename P::G, T>(nb, p.Gin, np, a);
     }
-    store_phi<P>(nb, p, s);
     return s;
 }
 
@@ -1000,7 +999,9 @@ template <int D, class P, class NB>
 __device__ __forceinline__ typename P::T phi_cell(const Geom &g, const Ptrs &p, int x, int y, int z)
 {
     const NB nb = make_nb(g, x, y, z, (NB *)nullptr);
-    return phi_body<D, P>(nb, g.np, p);
+    const typename P::T s = phi_value<D, P>(nb, g.np, p);
+    store_phi<P>(nb, p, s);
+    return s;
 }
 
 
@@ -1379,6 +1380,33 @@ __device__ __forceinline__ bool pack_cell(const Geom &g, int block, int &x, int 
 }
 
 
+// Tile of block `block` among nt: in order, or (KEPT) XCD k taking the k-th
+// eighth of them, so that neighbouring tiles share an L2.
+template <bool KEPT>
+__device__ __forceinline__ int tile_of(int block, int nt)
+{
+    if constexpr (KEPT) {
+        const int per = nt >> 3;
+        if (block < per * 8) return (block & 7) * per + (block >> 3);
+    }
+    return block;
+}
+
+template <int FORM, bool KEPT>
+__device__ __forceinline__ bool block_cell(const Geom &g, int &x, int &y, int &z)
+{
+    if constexpr (FORM == FORM_PACK) {
+        // lattices in the Infinity Cache: XCD k takes the k-th eighth of the
+        // blocks, as k_step2d (48 x 48 x 192 FP32 46.0 -> 42.5 us a step;
+        // larger ones stream better in plain order: 96 x 96 x 384 374 -> 379)
+        return pack_cell(g, tile_of<KEPT>(int(blockIdx.x), int(gridDim.x)), x, y, z);
+    } else {
+        thread_cell<FORM>(blockIdx.x * blockDim.x, blockIdx.y * blockDim.y, blockIdx.z * blockDim.z, x,
+                          y, z);
+        return x < g.nx && y < g.ny && z < g.nz;
+    }
+}
+
 // ------------------------------------------------------- next order parameter
 // phi^{n+1}(x) is the zeroth moment of the populations pulled at x (Sec. 2.2),
 // sum_a g*_a(x - c_a) under periodic wrap, with bounced-back values where the
@@ -1609,18 +1637,6 @@ __device__ __forceinline__ Ptrs batch_ptrs(const BatchDom &d, int in, bool have_
     return p;
 }
 
-// Tile of block `block` among nt: in order, or (KEPT) XCD k taking the k-th
-// eighth of them, so that neighbouring tiles share an L2.
-template <bool KEPT>
-__device__ __forceinline__ int tile_of(int block, int nt)
-{
-    if constexpr (KEPT) {
-        const int per = nt >> 3;
-        if (block < per * 8) return (block & 7) * per + (block >> 3);
-    }
-    return block;
-}
-
 // --------------------------------------------------------------- launchers
 
 inline dim3 grid_for(const Ctx &c)
@@ -1672,6 +1688,25 @@ inline unsigned pack_blocks(const Geom &g)
     return unsigned((plane + PACK_THREADS - 1) / PACK_THREADS) * unsigned(g.nz);
 }
 inline bool row_form(const Ctx &c) { return row_form_ok(c.dim, c.g, c.block); }
+
+// Calls fn.template operator()<NB, FORM>(grid, block) for the form of a launch
+// over the context's cells (KEEP: a Kept form where it applies).
+template <int D, class P, bool KEEP = true, class Fn>
+inline hipError_t with_form(const Ctx &c, Fn &&fn)
+{
+    auto go = [&]<int FORM>(dim3 grid, dim3 block) {
+        using NB = NbOf<FORM>;
+        if constexpr (KEEP && !P::F::shifted && D == 3) {
+            if (kept_in_cache(3, c.storage, c.g.np)) return fn.template operator()<Kept<NB>, FORM>(grid, block);
+        }
+        return fn.template operator()<NB, FORM>(grid, block);
+    };
+    if constexpr (D == 3) {
+        if (pack_form(c)) return go.template operator()<FORM_PACK>(dim3(pack_blocks(c.g)), dim3(PACK_THREADS));
+    }
+    return row_form(c) ? go.template operator()<FORM_ROW>(grid_for(c), c.block)
+                       : go.template operator()<FORM_LANE>(grid_for(c), c.block);
+}
 
 // Compile-time operator selection: bit 0 of COLL the flow collision, bit 1
 // the first-order phase-field equilibrium.

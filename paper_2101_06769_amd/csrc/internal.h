@@ -109,7 +109,8 @@ hipError_t launch_set_pop(const Ctx &c, int which, int a0, int a1, const double 
 // References of the FP16 formats (the ref array) for an initial state, from
 // FP64 order-parameter and pressure fields.
 hipError_t launch_set_refs(const Ctx &c, const double *phi, const double *pr);
-// One macroscopic field of the state held in Fin/Gin (phi must be current).
+// One macroscopic field of the state held in Fin/Gin (the phi array may be
+// rewritten on the way).
 hipError_t launch_field(const Ctx &c, int field, double *dst);
 // Deterministic FP64 reduction: partials (at least reduce_blocks() x 8
 // doubles), out[8] = {sum phi, sum rho ux, uy, uz, max|u|, nonfinite count}.

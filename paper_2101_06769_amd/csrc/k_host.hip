@@ -3,7 +3,7 @@
 #include <map>
 #include <mutex>
 
-#include "device.hpp"
+#include "step2d.hpp"
 
 namespace mplb {
 
@@ -165,21 +165,53 @@ __global__ void __launch_bounds__(256) k_set_pop(Geom g, PhysD ph, Ptrs p, int w
     }
 }
 
-template <int D, class P>
+// phi or rho of the state: no neighbour's phi is needed, so no phi pass.
+template <int D, class P, class NB, int FORM>
+__global__ void __launch_bounds__(256) k_field_phi(Geom g, Phys<typename P::T> ph, Ptrs p, int field,
+                                                   double *dst)
+{
+    using T = typename P::T;
+    int x, y, z;
+    if (!block_cell<FORM, false>(g, x, y, z)) return;
+    const NB nb = make_nb(g, x, y, z, (NB *)nullptr);
+    const T phi = phi_value<D, P>(nb, g.np, p);
+    *lane_ptr(dst, nb.row, nb.x) = double(field == 0 ? phi : ph.rho_l + ph.drho * phi);
+}
+
+template <typename T>
+__device__ __forceinline__ double field_of(const Cell<T> &c, int field)
+{
+    return double(field == 2 ? c.ux : field == 3 ? c.uy : field == 4 ? c.uz : c.pstar);
+}
+
+// A velocity component or the pressure, after a phi pass.
+template <int D, class P, class NB, int FORM>
 __global__ void __launch_bounds__(256) k_field(Geom g, Phys<typename P::T> ph, Ptrs p, int field,
                                                double *dst)
 {
-    using T = typename P::T;
-    const int x = blockIdx.x * blockDim.x + threadIdx.x;
-    const int y = blockIdx.y * blockDim.y + threadIdx.y;
-    const int z = blockIdx.z * blockDim.z + threadIdx.z;
-    if (x >= g.nx || y >= g.ny || z >= g.nz) return;
-    Cell<T> c;
-    const NbLane nb = make_nb(g, x, y, z, (NbLane *)nullptr);
+    int x, y, z;
+    if (!block_cell<FORM, false>(g, x, y, z)) return;
+    Cell<typename P::T> c;
+    const NB nb = make_nb(g, x, y, z, (NB *)nullptr);
     eval_cell<D, P>(nb, g.np, ph, p, c);
-    T v = field == 0 ? c.phi : field == 1 ? c.rho : field == 2 ? c.ux : field == 3 ? c.uy
-        : field == 4 ? c.uz : c.pstar;
-    dst[cell_of(g, x, y, z)] = double(v);
+    *lane_ptr(dst, nb.row, nb.x) = field_of(c, field);
+}
+
+// The same of a 2-D lattice in plain storage: phi summed in the block, as the
+// one-launch step does.
+template <class P, bool ROWU>
+__global__ void __launch_bounds__(STEP2D_THREADS) k_field2d(Geom g, Phys<typename P::T> ph, Ptrs p, int lbx,
+                                                            int ntx, int field, double *dst)
+{
+    using T = typename P::T;
+    __shared__ T lphi[step2d_slots()];
+    const int bid = tile_of<true>(int(blockIdx.x), int(gridDim.x));
+    const int by = ROWU ? STEP2D_THREADS / 64 : STEP2D_THREADS >> lbx;
+    NbTile<T, false> nb;
+    if (!step2d_load<P, ROWU, false>(g, p, lphi, lbx, (bid % ntx) << lbx, (bid / ntx) * by, nullptr, nb)) return;
+    Cell<T> c;
+    eval_cell<2, P>(nb, g.np, ph, p, c);
+    *lane_ptr(dst, nb.row, nb.x) = field_of(c, field);
 }
 
 constexpr int RED_BLOCKS = 1024;
@@ -306,10 +338,32 @@ hipError_t launch_set_pop(const Ctx &c, int which, int a0, int a1, const double 
 
 hipError_t launch_field(const Ctx &c, int field, double *dst)
 {
-    return dispatch(c, [&]<int D, class P>() {
-        hipLaunchKernelGGL((k_field<D, P>), grid_for(c), c.block, 0, c.stream, c.g,
-                           to_phys<typename P::T>(c.ph), c.p, field, dst);
-        return hipGetLastError();
+    return dispatch(c, [&]<int D, class P>() -> hipError_t {
+        const auto ph = to_phys<typename P::T>(c.ph);
+        if (field < 2) {
+            return with_form<D, P, false>(c, [&]<class NB, int FORM>(dim3 grid, dim3 block) {
+                hipLaunchKernelGGL((k_field_phi<D, P, NB, FORM>), grid, block, 0, c.stream, c.g, ph, c.p,
+                                   field, dst);
+                return hipGetLastError();
+            });
+        }
+        if constexpr (D == 2 && !P::F::shifted) {
+            const int lbx = step2d_width(c.g.nx), ntx = (c.g.nx + (1 << lbx) - 1) >> lbx;
+            auto go = [&](auto kernel) {
+                hipLaunchKernelGGL(kernel, dim3(step2d_tiles(c.g)), dim3(STEP2D_THREADS), 0, c.stream, c.g,
+                                   ph, c.p, lbx, ntx, field, dst);
+                return hipGetLastError();
+            };
+            return lbx == 6 ? go(k_field2d<P, true>) : go(k_field2d<P, false>);
+        } else {
+            const hipError_t e = launch_phi(c);
+            if (e != hipSuccess) return e;
+            return with_form<D, P, false>(c, [&]<class NB, int FORM>(dim3 grid, dim3 block) {
+                hipLaunchKernelGGL((k_field<D, P, NB, FORM>), grid, block, 0, c.stream, c.g, ph, c.p,
+                                   field, dst);
+                return hipGetLastError();
+            });
+        }
     });
 }
 

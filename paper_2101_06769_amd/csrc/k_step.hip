@@ -4,21 +4,6 @@
 
 namespace mplb {
 
-template <int FORM, bool KEPT>
-__device__ __forceinline__ bool block_cell(const Geom &g, int &x, int &y, int &z)
-{
-    if constexpr (FORM == FORM_PACK) {
-        // lattices in the Infinity Cache: XCD k takes the k-th eighth of the
-        // blocks, as k_step2d (48 x 48 x 192 FP32 46.0 -> 42.5 us a step;
-        // larger ones stream better in plain order: 96 x 96 x 384 374 -> 379)
-        return pack_cell(g, tile_of<KEPT>(int(blockIdx.x), int(gridDim.x)), x, y, z);
-    } else {
-        thread_cell<FORM>(blockIdx.x * blockDim.x, blockIdx.y * blockDim.y, blockIdx.z * blockDim.z, x,
-                          y, z);
-        return x < g.nx && y < g.ny && z < g.nz;
-    }
-}
-
 template <int D, class P, class NB, int FORM>
 __global__ void __launch_bounds__(256) k_phi(Geom g, Ptrs p)
 {
@@ -56,25 +41,6 @@ bool kept_in_cache(int dim, int storage, long long np)
     const long long f = storage == ST_FP64 ? 8 : storage == ST_FP32 ? 4 : 2;
     const long long gg = storage == ST_FP64 ? 8 : storage == ST_FP16S_ALL ? 2 : 4;
     return 2 * (dim == 2 ? 9 : 27) * np * (f + gg) <= (256ll << 20);
-}
-
-// Calls fn.template operator()<NB, FORM>(grid, block) for the form of a launch
-// over the context's cells.
-template <int D, class P, class Fn>
-static hipError_t with_form(const Ctx &c, Fn &&fn)
-{
-    auto go = [&]<int FORM>(dim3 grid, dim3 block) {
-        using NB = NbOf<FORM>;
-        if constexpr (!P::F::shifted && D == 3) {
-            if (kept_in_cache(3, c.storage, c.g.np)) return fn.template operator()<Kept<NB>, FORM>(grid, block);
-        }
-        return fn.template operator()<NB, FORM>(grid, block);
-    };
-    if constexpr (D == 3) {
-        if (pack_form(c)) return go.template operator()<FORM_PACK>(dim3(pack_blocks(c.g)), dim3(PACK_THREADS));
-    }
-    return row_form(c) ? go.template operator()<FORM_ROW>(grid_for(c), c.block)
-                       : go.template operator()<FORM_LANE>(grid_for(c), c.block);
 }
 
 hipError_t launch_phi(const Ctx &c)

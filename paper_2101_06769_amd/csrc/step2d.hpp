@@ -123,16 +123,17 @@ constexpr int step2d_slots()
     return most;
 }
 
-// One tile from (x0, y0), bx = 2^lbx cells wide, 256 / bx rows high.
+// The first half of a tile from (x0, y0), bx = 2^lbx cells wide, 256 / bx rows
+// high: the thread's cell with its pulled populations, and phi of the tile and
+// its ring in lphi.  False for threads without a cell.
 // KEPT: the populations are stored to stay in the Infinity Cache (kept_in_cache).
 // flag, if given: or-ed with 1 where phi is not finite.
 // Every thread of the block calls it (it holds a barrier).  ROWU: bx = 64, a
 // wavefront per row; the rows below and above the tile are summed by the
 // first two wavefronts in row form, the columns beside it by the third.
-template <class P, int COLL, bool ROWU, bool KEPT>
-__device__ __forceinline__ void step2d_tile(const Geom &g, const Phys<typename P::T> &ph, const Ptrs &p,
-                                            typename P::T *lphi, int lbx, int x0, int y0,
-                                            int *flag = nullptr)
+template <class P, bool ROWU, bool KEPT>
+__device__ __forceinline__ bool step2d_load(const Geom &g, const Ptrs &p, typename P::T *lphi, int lbx,
+                                            int x0, int y0, int *flag, NbTile<typename P::T, KEPT> &nb)
 {
     using T = typename P::T;
     const int bx = ROWU ? 64 : 1 << lbx, by = STEP2D_THREADS / bx, ls = bx + 2;
@@ -145,7 +146,6 @@ __device__ __forceinline__ void step2d_tile(const Geom &g, const Phys<typename P
     auto slot = [&](int i, int j) { return lphi + (j + 1) * ls + i + 1; };
     const bool active = tx < w && ty < h;
     const int x = x0 + tx, y = y0 + ty;
-    NbTile<T, KEPT> nb;
     if (active) {
         const Pull2d<ROWU> c(g, x, y);
         c.load(G, g.np, nb.gp);
@@ -181,12 +181,21 @@ __device__ __forceinline__ void step2d_tile(const Geom &g, const Phys<typename P
         if (flag && !__builtin_isfinite(s)) atomicOr(flag, 1);
     }
     __syncthreads();
-    if (!active) return;
     nb.row = y * g.nx;
     nb.x = x;
     nb.lphi = slot(tx, ty);
     nb.ls = ls;
-    collide_body<2, P, COLL>(nb, g, ph, p);
+    return active;
+}
+
+// One tile of the step.
+template <class P, int COLL, bool ROWU, bool KEPT>
+__device__ __forceinline__ void step2d_tile(const Geom &g, const Phys<typename P::T> &ph, const Ptrs &p,
+                                            typename P::T *lphi, int lbx, int x0, int y0,
+                                            int *flag = nullptr)
+{
+    NbTile<typename P::T, KEPT> nb;
+    if (step2d_load<P, ROWU, KEPT>(g, p, lphi, lbx, x0, y0, flag, nb)) collide_body<2, P, COLL>(nb, g, ph, p);
 }
 
 }  // namespace mplb
