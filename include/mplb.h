@@ -166,8 +166,10 @@ int mplb_init(mplb_solver *s, const double *phi, const double *u, const double *
  * the antidiffusion source (Sec. 2.2, Eqs. LBM_AC and
  * phase_source_post_discretization), and streaming with the boundary rules
  * of Sec. 3 (half-way bounce-back walls, symmetry planes, periodic axes).
- * Runs of 16 steady-state steps are launched as one captured HIP graph (the
- * same kernels and arguments, the same results; design, not in the paper):
+ * Runs of 16 (some small lattices 18) steady-state steps are launched as one
+ * captured HIP graph (the same kernels and arguments, the same results; design,
+ * not in the paper); small 2-D lattices in plain storage take two to four
+ * steps per launch, with the results of single steps:
  * the graph is captured on a stream of the handle's own at the first such
  * run and again when the level parity, the block or the step form changes.
  * Errors: EINVAL, ESTATE (not initialised, or attached to a batch),

@@ -13,7 +13,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libmplb.so")
-SOURCES = ["k_step.hip", "k_step2d.hip", "k_nphi.hip", "k_host.hip", "k_batch.hip", "k_batch_nphi.hip", "api.cpp"]
+SOURCES = ["k_step.hip", "k_step2d.hip", "k_multi2d.hip", "k_nphi.hip", "k_host.hip", "k_batch.hip", "k_batch_nphi.hip", "api.cpp"]
 
 # hipcc flags: gfx950 only, C++20, no packed-FP32 instructions, and
 # multiply-add fusion only within one source expression (-ffp-contract=on):

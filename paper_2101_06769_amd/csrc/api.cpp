@@ -225,7 +225,7 @@ struct mplb_solver {
     bool nphi_valid;  // the last update wrote partial sums of the current phi
     dim3 block;
     mplb::PhysD ph;
-    // Steps replayed as a captured graph (mplb_step): GRAPH_STEPS steps from
+    // Steps replayed as a captured graph (mplb_step): graph_steps from
     // level g_cur with block g_block and the phi-summing update on or off
     // (g_nphi), captured on a private stream at the default priority.
     hipStream_t cap;
@@ -264,6 +264,8 @@ struct mplb_solver {
     // The step is one launch, which sums phi in its blocks and leaves the phi
     // array alone.
     bool one_launch() const { return mplb::step2d_ok(prm.dim, prm.storage); }
+    // Steps that one launch takes in a run of steps (1: single steps).
+    int multi_steps() const { return mplb::multi2d_steps(ctx(0)); }
     // The phi array of the current level for a reader of it between steps.
     hipError_t refresh_phi(const mplb::Ctx &c) const
     {
@@ -549,11 +551,11 @@ int mplb_init(mplb_solver *s, const double *phi, const double *u, const double *
 
 namespace {
 
-// Steps per captured graph of mplb_step: even, so that the level parity the
-// graph's arguments were taken at returns after each replay.
-constexpr int GRAPH_STEPS = 16;
+// Steps per captured graph of mplb_step: an even number of launches, so that the
+// level parity the graph's arguments were taken at returns after each replay.
+int graph_steps(const mplb_solver *s) { return s->multi_steps() == 3 ? 18 : 16; }
 
-// GRAPH_STEPS steps of the steady state (the (phi u) history present; the phi
+// graph_steps of the steady state (the (phi u) history present; the phi
 // stage takes the same form every step) as one graph launch on the solver's
 // stream.  The graph is captured once per (level parity, block, step form) on
 // the solver's private stream; its kernels are those of a direct step with
@@ -569,11 +571,16 @@ int replay_steps(mplb_solver *s)
         HIPCHK(hipStreamBeginCapture(s->cap, hipStreamCaptureModeThreadLocal));
         hipError_t e = hipSuccess;
         int cur = s->cur;
-        for (int k = 0; k < GRAPH_STEPS && e == hipSuccess; ++k) {
+        const int multi = s->multi_steps();
+        for (int k = 0, n = graph_steps(s); k < n && e == hipSuccess; k += multi) {
             mplb::Ctx c = s->ctx(cur);
             c.stream = s->cap;
-            e = s->launch_phi_stage(c);
-            if (e == hipSuccess) e = s->launch_update_stage(c);
+            if (multi > 1) {
+                e = mplb::launch_multi2d(c, multi);
+            } else {
+                e = s->launch_phi_stage(c);
+                if (e == hipSuccess) e = s->launch_update_stage(c);
+            }
             cur ^= 1;
         }
         hipGraph_t graph = nullptr;
@@ -608,11 +615,20 @@ int mplb_step(mplb_solver *s, int64_t nsteps)
     for (int64_t i = 0; i < nsteps;) {
         const mplb::Ctx c = s->ctx(s->cur);
         const bool steady = s->hist && (!s->use_nphi(c) || s->nphi_valid);
-        if (steady && nsteps - i >= GRAPH_STEPS) {
+        if (steady && nsteps - i >= graph_steps(s)) {
             const int rc = replay_steps(s);
             if (rc != MPLB_OK) return rc;
-            s->steps += GRAPH_STEPS;
-            i += GRAPH_STEPS;
+            s->steps += graph_steps(s);
+            i += graph_steps(s);
+            continue;
+        }
+        const int multi = s->multi_steps();
+        if (multi > 1 && nsteps - i >= multi) {
+            HIPCHK(mplb::launch_multi2d(c, multi));
+            s->cur ^= 1;
+            s->steps += multi;
+            s->hist = true;
+            i += multi;
             continue;
         }
         HIPCHK(s->launch_phi_stage(c));
@@ -1451,14 +1467,14 @@ int mplb_batch_step(mplb_batch *b, int64_t nsteps)
         for (long long k = lo; k < hi;) {
             const mplb::Ctx c = s->ctx(s->cur);
             const bool steady = s->hist && (!s->use_nphi(c) || s->nphi_valid);
-            if (steady && hi - k >= GRAPH_STEPS) {
+            if (steady && hi - k >= graph_steps(s)) {
                 // a run of steps as the solver's step graph, its phi checked first
                 HIPCHK(s->refresh_phi(c));
                 HIPCHK(mplb::launch_flag_nonfinite(c, b->d_status + i));
                 const int rc = replay_steps(s);
                 if (rc != MPLB_OK) return rc;
-                s->steps += GRAPH_STEPS;
-                k += GRAPH_STEPS;
+                s->steps += graph_steps(s);
+                k += graph_steps(s);
                 continue;
             }
             HIPCHK(s->launch_phi_stage(c));

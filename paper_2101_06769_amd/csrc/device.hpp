@@ -277,8 +277,33 @@ struct NbTile {
     int ls;
     T f[9], gp[9];
 };
+// Cell of the 2-D kernel that takes several steps (k_multi2d): populations
+// and phi in LDS.  e: the cell's slot; ox, oy: offsets of the neighbours' phi
+// slots (the own one beyond a wall or symmetry plane).
+constexpr int MULTI_EDGE = 24, MULTI_CELLS = MULTI_EDGE * MULTI_EDGE;
+template <typename T>
+struct NbMulti {
+    static constexpr int row = 0, x = 0;  // no place in the arrays
+    T *pop;        // [18][MULTI_CELLS] at the own slot: f', then g
+    const T *phi;  // [MULTI_CELLS] at the own slot
+    int ox[3], oy[3];
+    T f[9], gp[9];
+};
+template <class NB>
+constexpr bool in_lds = false;
+template <typename T>
+constexpr bool in_lds<NbMulti<T>> = true;
+
+template <typename T>
+__device__ __forceinline__ T phi_at(const NbMulti<T> &n, const T *, int cx, int cy, int)
+{
+    return n.phi[n.oy[1 + cy] + n.ox[1 + cx]];
+}
+
 template <class NB>
 constexpr bool in_tile = false;
+template <typename T>
+constexpr bool in_tile<NbMulti<T>> = true;
 template <typename T, bool KEPT>
 constexpr bool in_tile<NbTile<T, KEPT>> = true;
 
@@ -305,6 +330,18 @@ __device__ __forceinline__ void store_out(V v, gptr<E> at)
         *at = v;
     else
         __builtin_nontemporal_store(v, at);
+}
+
+// Post-collision value of direction a of a set in plain storage (0 f', 1 g),
+// to the cell's place in the output array or in LDS.
+template <int SET, class S, class NB, typename T>
+__device__ __forceinline__ void put_pop(const NB &nb, void *out, long long np, int row, int x, int a, T v)
+{
+    if constexpr (in_lds<NB>)
+        nb.pop[(9 * SET + a) * MULTI_CELLS] = v;
+    else
+        store_out<NB>(typename S::raw(v),
+                      lane_ptr(static_cast<typename S::raw *>(out), (long long)a * np + row, x));
 }
 
 // Pre-collision population a of a set in plain storage, where the cell's form
@@ -1110,8 +1147,7 @@ __device__ __forceinline__ void collide_body(const NB &nb, const Geom &g,
             } else {
                 const T v = dev + weight<D, T>(a) * c.pstar;
                 fsum += v;
-                store_out<NB>(typename P::F::raw(v),
-                    lane_ptr(static_cast<typename P::F::raw *>(p.Fout), (long long)a * g.np + row, xl));
+                put_pop<0, typename P::F>(nb, p.Fout, g.np, row, xl, a, v);
             }
         };
         // the rest direction: the remainder of sum f'* = sum f' + sum Xi, so the
@@ -1120,8 +1156,7 @@ __device__ __forceinline__ void collide_body(const NB &nb, const Geom &g,
             if constexpr (P::F::shifted)
                 __builtin_nontemporal_store(float(v0), lane_ptr(p.frest_out, row, xl));
             else
-                store_out<NB>(typename P::F::raw(v0),
-                    lane_ptr(static_cast<typename P::F::raw *>(p.Fout), (long long)(Q / 2) * g.np + row, xl));
+                put_pop<0, typename P::F>(nb, p.Fout, g.np, row, xl, Q / 2, v0);
         };
         if constexpr ((COLL & 1) == 0) {
             // second moments of Xi in closed form (4th-order isotropy of the lattice)
@@ -1240,8 +1275,7 @@ __device__ __forceinline__ void collide_body(const NB &nb, const Geom &g,
                 if constexpr (KEEP) keep[nphi_slot(a) * kstride] = dec;
             } else {
                 gsum += gout;
-                store_out<NB>(typename P::G::raw(gout),
-                    lane_ptr(static_cast<typename P::G::raw *>(p.Gout), (long long)a * g.np + row, xl));
+                put_pop<1, typename P::G>(nb, p.Gout, g.np, row, xl, a, gout);
                 if constexpr (KEEP) keep[nphi_slot(a) * kstride] = gout;
             }
         };
@@ -1318,8 +1352,7 @@ __device__ __forceinline__ void collide_body(const NB &nb, const Geom &g,
             if constexpr (P::G::shifted)
                 __builtin_nontemporal_store(float(g0), lane_ptr(p.grest_out, row, xl));
             else
-                store_out<NB>(typename P::G::raw(g0),
-                    lane_ptr(static_cast<typename P::G::raw *>(p.Gout), (long long)(Q / 2) * g.np + row, xl));
+                put_pop<1, typename P::G>(nb, p.Gout, g.np, row, xl, Q / 2, g0);
             if constexpr (KEEP) *keep_rest = g0;
         };
         cac(std::integral_constant<bool, (COLL & 2) != 0>{});

@@ -72,6 +72,11 @@ hipError_t launch_collide(const Ctx &c);
 bool step2d_ok(int dim, int storage);
 int step2d_tiles(const Geom &g);
 hipError_t launch_step2d(const Ctx &c);
+// Several steps of a small such lattice in one launch, from the Fin/Gin to the
+// Fout/Gout buffers: the number of steps multi2d_steps gives (1: none; single
+// steps instead).
+int multi2d_steps(const Ctx &c);
+hipError_t launch_multi2d(const Ctx &c, int steps);
 // Partial sums of the next order parameter, written by launch_collide_nphi
 // for launch_phi_merge of the following step: part [3][np], edge
 // [2][3][ny / by][nz][nx] in the arithmetic type; by = tile rows,

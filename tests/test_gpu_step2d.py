@@ -2,7 +2,8 @@
 and columns at and beside the tile widths (8 to 64 cells by 256 threads), one
 cell wide or high, every mix of periodic axes, walls and symmetry planes, and
 both collision operators; one step against the FP64 oracle at the one-step
-bars (FP64 1e-12, FP32 2e-6), and a batch of all of them, empty slots between
+bars (FP64 1e-12, FP32 2e-6); runs of steps (several a launch on small lattices)
+bit for bit the same steps one by one; and a batch of all of them, empty slots between
 them, bit for bit the solvers alone over steps launched one by one and as
 graphs."""
 import numpy as np
@@ -38,6 +39,31 @@ def test_one_step_against_the_oracle(storage, bc):
         ef = rel_err(from_abi(2, s.get_populations(0)), f1)
         eg = rel_err(from_abi(2, s.get_populations(1)), g1)
         assert ef < TOL1[storage] and eg < TOL1[storage], (nx, ny, bc, ef, eg)
+
+
+# two, three and four steps a launch (blocks of 16, 12 and 8 cells a side), and single steps
+RUN_SIZES = [(1, 1), (1, 40), (3, 2), (8, 8), (9, 7), (17, 25), (64, 64), (130, 130), (131, 97),
+             (200, 200), (245, 210), (400, 300)]
+
+
+@pytest.mark.parametrize("storage", ["fp64", "fp32"])
+@pytest.mark.parametrize("bc", BCS)
+def test_runs_equal_single_steps_bitwise(storage, bc):
+    for i, (nx, ny) in enumerate(RUN_SIZES):
+        params = params_for(2, (nx, ny, 1), bc + (0,))
+        params["collision"] = i % 2
+        params["cac_edf"] = int(i % 5 == 4)
+        fields = inputs.random_state(params, seed=70 + i)
+        a, b = (mplb.Solver(params, storage=storage) for _ in range(2))
+        a.init(*fields)
+        b.init(*fields)
+        for _ in range(43):
+            a.step(1)
+        for n in (2, 1, 40):  # direct launches, then graphs from either level and a rest
+            b.step(n)
+        assert a.steps_done() == b.steps_done() == 43
+        for w in (0, 1):
+            assert np.array_equal(a.get_populations(w), b.get_populations(w)), (nx, ny, bc, w)
 
 
 @pytest.mark.parametrize("storage", ["fp64", "fp32"])
