@@ -179,7 +179,7 @@ int mplb_step(mplb_solver *s, int64_t nsteps);
 /* As mplb_step, but records HIP events around every kernel launch on the
  * solver's stream and returns the summed device time of the two launches of
  * each step (ms_phi: order-parameter stage; ms_collide: cell update) in
- * milliseconds (2-D lattices in plain storage step in one launch, counted
+ * milliseconds (2-D lattices step in one launch, counted
  * in ms_collide: ms_phi is then 0 or a few microseconds of event overhead a
  * step).  Synchronises the stream.  For profiling; the events add a
  * few microseconds per step.  Design, not in the paper.  Errors: as
@@ -253,8 +253,8 @@ int mplb_save(mplb_solver *s, void *host_blob, size_t bytes);
 int mplb_load(mplb_solver *s, const void *host_blob, size_t bytes);
 
 /* Threads per block of the cell update (x, y, z); (0, 0, 0) = library
- * default (as wide in x as the lattice, up to 256).  2-D lattices in plain
- * storage (FP64, FP32) step in one launch on tiles of the library's own.  Between 1 and 256
+ * default (as wide in x as the lattice, up to 256).  2-D lattices step
+ * in one launch on tiles of the library's own.  Between 1 and 256
  * threads; bz = 1 in 2-D.  Blocks a multiple of 64 wide in x on lattices
  * periodic in x take wavefront-uniform (row-form) addressing; results do not
  * depend on the shape.  Errors: EINVAL.  Design, not in the paper. */
@@ -301,8 +301,8 @@ void mplb_destroy(mplb_solver *s);
  * Batches (design, not in the paper): many independent solvers of one
  * dimension and storage format advance together.  The small ones share
  * launches over a tile list that covers every such lattice, one block per
- * tile: per step a phi launch and an update launch (2-D in plain storage: one
- * launch for both, on tiles of the library's own), plus one launch per row
+ * tile: per step a phi launch and an update launch (2-D: one launch for
+ * both, on tiles of the library's own), plus one launch per row
  * length (64, 128, 192, 256, 512) for the solvers whose update sums the next
  * phi (mplb_set_phi_partials); large ones step with their own kernels beside
  * them (mplb_batch_set_solo_cells).  Each

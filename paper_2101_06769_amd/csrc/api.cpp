@@ -55,7 +55,7 @@ struct Layout {
     int Q;
     long long N, np;
     size_t sF, sG, sT;
-    size_t F[2], G[2], phi, ref, frest[2], grest[2], phiu[2], npart, nedge, partials, result, total;
+    size_t F[2], G[2], phi, ref[2], frest[2], grest[2], phiu[2], npart, nedge, partials, result, total;
     size_t staging_bytes;
     size_t bF, bG;  // bytes of one population set of each kind (rounded to ALIGN)
 };
@@ -127,9 +127,14 @@ Layout make_layout(const mplb_params *p)
     L.phi = off;
     off += up(L.np * (f16 ? 8 : L.sT), ALIGN);
     const size_t b4 = up(L.np * 4, ALIGN);
-    L.ref = 0;
+    L.ref[0] = L.ref[1] = 0;
     if (f16) {
-        L.ref = off;
+        L.ref[0] = L.ref[1] = off;
+        off += b4;
+    }
+    if (f16 && p->dim == 2) {
+        // one-launch steps write the next level's references while others read
+        L.ref[1] = off;
         off += b4;
     }
     for (int k = 0; k < 2; ++k) {
@@ -263,7 +268,7 @@ struct mplb_solver {
     }
     // The step is one launch, which sums phi in its blocks and leaves the phi
     // array alone.
-    bool one_launch() const { return mplb::step2d_ok(prm.dim, prm.storage); }
+    bool one_launch() const { return prm.dim == 2; }
     // Steps that one launch takes in a run of steps (1: single steps).
     int multi_steps() const { return mplb::multi2d_steps(ctx(0)); }
     // The phi array of the current level for a reader of it between steps.
@@ -312,7 +317,8 @@ struct mplb_solver {
         c.p.Fout = F(1 - in);
         c.p.Gout = G(1 - in);
         c.p.phi = base + L.phi;
-        c.p.ref = static_cast<unsigned *>(at(L.ref));
+        c.p.ref_in = static_cast<const unsigned *>(at(L.ref[in]));
+        c.p.ref = static_cast<unsigned *>(at(L.ref[1 - in]));
         c.p.frest_in = static_cast<const float *>(at(L.frest[in]));
         c.p.grest_in = static_cast<const float *>(at(L.grest[in]));
         c.p.frest_out = static_cast<float *>(at(L.frest[1 - in]));
@@ -332,7 +338,7 @@ struct mplb_solver {
         r.push_back({L.F[k], L.bF});
         r.push_back({L.G[k], L.bG});
         const size_t b4 = up(L.np * 4, ALIGN);
-        if (L.ref) r.push_back({L.ref, b4});
+        if (L.ref[k]) r.push_back({L.ref[k], b4});
         if (L.frest[k]) r.push_back({L.frest[k], b4});
         if (L.grest[k]) r.push_back({L.grest[k], b4});
         if (L.phiu[k]) r.push_back({L.phiu[k], size_t(3) * L.np * L.sT});
@@ -923,8 +929,8 @@ struct mplb_batch {
     int *d_ntiles;
     long long *d_tbase;
     int *d_status;  // per slot: non-zero once the phi stage met a non-finite value
-    // 2-D domains in plain storage: one launch per step over step2d tiles
-    bool one_launch() const { return mplb::step2d_ok(dim, storage); }
+    // 2-D domains: one launch per step over step2d tiles
+    bool one_launch() const { return dim == 2; }
     int *d_table2d;  // see launch_batch_step2d
     std::vector<mplb_solver *> slot;
     std::vector<mplb::BatchDom> doms;
@@ -934,8 +940,8 @@ struct mplb_batch {
     struct Group {
         bool kept;  // its populations stay in the Infinity Cache
         int grid[2 + mplb::NPHI_GROUPS];  // blocks of the phi, update and phi-summing update
-                                          // launches (0 for none); grid[0] the only one in 2-D plain
-                                          // storage: tile counts rounded up by at most an eighth,
+                                          // launches (0 for none), grid[0] the only one in 2-D:
+                                          // tile counts rounded up by at most an eighth,
                                           // so that a captured graph survives most changes
         bool operator==(const Group &) const = default;
     };
@@ -1307,6 +1313,7 @@ int mplb_batch_attach(mplb_batch *b, mplb_solver *s, int64_t nsteps, int32_t *sl
     for (int j = 0; j < 2; ++j) {
         d.F[j] = s->F(j);
         d.G[j] = s->G(j);
+        d.ref[j] = static_cast<unsigned *>(s->at(s->L.ref[j]));
         d.frest[j] = static_cast<float *>(s->at(s->L.frest[j]));
         d.grest[j] = static_cast<float *>(s->at(s->L.grest[j]));
         d.phiu[j] = s->at(s->L.phiu[j]);
@@ -1314,7 +1321,6 @@ int mplb_batch_attach(mplb_batch *b, mplb_solver *s, int64_t nsteps, int32_t *sl
     // the domain's first batch step is b->t: history from there if it has one
     d.hist_from = s->hist ? b->t : b->t + 1;
     d.phi = s->base + s->L.phi;
-    d.ref = static_cast<unsigned *>(s->at(s->L.ref));
     // the phi-summing update: upload_tables sets nphi_by and the pointers; a
     // solver whose last update left partial sums merges them at its first
     // batch step, as its own next step would
@@ -1401,7 +1407,7 @@ hipError_t shared_steps(mplb_batch *b, int n)
                     ? mplb::launch_batch_step2d(b->storage, b->collision, gr.kept, b->d_doms, b->d_table2d,
                                                 b->capacity, int(gi), b->d_tbase, k, gr.grid[0],
                                                 b->d_status, b->side)
-                    : mplb::launch_batch_step(b->dim, b->storage, b->collision, b->form, gr.kept, b->d_doms,
+                    : mplb::launch_batch_step(b->storage, b->collision, b->form, gr.kept, b->d_doms,
                                               b->d_tiles, b->d_ntiles + gi * mplb::GROUP_INTS, b->d_tbase,
                                               k, b->block, gr.grid, b->d_status, b->side);
     }

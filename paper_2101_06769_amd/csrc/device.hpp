@@ -307,6 +307,23 @@ constexpr bool in_tile<NbMulti<T>> = true;
 template <typename T, bool KEPT>
 constexpr bool in_tile<NbTile<T, KEPT>> = true;
 
+// The same in the FP16 formats: the tile holds the records (phi, references),
+// and the codes are pulled from memory through NB's addressing.
+template <class NB, bool KEPT>
+struct NbTile16 : NB {
+    const unsigned long long *lrec;
+    int ls;
+};
+template <class NB, bool KEPT>
+constexpr bool in_tile<NbTile16<NB, KEPT>> = true;
+
+template <class NB, bool KEPT>
+__device__ __forceinline__ unsigned long long phi_at(const NbTile16<NB, KEPT> &n, const unsigned long long *,
+                                                     int cx, int cy, int)
+{
+    return n.lrec[cy * n.ls + cx];
+}
+
 template <typename T, bool KEPT>
 __device__ __forceinline__ T phi_at(const NbTile<T, KEPT> &n, const T *, int cx, int cy, int)
 {
@@ -319,6 +336,8 @@ template <class NB>
 constexpr bool is_kept<Kept<NB>> = true;
 template <typename T>
 constexpr bool is_kept<NbTile<T, true>> = true;
+template <class NB>
+constexpr bool is_kept<NbTile16<NB, true>> = true;
 
 // Stores a post-collision value: non-temporally, or (a form whose kept is set)
 // as an ordinary store, which leaves it in the Infinity Cache for the next
@@ -487,7 +506,9 @@ template <bool BUF, class NB>
 __device__ __forceinline__ void store_code(const NB &, void *base, long long plane, int row, int x,
                                            unsigned short bits)
 {
-    if constexpr (BUF && !std::is_base_of<NbLane, NB>::value) {
+    if constexpr (is_kept<NB>) {
+        *lane_ptr(static_cast<unsigned short *>(base), plane + row, x) = bits;
+    } else if constexpr (BUF && !std::is_base_of<NbLane, NB>::value) {
         // raw buffer (stride 0) without a range limit; word 3 as gfx9 takes it for
         // untyped accesses; cache policy 2: non-temporal
         const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(
@@ -669,8 +690,8 @@ __device__ __forceinline__ void eval_cell16_paired(const NB &nb, long long np, c
         lap += w * ((pp - p0) + (pm - p0));
         if (gref) gref[a - (Q / 2 + 1)] = unsigned(half_bits(pp)) | (unsigned(half_bits(pm)) << 16);
         const PullLoc la = pull_loc<D>(nb, a), lb = pull_loc<D>(nb, b);
-        const float qa = load_code<true>(nb, p.Fin, (long long)la.dir * np, la);
-        const float qb = load_code<true>(nb, p.Fin, (long long)lb.dir * np, lb);
+        const float qa = load_code<!is_kept<NB>>(nb, p.Fin, (long long)la.dir * np, la);
+        const float qb = load_code<!is_kept<NB>>(nb, p.Fin, (long long)lb.dir * np, lb);
         // the reference words selected as integers: no branch on the
         // (wavefront-uniform in the row form) bounce-back flags
         const Ref16 ra = unpack_ref(la.bb ? own_bits : rec_ref(rm));
@@ -996,7 +1017,7 @@ __device__ __forceinline__ void store_phi(const NB &nb, const Ptrs &p, typename 
     using T = typename P::T;
     // non-temporal: read a launch later
     if constexpr (P::F::shifted)
-        __builtin_nontemporal_store(make_rec(v, own_at(nb, static_cast<const unsigned *>(p.ref))),
+        __builtin_nontemporal_store(make_rec(v, own_at(nb, p.ref_in)),
                                     lane_ptr(static_cast<unsigned long long *>(p.phi), nb.row, nb.x));
     else
         store_out<NB>(v, lane_ptr(static_cast<T *>(p.phi), nb.row, nb.x));
@@ -1014,14 +1035,14 @@ __device__ __forceinline__ typename P::T phi_value(const NB &nb, long long np, c
         // the writer's phi over that sum: where a cell receives the values it
         // sent (a uniform region) the sum reproduces its phi exactly, so the
         // rounding of the sums leaves the phase mass without bias
-        const float F = unpack_ref(own_at(nb, static_cast<const unsigned *>(p.ref))).F;
+        const float F = unpack_ref(own_at(nb, p.ref_in)).F;
         T m = 0;
 #pragma unroll
         for (int a = Q / 2 + 1; a < Q; ++a) {
             const int b = opposite<D>(a);
             const PullLoc la = pull_loc<D>(nb, a), lb = pull_loc<D>(nb, b);
-            m += dec_g16(weight<D, float>(a), F, load_code<true>(nb, p.Gin, (long long)la.dir * np, la));
-            m += dec_g16(weight<D, float>(b), F, load_code<true>(nb, p.Gin, (long long)lb.dir * np, lb));
+            m += dec_g16(weight<D, float>(a), F, load_code<!is_kept<NB>>(nb, p.Gin, (long long)la.dir * np, la));
+            m += dec_g16(weight<D, float>(b), F, load_code<!is_kept<NB>>(nb, p.Gin, (long long)lb.dir * np, lb));
         }
         s = own_at(nb, p.grest_in) + m;
     } else {
@@ -1154,7 +1175,7 @@ __device__ __forceinline__ void collide_body(const NB &nb, const Geom &g,
         // zeroth moment does not drift with the rounding of the stored values
         auto emit_rest = [&](T v0) {
             if constexpr (P::F::shifted)
-                __builtin_nontemporal_store(float(v0), lane_ptr(p.frest_out, row, xl));
+                store_out<NB>(float(v0), lane_ptr(p.frest_out, row, xl));
             else
                 put_pop<0, typename P::F>(nb, p.Fout, g.np, row, xl, Q / 2, v0);
         };
@@ -1226,7 +1247,11 @@ __device__ __forceinline__ void collide_body(const NB &nb, const Geom &g,
                         v = own_at(nb, p.frest_in);
                     } else {
                         const PullLoc l = pull_loc<D>(nb, a);
-                        const Ref16 R = unpack_ref(rec_ref(l.bb ? own_at(nb, rec) : load_loc(nb, rec, 0, l)));
+                        Ref16 R;
+                        if constexpr (in_tile<NB>)
+                            R = unpack_ref(rec_ref(l.bb ? phi_at(nb, rec, 0, 0, 0) : phi_at(nb, rec, -cx, -cy, -cz)));
+                        else
+                            R = unpack_ref(rec_ref(l.bb ? own_at(nb, rec) : load_loc(nb, rec, 0, l)));
                         v = dec_f16(weight<D, float>(a), R, flow_scale16(ph, R.F),
                                     load_code(nb, p.Fin, (long long)l.dir * g.np, l));
                     }
@@ -1247,7 +1272,7 @@ __device__ __forceinline__ void collide_body(const NB &nb, const Geom &g,
             }
         }
         // non-temporal, as the codes: the order-parameter stage reads it a launch later
-        if constexpr (P::F::shifted) __builtin_nontemporal_store(rw, lane_ptr(p.ref, row, xl));
+        if constexpr (P::F::shifted) store_out<NB>(rw, lane_ptr(p.ref, row, xl));
     };
 
     // --- phase field (Sec. 2.2)
@@ -1310,7 +1335,7 @@ __device__ __forceinline__ void collide_body(const NB &nb, const Geom &g,
                     } else if constexpr (P::G::shifted) {
                         const PullLoc l = pull_loc<D>(nb, a);
                         pre[a] = dec_g16(weight<D, float>(a), c.Fown,
-                                         load_code<true>(nb, p.Gin, (long long)l.dir * g.np, l));
+                                         load_code<!is_kept<NB>>(nb, p.Gin, (long long)l.dir * g.np, l));
                     } else {
                         pre[a] = pull<D, typename P::G, T>(nb, p.Gin, g.np, a);
                     }
@@ -1350,7 +1375,7 @@ __device__ __forceinline__ void collide_body(const NB &nb, const Geom &g,
             }
             const T g0 = c.phi - gsum;
             if constexpr (P::G::shifted)
-                __builtin_nontemporal_store(float(g0), lane_ptr(p.grest_out, row, xl));
+                store_out<NB>(float(g0), lane_ptr(p.grest_out, row, xl));
             else
                 put_pop<1, typename P::G>(nb, p.Gout, g.np, row, xl, Q / 2, g0);
             if constexpr (KEEP) *keep_rest = g0;
@@ -1637,7 +1662,7 @@ __device__ __forceinline__ typename P::T nphi_merge_cell(const Geom &g, const Pt
     }
     const T s = nphi_merge_sum(g, v, z, first, last);
     if constexpr (P::F::shifted)
-        __builtin_nontemporal_store(make_rec(s, *lane_ptr(static_cast<const unsigned *>(p.ref), row, x)),
+        __builtin_nontemporal_store(make_rec(s, *lane_ptr(p.ref_in, row, x)),
                                     lane_ptr(static_cast<unsigned long long *>(p.phi), row, x));
     else
         store_out<NB>(s, lane_ptr(static_cast<T *>(p.phi), row, x));
@@ -1662,7 +1687,8 @@ __device__ __forceinline__ Ptrs batch_ptrs(const BatchDom &d, int in, bool have_
     p.Fout = d.F[1 - in];
     p.Gout = d.G[1 - in];
     p.phi = d.phi;
-    p.ref = d.ref;
+    p.ref_in = d.ref[in];
+    p.ref = d.ref[1 - in];
     p.frest_in = d.frest[in];
     p.grest_in = d.grest[in];
     p.frest_out = d.frest[1 - in];

@@ -50,6 +50,10 @@ struct Ptrs {
     const void *phiu_in;
     void *phiu_out;
     int have_prev;
+    // FP16 formats: the references of the values the cells wrote a step
+    // earlier (ref itself, read by the phi stage before the update writes it;
+    // another array where the step is one launch)
+    const unsigned *ref_in;
 };
 
 struct Ctx {
@@ -64,15 +68,13 @@ struct Ctx {
 
 hipError_t launch_phi(const Ctx &c);
 hipError_t launch_collide(const Ctx &c);
-// The whole step of a 2-D lattice in plain storage (FP64, FP32) in one launch:
-// each block sums phi for its tile and the ring of cells around it into LDS,
-// then updates its cells; the phi array is not written.  step2d_ok tells
-// whether it applies.  Its tiles (step2d_tiles of them) do not depend on the
-// context's block.
-bool step2d_ok(int dim, int storage);
+// The whole step of a 2-D lattice in one launch: each block sums phi for its
+// tile and the ring of cells around it into LDS, then updates its cells; the
+// phi array is not written.  Its tiles (step2d_tiles of them) do not depend on
+// the context's block.
 int step2d_tiles(const Geom &g);
 hipError_t launch_step2d(const Ctx &c);
-// Several steps of a small such lattice in one launch, from the Fin/Gin to the
+// Several steps of a small such lattice in plain storage in one launch, from the Fin/Gin to the
 // Fout/Gout buffers: the number of steps multi2d_steps gives (1: none; single
 // steps instead).
 int multi2d_steps(const Ctx &c);
@@ -133,7 +135,7 @@ struct BatchDom {
     Geom g;
     PhysD ph;
     void *F[2], *G[2], *phi;
-    unsigned *ref;
+    unsigned *ref[2];
     float *frest[2], *grest[2];
     void *phiu[2];
     long long first, last;  // active for batch steps first <= t < last
@@ -159,8 +161,7 @@ struct BatchTile {
 // steps before the next group does.  At most BATCH_GROUPS groups.
 constexpr int BATCH_GROUPS = 32;
 
-// One step of a group of 2-D domains in plain storage (step2d_ok) in one
-// launch.  table: two ints per group (first position and number of domains),
+// One step of a group of 2-D domains in one launch.  table: two ints per group (first position and number of domains),
 // then the domains by position, then per group its running tile counts
 // (step2d_tiles; number of domains + 1 entries, so position + group is their
 // start).  Blocks beyond the last count exit.  status as for launch_batch_step.
@@ -176,11 +177,12 @@ bool kept_in_cache(int dim, int storage, long long np);
 bool row_form_ok(int dim, const Geom &g, dim3 block);
 // Addressing of a launch: per lane, rows, or packed planes (3-D).
 enum { FORM_LANE, FORM_ROW, FORM_PACK };
-// One step of a group over the tile list, batch step index *tbase + step_off.
+// One step of a group of 3-D domains over the tile list, batch step index *tbase +
+// step_off.
 // collision: operator code, bit 0 the flow collision, bit 1 the first-order
 // phase-field equilibrium (shared by all domains).  form: FORM_ROW where
 // every domain the block kernels update satisfies row_form_ok with its tile
-// width, FORM_PACK where each is 3-D, periodic in x and y and within 32-bit
+// width, FORM_PACK where each is periodic in x and y and within 32-bit
 // indices (tiles of w = 0).
 // ntiles, GROUP_INTS of them: the group's first tile; the number of block
 // tiles of the domains the block kernels update, which come first; that number
@@ -193,7 +195,7 @@ enum { FORM_LANE, FORM_ROW, FORM_PACK };
 // status[dom] is or-ed with 1 when the phi stage finds a non-finite order
 // parameter in that domain.
 constexpr int GROUP_INTS = 16;
-hipError_t launch_batch_step(int dim, int storage, int collision, int form, bool kept,
+hipError_t launch_batch_step(int storage, int collision, int form, bool kept,
                              const BatchDom *doms, const BatchTile *tiles, const int *ntiles,
                              const long long *tbase, int step_off, dim3 block, const int *grid,
                              int *status, hipStream_t stream);

@@ -70,7 +70,7 @@ kb_step2d(const BatchDom *__restrict__ doms, const int *__restrict__ table, int 
           const long long *tbase, int step_off, int *status)
 {
     using T = typename P::T;
-    __shared__ T lphi[step2d_slots()];
+    __shared__ typename std::conditional<P::F::shifted, unsigned long long, T>::type lds[step2d_slots()];
     const int pos = table[2 * group], n = table[2 * group + 1];
     const int *ids = table + 2 * BATCH_GROUPS + pos, *tile0 = table + 2 * BATCH_GROUPS + capacity + pos + group;
     const int nt = tile0[n];
@@ -95,27 +95,30 @@ kb_step2d(const BatchDom *__restrict__ doms, const int *__restrict__ table, int 
     const int lbx = step2d_width(g.nx), by = STEP2D_THREADS >> lbx;
     const int ntx = (g.nx + (1 << lbx) - 1) >> lbx, k = bid - tile0[at];
     const int x0 = (k % ntx) << lbx, y0 = (k / ntx) * by;
-    if (lbx == 6)
-        step2d_tile<P, COLL, true, KEPT>(g, ph, p, lphi, lbx, x0, y0, status + dom);
-    else
-        step2d_tile<P, COLL, false, KEPT>(g, ph, p, lphi, lbx, x0, y0, status + dom);
+    step2d_any<P, COLL, KEPT>(g, ph, p, lds, step2d_rows<P>(g, lbx), lbx, x0, y0, status + dom);
 }
 
 hipError_t launch_batch_step2d(int storage, int collision, bool kept, const BatchDom *doms,
                                const int *table, int capacity, int group, const long long *tbase,
                                int step_off, int grid, int *status, hipStream_t stream)
 {
-    if (!step2d_ok(2, storage)) return hipErrorInvalidValue;
-    return with_coll(collision, [&](auto cc) {
-        constexpr int COLL = decltype(cc)::value;
-        auto go = [&](auto kernel) {
-            hipLaunchKernelGGL(kernel, dim3(grid), dim3(STEP2D_THREADS), 0, stream, doms, table, capacity,
-                               group, tbase, step_off, status);
-            return hipGetLastError();
-        };
-        if (storage == ST_FP64)
-            return kept ? go(kb_step2d<P64, COLL, true>) : go(kb_step2d<P64, COLL, false>);
-        return kept ? go(kb_step2d<P32, COLL, true>) : go(kb_step2d<P32, COLL, false>);
+    Ctx c{};
+    c.dim = 2;
+    c.storage = storage;
+    return dispatch(c, [&]<int D, class P>() -> hipError_t {
+        if constexpr (D != 2) {
+            return hipErrorInvalidValue;
+        } else {
+            return with_coll(collision, [&](auto cc) {
+                constexpr int COLL = decltype(cc)::value;
+                auto go = [&](auto kernel) {
+                    hipLaunchKernelGGL(kernel, dim3(grid), dim3(STEP2D_THREADS), 0, stream, doms, table, capacity,
+                                       group, tbase, step_off, status);
+                    return hipGetLastError();
+                };
+                return kept ? go(kb_step2d<P, COLL, true>) : go(kb_step2d<P, COLL, false>);
+            });
+        }
     });
 }
 
@@ -127,13 +130,13 @@ __global__ void __launch_bounds__(256) k_fill_i32(int *ptr, int n, int v)
     if (i < n) ptr[i] = v;
 }
 
-hipError_t launch_batch_step(int dim, int storage, int collision, int form, bool kept,
+hipError_t launch_batch_step(int storage, int collision, int form, bool kept,
                              const BatchDom *doms, const BatchTile *tiles, const int *ntiles,
                              const long long *tbase, int step_off, dim3 block, const int *grid,
                              int *status, hipStream_t stream)
 {
     Ctx c{};
-    c.dim = dim;
+    c.dim = 3;
     c.storage = storage;
     auto step = [&]<int D, class P, class NB, int FORM>() -> hipError_t {
         auto go = [&](auto k, int nblk, size_t lds) {
@@ -152,13 +155,12 @@ hipError_t launch_batch_step(int dim, int storage, int collision, int form, bool
         });
     };
     return dispatch(c, [&]<int D, class P>() -> hipError_t {
-        // 2-D domains in plain storage step in one launch (launch_batch_step2d)
-        if constexpr (D == 2 && !P::F::shifted) {
-            return hipErrorInvalidValue;
+        if constexpr (D == 2) {
+            return hipErrorInvalidValue;  // one launch: launch_batch_step2d
         } else {
             auto by_form = [&]<int FORM>() -> hipError_t {
                 using NB = NbOf<FORM>;
-                if constexpr (D == 3 && !P::F::shifted) {
+                if constexpr (!P::F::shifted) {
                     if (kept) return step.template operator()<D, P, Kept<NB>, FORM>();
                 }
                 return step.template operator()<D, P, NB, FORM>();
@@ -168,10 +170,10 @@ hipError_t launch_batch_step(int dim, int storage, int collision, int form, bool
                 e = by_form.template operator()<FORM_LANE>();
             } else if (form == FORM_ROW) {
                 e = by_form.template operator()<FORM_ROW>();
-            } else if constexpr (D == 3) {
+            } else {
                 e = by_form.template operator()<FORM_PACK>();
             }
-            if (e == hipSuccess && D == 3)
+            if (e == hipSuccess)
                 e = launch_batch_nphi(storage, collision, kept, doms, tiles, ntiles, tbase, step_off, grid, stream);
             return e;
         }

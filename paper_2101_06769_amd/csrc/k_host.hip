@@ -55,7 +55,7 @@ __device__ __forceinline__ double get_value(const Geom &g, const Ptrs &p, const 
     if (which == 0) {
         if constexpr (P::F::shifted) {
             if (a == Q / 2) return p.frest_in[me];
-            const Ref16 R = unpack_ref(p.ref[cell]);
+            const Ref16 R = unpack_ref(p.ref_in[cell]);
             return dec_f16(weight<D, float>(a), R, flow_scale16(pf, R.F),
                            half_val(static_cast<const unsigned short *>(p.Fin)[e]));
         } else {
@@ -64,7 +64,7 @@ __device__ __forceinline__ double get_value(const Geom &g, const Ptrs &p, const 
     } else {
         if constexpr (P::G::shifted) {
             if (a == Q / 2) return p.grest_in[me];
-            return dec_g16(weight<D, float>(a), unpack_ref(p.ref[me]).F,
+            return dec_g16(weight<D, float>(a), unpack_ref(p.ref_in[me]).F,
                            half_val(static_cast<const unsigned short *>(p.Gin)[e]));
         } else {
             return double(static_cast<const typename P::G::raw *>(p.Gin)[e]);

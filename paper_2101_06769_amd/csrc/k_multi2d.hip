@@ -134,7 +134,7 @@ static long long multi2d_tiles(const Geom &g, int steps)
 int multi2d_steps(const Ctx &c)
 {
     // the first-order phase-field equilibrium keeps (phi u) of every step in memory
-    if (!step2d_ok(c.dim, c.storage) || c.ph.cac_edf) return 1;
+    if (c.dim != 2 || (c.storage != ST_FP64 && c.storage != ST_FP32) || c.ph.cac_edf) return 1;
     for (int steps = 4; steps > 1; --steps)
         if (multi2d_tiles(c.g, steps) <= 256) return steps;
     return 1;

@@ -76,7 +76,7 @@ __global__ void __launch_bounds__(256) k_phi_merge(Geom g, Ptrs p, NextPhi q)
         const long long row = (long long)(z * g.ny + y) * g.nx;
         const T s = nphi_merge_sum(g, v[k], z, first, last);
         if constexpr (P::F::shifted)
-            __builtin_nontemporal_store(make_rec(s, *lane_ptr(static_cast<const unsigned *>(p.ref), row, x)),
+            __builtin_nontemporal_store(make_rec(s, *lane_ptr(p.ref_in, row, x)),
                                         lane_ptr(static_cast<unsigned long long *>(p.phi), row, x));
         else
             store_out<NB>(s, lane_ptr(static_cast<T *>(p.phi), row, x));

@@ -57,9 +57,8 @@ hipError_t launch_collide(const Ctx &c)
 {
     return dispatch(c, [&]<int D, class P>() -> hipError_t {
         using T = typename P::T;
-        // 2-D lattices in plain storage step in one launch (launch_step2d)
-        if constexpr (D == 2 && !P::F::shifted) {
-            return hipErrorInvalidValue;
+        if constexpr (D == 2) {
+            return hipErrorInvalidValue;  // one launch: launch_step2d
         } else {
             return with_coll(coll_code(c.ph), [&](auto cc) {
                 constexpr int COLL = decltype(cc)::value;

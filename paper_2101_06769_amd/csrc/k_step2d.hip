@@ -7,17 +7,15 @@ namespace mplb {
 // the tiles, so that the rows two tiles share are read through one L2
 // (1024 x 1024 FP32: 38.2 -> 36.9 us, 800 x 400: 15.0 -> 13.4 us with an earlier
 // form of the kernel).
-template <class P, int COLL, bool ROWU, bool KEPT>
+template <class P, int COLL, bool ROWS, bool KEPT>
 __global__ void __launch_bounds__(STEP2D_THREADS)
 k_step2d(Geom g, Phys<typename P::T> ph, Ptrs p, int lbx, int ntx)
 {
-    __shared__ typename P::T lphi[step2d_slots()];
+    __shared__ typename std::conditional<P::F::shifted, unsigned long long, typename P::T>::type lds[step2d_slots()];
     const int bid = tile_of<true>(int(blockIdx.x), int(gridDim.x));
-    const int by = ROWU ? STEP2D_THREADS / 64 : STEP2D_THREADS >> lbx;
-    step2d_tile<P, COLL, ROWU, KEPT>(g, ph, p, lphi, lbx, (bid % ntx) << lbx, (bid / ntx) * by);
+    const int x0 = (bid % ntx) << lbx, y0 = (bid / ntx) * (STEP2D_THREADS >> lbx);
+    step2d_any<P, COLL, KEPT>(g, ph, p, lds, ROWS, lbx, x0, y0, nullptr);
 }
-
-bool step2d_ok(int dim, int storage) { return dim == 2 && (storage == ST_FP64 || storage == ST_FP32); }
 
 int step2d_tiles(const Geom &g)
 {
@@ -27,23 +25,25 @@ int step2d_tiles(const Geom &g)
 
 hipError_t launch_step2d(const Ctx &c)
 {
-    if (!step2d_ok(c.dim, c.storage)) return hipErrorInvalidValue;
     const int lbx = step2d_width(c.g.nx);
     const int ntx = (c.g.nx + (1 << lbx) - 1) >> lbx;
     const bool kept = kept_in_cache(2, c.storage, c.g.np);
-    return with_coll(coll_code(c.ph), [&](auto cc) {
-        constexpr int COLL = decltype(cc)::value;
-        auto go = [&]<class P>(P *) {
+    return dispatch(c, [&]<int D, class P>() -> hipError_t {
+        if constexpr (D != 2) {
+            return hipErrorInvalidValue;
+        } else {
             auto launch = [&](auto kernel) {
                 hipLaunchKernelGGL(kernel, dim3(step2d_tiles(c.g)), dim3(STEP2D_THREADS), 0,
                                    c.stream, c.g, to_phys<typename P::T>(c.ph), c.p, lbx, ntx);
                 return hipGetLastError();
             };
-            if (lbx < 6)
-                return kept ? launch(k_step2d<P, COLL, false, true>) : launch(k_step2d<P, COLL, false, false>);
-            return kept ? launch(k_step2d<P, COLL, true, true>) : launch(k_step2d<P, COLL, true, false>);
-        };
-        return c.storage == ST_FP64 ? go((P64 *)nullptr) : go((P32 *)nullptr);
+            return with_coll(coll_code(c.ph), [&](auto cc) {
+                constexpr int COLL = decltype(cc)::value;
+                if (!step2d_rows<P>(c.g, lbx))
+                    return kept ? launch(k_step2d<P, COLL, false, true>) : launch(k_step2d<P, COLL, false, false>);
+                return kept ? launch(k_step2d<P, COLL, true, true>) : launch(k_step2d<P, COLL, true, false>);
+            });
+        }
     });
 }
 

@@ -1,4 +1,4 @@
-// The one-launch step of 2-D lattices in plain storage: a block sums phi for
+// The one-launch step of 2-D lattices: a block sums phi for
 // its tile and the ring of cells around it into LDS, then updates its cells.
 // A separate phi pass costs a launch (2.6 of the 7.0 us of a 64 x 256 FP64
 // step) and reads the phase-field set twice (40 of 188 B/cell).  The sums, the
@@ -196,6 +196,85 @@ __device__ __forceinline__ void step2d_tile(const Geom &g, const Phys<typename P
 {
     NbTile<typename P::T, KEPT> nb;
     if (step2d_load<P, ROWU, KEPT>(g, p, lphi, lbx, x0, y0, flag, nb)) collide_body<2, P, COLL>(nb, g, ph, p);
+}
+
+// One tile of the step in the FP16 formats (NB: NbRow, bx = 64, or NbLane).
+// The references of the level are in p.ref_in, and the update writes the next
+// level's to another array, since neighbouring blocks still read these.
+template <class P, int COLL, class NB, bool KEPT>
+__device__ __forceinline__ void step2d_tile16(const Geom &g, const Phys<float> &ph, const Ptrs &p,
+                                              unsigned long long *lrec, int lbx, int x0, int y0,
+                                              int *flag = nullptr)
+{
+    constexpr bool ROWU = std::is_same<NB, NbRow>::value;
+    const int bx = ROWU ? 64 : 1 << lbx, by = STEP2D_THREADS / bx, ls = bx + 2;
+    const int tid = int(threadIdx.x);
+    const int tx = tid & (bx - 1);
+    const int ty = ROWU ? __builtin_amdgcn_readfirstlane(tid >> 6) : tid >> lbx;
+    const int w = min(bx, g.nx - x0), h = min(by, g.ny - y0);
+    auto slot = [&](int i, int j) { return lrec + (j + 1) * ls + i + 1; };
+    auto record = [&](const auto &nb, unsigned long long *to) {
+        const float s = phi_value<2, P>(nb, g.np, p);
+        *to = make_rec(s, own_at(nb, p.ref_in));
+        return s;
+    };
+    // the ring: beyond walls and symmetry planes the mirrored cell's record
+    auto ring = [&](auto *form, int i, int j) {
+        record(make_nb(g, stencil_coord(x0 + i, g.nx, g.bcx), stencil_coord(y0 + j, g.ny, g.bcy), 0, form),
+               slot(i, j));
+    };
+    const bool active = tx < w && ty < h;
+    NbTile16<NB, KEPT> nb;
+    if (active) {
+        static_cast<NB &>(nb) = make_nb(g, x0 + tx, y0 + ty, 0, (NB *)nullptr);
+        nb.lrec = slot(tx, ty);
+        nb.ls = ls;
+        const float s = record(nb, slot(tx, ty));
+        if (flag && !__builtin_isfinite(s)) atomicOr(flag, 1);
+    }
+    if constexpr (ROWU) {
+        if (ty < 2) {
+            if (tx < w) ring((Kept<NB> *)nullptr, tx, ty == 0 ? -1 : h);
+        } else if (ty == 2) {
+            const int n = h + 2;
+            if (tx < 2 * n) ring((Kept<NbLane> *)nullptr, tx < n ? -1 : w, (tx < n ? tx : tx - n) - 1);
+        }
+    } else if (tid < 2 * (w + 2 + h)) {
+        const int k = tid - 2 * (w + 2);
+        if (k < 0)
+            ring((Kept<NbLane> *)nullptr, (tid < w + 2 ? tid : tid - (w + 2)) - 1, tid < w + 2 ? -1 : h);
+        else
+            ring((Kept<NbLane> *)nullptr, k < h ? -1 : w, k < h ? k : k - h);
+    }
+    __syncthreads();
+    if (active) collide_body<2, P, COLL>(nb, g, ph, p);
+}
+
+// One tile in any format.  rows: the row forms apply (step2d_rows).
+template <class P, int COLL, bool KEPT>
+__device__ __forceinline__ void step2d_any(const Geom &g, const Phys<typename P::T> &ph, const Ptrs &p,
+                                           void *lds, bool rows, int lbx, int x0, int y0, int *flag)
+{
+    if constexpr (P::F::shifted) {
+        auto *lrec = static_cast<unsigned long long *>(lds);
+        if (rows)
+            step2d_tile16<P, COLL, NbRow, KEPT>(g, ph, p, lrec, lbx, x0, y0, flag);
+        else
+            step2d_tile16<P, COLL, NbLane, KEPT>(g, ph, p, lrec, lbx, x0, y0, flag);
+    } else {
+        auto *lphi = static_cast<typename P::T *>(lds);
+        if (rows)
+            step2d_tile<P, COLL, true, KEPT>(g, ph, p, lphi, lbx, x0, y0, flag);
+        else
+            step2d_tile<P, COLL, false, KEPT>(g, ph, p, lphi, lbx, x0, y0, flag);
+    }
+}
+// Tiles of whole wavefronts; in the FP16 formats, whose pulls take the 3-D
+// kernels' forms, also x periodic and 32-bit indices.
+template <class P>
+__host__ __device__ inline bool step2d_rows(const Geom &g, int lbx)
+{
+    return lbx == 6 && (!P::F::shifted || (g.bcx == BC_PER && 9 * g.np < (1ll << 31)));
 }
 
 }  // namespace mplb

@@ -1,4 +1,4 @@
-"""The one-launch 2-D step (plain storage) where its tiles can go wrong: rows
+"""The one-launch 2-D step where its tiles can go wrong: rows
 and columns at and beside the tile widths (8 to 64 cells by 256 threads), one
 cell wide or high, every mix of periodic axes, walls and symmetry planes, and
 both collision operators; one step against the FP64 oracle at the one-step
@@ -66,7 +66,29 @@ def test_runs_equal_single_steps_bitwise(storage, bc):
             assert np.array_equal(a.get_populations(w), b.get_populations(w)), (nx, ny, bc, w)
 
 
-@pytest.mark.parametrize("storage", ["fp64", "fp32"])
+@pytest.mark.parametrize("storage", ["fp16s", "fp16s_all"])
+@pytest.mark.parametrize("bc", [(0, 0), (0, 1), (1, 2), (2, 1)])
+def test_fp16_checkpoints_at_either_level(storage, bc):
+    # the references of a level lie in one of two arrays; a state saved at
+    # either resumes bit for bit, and fields and populations read between
+    # steps leave it alone
+    for i, (nx, ny) in enumerate(SIZES):
+        params = params_for(2, (nx, ny, 1), bc + (0,))
+        params["collision"] = i % 2
+        fields = inputs.random_state(params, seed=90 + i)
+        a, b = (mplb.Solver(params, storage=storage) for _ in range(2))
+        a.init(*fields)
+        a.step(7 + i % 2)
+        b.load(a.save())
+        assert np.array_equal(a.read(mplb.FIELD_UX), b.read(mplb.FIELD_UX))
+        a.reduce()
+        a.step(5)
+        b.step(5)
+        for w in (0, 1):
+            assert np.array_equal(a.get_populations(w), b.get_populations(w)), (nx, ny, w)
+
+
+@pytest.mark.parametrize("storage", ["fp64", "fp32", "fp16s", "fp16s_all"])
 def test_batch_equals_alone_bitwise(storage):
     cases = []
     for i, (nx, ny) in enumerate(SIZES):
