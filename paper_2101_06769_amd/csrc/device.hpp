@@ -1726,20 +1726,20 @@ inline hipError_t dispatch(const Ctx &c, Fn &&fn)
     return hipErrorInvalidValue;
 }
 
-// Packed planes on 3-D lattices periodic in x and y whose rows are not whole
-// wavefronts, the arrays within 32-bit indices: where the populations stay in
-// the Infinity Cache, and elsewhere where rows would fill less than 3/4 of
-// their blocks (300 x 100 x 100 FP32, 59%: 534 us a step in rows, 342 packed;
-// 96 x 96 x 384, 75%: 364 and 374, a packed wavefront's loads crossing the ends
-// of rows).
+// Packed planes on 3-D lattices periodic in x and y, the arrays within 32-bit
+// indices, where rows would leave lanes idle.  Per step, rows and packed: FP32
+// 97 x 96 x 200 282 and 201 us, 200 x 100 x 150 409 and 326, 300 x 100 x 100 541 and
+// 350, 320 x 128 x 160 850 and 694; FP64 96 x 96 x 200 405 and 386; FP16S_ALL
+// 96 x 96 x 384 334 and 282.  Rows stay where they fill 3/4 of their blocks and
+// start at cache lines in FP32, which a packed wavefront's would straddle
+// (96 x 96 x 384 364 and 374, 576 x 100 x 100 586 and 594).
 inline bool pack_form(const Ctx &c)
 {
-    if (c.dim != 3 || c.g.bcx != BC_PER || c.g.bcy != BC_PER || c.g.nx % 64 == 0 ||
-        27 * c.g.np >= (1ll << 31))
-        return false;
-    if (kept_in_cache(3, c.storage, c.g.np)) return true;
-    const int bx = int(c.block.x);
-    return bx % 64 != 0 || 4ll * c.g.nx < 3ll * ((c.g.nx + bx - 1) / bx * bx);
+    if (c.dim != 3 || c.g.bcx != BC_PER || c.g.bcy != BC_PER || 27 * c.g.np >= (1ll << 31)) return false;
+    const long long nx = c.g.nx, bx = c.block.x, wide = (nx + bx - 1) / bx * bx;
+    if (bx % 64 != 0) return true;
+    if (kept_in_cache(3, c.storage, c.g.np)) return nx % 64 != 0;
+    return wide != nx && !(c.storage == ST_FP32 && nx % 32 == 0 && 4 * nx >= 3 * wide);
 }
 inline unsigned pack_blocks(const Geom &g)
 {
@@ -1748,11 +1748,26 @@ inline unsigned pack_blocks(const Geom &g)
 }
 inline bool row_form(const Ctx &c) { return row_form_ok(c.dim, c.g, c.block); }
 
+// The context's block, or one a wavefront wide where its rows would fill less
+// than 3/4 of it and a wavefront's width fills more (320 cells take two blocks
+// of 256).  Lattices with walls or symmetry planes in x or y: the others are
+// packed (320 x 128 x 160, measured periodic: FP64 1759 -> 1336 us a step).
+inline dim3 filled_block(const Ctx &c)
+{
+    const long long nx = c.g.nx, bx = c.block.x;
+    const long long wide = (nx + bx - 1) / bx * bx, waves = (nx + 63) / 64 * 64;
+    if (4 * nx >= 3 * wide || waves >= wide) return c.block;
+    const unsigned by = c.g.ny >= 4 ? 4 : c.g.ny >= 2 ? 2 : 1;
+    return dim3(64, by, c.g.nz >= int(4 / by) ? 4 / by : 1);
+}
+
 // Calls fn.template operator()<NB, FORM>(grid, block) for the form of a launch
 // over the context's cells (KEEP: a Kept form where it applies).
 template <int D, class P, bool KEEP = true, class Fn>
-inline hipError_t with_form(const Ctx &c, Fn &&fn)
+inline hipError_t with_form(const Ctx &ctx, Fn &&fn)
 {
+    Ctx c = ctx;
+    if constexpr (D == 3) c.block = filled_block(c);
     auto go = [&]<int FORM>(dim3 grid, dim3 block) {
         using NB = NbOf<FORM>;
         if constexpr (KEEP && !P::F::shifted && D == 3) {
@@ -1761,7 +1776,7 @@ inline hipError_t with_form(const Ctx &c, Fn &&fn)
         return fn.template operator()<NB, FORM>(grid, block);
     };
     if constexpr (D == 3) {
-        if (pack_form(c)) return go.template operator()<FORM_PACK>(dim3(pack_blocks(c.g)), dim3(PACK_THREADS));
+        if (pack_form(ctx)) return go.template operator()<FORM_PACK>(dim3(pack_blocks(c.g)), dim3(PACK_THREADS));
     }
     return row_form(c) ? go.template operator()<FORM_ROW>(grid_for(c), c.block)
                        : go.template operator()<FORM_LANE>(grid_for(c), c.block);

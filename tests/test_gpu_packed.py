@@ -64,6 +64,13 @@ def test_phi_summing_update_in_the_cache(storage, n, bc):
     check(n, bc, storage, 90, steps=2)
 
 
+@pytest.mark.parametrize("n,bc", [((320, 3, 5), (0, 0, 1)), ((320, 1, 3), (0, 1, 0)), ((290, 5, 2), (1, 0, 0)),
+                                  ((258, 2, 2), (2, 2, 1))])
+def test_rows_that_would_leave_blocks_empty(n, bc):
+    # two blocks of 256 per row otherwise
+    check(n, bc, "fp64", 95)
+
+
 def test_packed_first_order_equilibrium_equals_the_batch():
     params = params_for(3, (36, 10, 9), (0, 0, 1))
     params["cac_edf"] = 1
