@@ -508,7 +508,7 @@ __device__ __forceinline__ void store_code(const NB &, void *base, long long pla
 {
     if constexpr (is_kept<NB>) {
         *lane_ptr(static_cast<unsigned short *>(base), plane + row, x) = bits;
-    } else if constexpr (BUF && !std::is_base_of<NbLane, NB>::value) {
+    } else if constexpr (BUF && (std::is_base_of<NbRow, NB>::value || std::is_base_of<NbPack, NB>::value)) {
         // raw buffer (stride 0) without a range limit; word 3 as gfx9 takes it for
         // untyped accesses; cache policy 2: non-temporal
         const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(

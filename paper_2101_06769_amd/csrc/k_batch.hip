@@ -95,7 +95,14 @@ kb_step2d(const BatchDom *__restrict__ doms, const int *__restrict__ table, int 
     const int lbx = step2d_width(g.nx), by = STEP2D_THREADS >> lbx;
     const int ntx = (g.nx + (1 << lbx) - 1) >> lbx, k = bid - tile0[at];
     const int x0 = (k % ntx) << lbx, y0 = (k / ntx) * by;
-    step2d_any<P, COLL, KEPT>(g, ph, p, lds, step2d_rows<P>(g, lbx), lbx, x0, y0, status + dom);
+    // the fast tile form of the format, and one for all other domains: in the
+    // FP16 formats the one of fewest registers, since both bodies share the
+    // kernel's (NbLane 64, NbFlat 98; 24 domains FP16S 42 and 47 us a step)
+    constexpr int FAST = P::F::shifted ? TILE_ROW : TILE_WIDE, OTHER = P::F::shifted ? TILE_LANE : TILE_NARROW;
+    if (step2d_form<P>(g, lbx) == FAST)
+        step2d_any<P, COLL, KEPT, FAST>(g, ph, p, lds, lbx, x0, y0, status + dom);
+    else
+        step2d_any<P, COLL, KEPT, OTHER>(g, ph, p, lds, lbx, x0, y0, status + dom);
 }
 
 hipError_t launch_batch_step2d(int storage, int collision, bool kept, const BatchDom *doms,

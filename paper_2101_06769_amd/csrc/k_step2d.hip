@@ -7,14 +7,14 @@ namespace mplb {
 // the tiles, so that the rows two tiles share are read through one L2
 // (1024 x 1024 FP32: 38.2 -> 36.9 us, 800 x 400: 15.0 -> 13.4 us with an earlier
 // form of the kernel).
-template <class P, int COLL, bool ROWS, bool KEPT>
+template <class P, int COLL, int TILE, bool KEPT>
 __global__ void __launch_bounds__(STEP2D_THREADS)
 k_step2d(Geom g, Phys<typename P::T> ph, Ptrs p, int lbx, int ntx)
 {
     __shared__ typename std::conditional<P::F::shifted, unsigned long long, typename P::T>::type lds[step2d_slots()];
     const int bid = tile_of<true>(int(blockIdx.x), int(gridDim.x));
     const int x0 = (bid % ntx) << lbx, y0 = (bid / ntx) * (STEP2D_THREADS >> lbx);
-    step2d_any<P, COLL, KEPT>(g, ph, p, lds, ROWS, lbx, x0, y0, nullptr);
+    step2d_any<P, COLL, KEPT, TILE>(g, ph, p, lds, lbx, x0, y0, nullptr);
 }
 
 int step2d_tiles(const Geom &g)
@@ -39,9 +39,15 @@ hipError_t launch_step2d(const Ctx &c)
             };
             return with_coll(coll_code(c.ph), [&](auto cc) {
                 constexpr int COLL = decltype(cc)::value;
-                if (!step2d_rows<P>(c.g, lbx))
-                    return kept ? launch(k_step2d<P, COLL, false, true>) : launch(k_step2d<P, COLL, false, false>);
-                return kept ? launch(k_step2d<P, COLL, true, true>) : launch(k_step2d<P, COLL, true, false>);
+                auto by_tile = [&]<int TILE>() {
+                    return kept ? launch(k_step2d<P, COLL, TILE, true>) : launch(k_step2d<P, COLL, TILE, false>);
+                };
+                const int form = step2d_form<P>(c.g, lbx);
+                if constexpr (P::F::shifted) {
+                    if (form == TILE_ROW) return by_tile.template operator()<TILE_ROW>();
+                }
+                return form == TILE_NARROW ? by_tile.template operator()<TILE_NARROW>()
+                                           : by_tile.template operator()<TILE_WIDE>();
             });
         }
     });

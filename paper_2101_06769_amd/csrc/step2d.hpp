@@ -198,19 +198,80 @@ __device__ __forceinline__ void step2d_tile(const Geom &g, const Phys<typename P
     if (step2d_load<P, ROWU, KEPT>(g, p, lphi, lbx, x0, y0, flag, nb)) collide_body<2, P, COLL>(nb, g, ph, p);
 }
 
-// One tile of the step in the FP16 formats (NB: NbRow, bx = 64, or NbLane).
+// Lane form of the FP16 formats' pulls: the rules of both axes as per-lane selects
+// (where y is wavefront-uniform, its part is scalar), against the branches of
+// NbLane: 100 x 130 between symmetry planes FP16S 7.8 -> 5.3 us a step.
+struct NbFlat {
+    int x, row;
+    int xs[3], r[3];  // columns and rows of the neighbours (the own one beyond a wall or symmetry plane)
+    bool lo, hi, bot, top;  // at an end of an axis that is not periodic
+    bool wx, wy;            // that end is a wall (else a symmetry plane)
+};
+__device__ __forceinline__ NbFlat make_nb(const Geom &g, int x, int y, int, NbFlat *)
+{
+    NbFlat n;
+    const bool px = g.bcx == BC_PER, py = g.bcy == BC_PER;
+    n.x = x;
+    n.row = y * g.nx;
+    n.lo = !px && x == 0;
+    n.hi = !px && x == g.nx - 1;
+    n.bot = !py && y == 0;
+    n.top = !py && y == g.ny - 1;
+    n.wx = g.bcx == BC_WALL;
+    n.wy = g.bcy == BC_WALL;
+    n.xs[0] = x > 0 ? x - 1 : px ? g.nx - 1 : x;
+    n.xs[1] = x;
+    n.xs[2] = x < g.nx - 1 ? x + 1 : px ? 0 : x;
+    n.r[0] = (y > 0 ? y - 1 : py ? g.ny - 1 : y) * g.nx;
+    n.r[1] = n.row;
+    n.r[2] = (y < g.ny - 1 ? y + 1 : py ? 0 : y) * g.nx;
+    return n;
+}
+template <int D>
+__device__ __forceinline__ PullLoc pull_loc(const NbFlat &n, int a)
+{
+    static_assert(D == 2, "2-D only");
+    const int cx = cx_of(a), cy = cy_of(a);
+    const bool ex = cx > 0 ? n.lo : cx < 0 ? n.hi : false, ey = cy > 0 ? n.bot : cy < 0 ? n.top : false;
+    PullLoc l;
+    l.bb = (ex && n.wx) || (ey && n.wy);
+    l.dir = l.bb ? 8 - a : a - (ex ? 2 * cx : 0) - (ey ? 6 * cy : 0);
+    l.rs = l.bb ? n.row : n.r[1 - cy];
+    l.xs = l.bb ? n.x : n.xs[1 - cx];
+    return l;
+}
+template <bool NT = false, typename R>
+__device__ __forceinline__ R load_loc(const NbFlat &, const R *base, long long plane, const PullLoc &l)
+{
+    if constexpr (NT)
+        return __builtin_nontemporal_load(&((gptr<const R>)base)[plane + l.rs + l.xs]);
+    else
+        return gld(base, plane + l.rs + l.xs);
+}
+template <int D>
+__device__ __forceinline__ bool wall_out(const NbFlat &n, int a)
+{
+    const int cx = cx_of(a), cy = cy_of(a);
+    return (n.wx && (cx > 0 ? n.hi : cx < 0 ? n.lo : false)) || (n.wy && (cy > 0 ? n.top : cy < 0 ? n.bot : false));
+}
+template <typename R>
+__device__ __forceinline__ R own_at(const NbFlat &n, const R *base)
+{
+    return gld(base, n.row + n.x);
+}
+
+// One tile of the step in the FP16 formats (NB: NbRow, bx = 64, or NbFlat).
 // The references of the level are in p.ref_in, and the update writes the next
 // level's to another array, since neighbouring blocks still read these.
-template <class P, int COLL, class NB, bool KEPT>
+template <class P, int COLL, class NB, bool KEPT, bool WIDE>
 __device__ __forceinline__ void step2d_tile16(const Geom &g, const Phys<float> &ph, const Ptrs &p,
                                               unsigned long long *lrec, int lbx, int x0, int y0,
                                               int *flag = nullptr)
 {
-    constexpr bool ROWU = std::is_same<NB, NbRow>::value;
-    const int bx = ROWU ? 64 : 1 << lbx, by = STEP2D_THREADS / bx, ls = bx + 2;
+    const int bx = WIDE ? 64 : 1 << lbx, by = STEP2D_THREADS / bx, ls = bx + 2;
     const int tid = int(threadIdx.x);
     const int tx = tid & (bx - 1);
-    const int ty = ROWU ? __builtin_amdgcn_readfirstlane(tid >> 6) : tid >> lbx;
+    const int ty = WIDE ? __builtin_amdgcn_readfirstlane(tid >> 6) : tid >> lbx;
     const int w = min(bx, g.nx - x0), h = min(by, g.ny - y0);
     auto slot = [&](int i, int j) { return lrec + (j + 1) * ls + i + 1; };
     auto record = [&](const auto &nb, unsigned long long *to) {
@@ -232,49 +293,48 @@ __device__ __forceinline__ void step2d_tile16(const Geom &g, const Phys<float> &
         const float s = record(nb, slot(tx, ty));
         if (flag && !__builtin_isfinite(s)) atomicOr(flag, 1);
     }
-    if constexpr (ROWU) {
+    if constexpr (WIDE) {
         if (ty < 2) {
             if (tx < w) ring((Kept<NB> *)nullptr, tx, ty == 0 ? -1 : h);
         } else if (ty == 2) {
             const int n = h + 2;
-            if (tx < 2 * n) ring((Kept<NbLane> *)nullptr, tx < n ? -1 : w, (tx < n ? tx : tx - n) - 1);
+            if (tx < 2 * n) ring((Kept<NbFlat> *)nullptr, tx < n ? -1 : w, (tx < n ? tx : tx - n) - 1);
         }
     } else if (tid < 2 * (w + 2 + h)) {
         const int k = tid - 2 * (w + 2);
         if (k < 0)
-            ring((Kept<NbLane> *)nullptr, (tid < w + 2 ? tid : tid - (w + 2)) - 1, tid < w + 2 ? -1 : h);
+            ring((Kept<NbFlat> *)nullptr, (tid < w + 2 ? tid : tid - (w + 2)) - 1, tid < w + 2 ? -1 : h);
         else
-            ring((Kept<NbLane> *)nullptr, k < h ? -1 : w, k < h ? k : k - h);
+            ring((Kept<NbFlat> *)nullptr, k < h ? -1 : w, k < h ? k : k - h);
     }
     __syncthreads();
     if (active) collide_body<2, P, COLL>(nb, g, ph, p);
 }
 
-// One tile in any format.  rows: the row forms apply (step2d_rows).
-template <class P, int COLL, bool KEPT>
+// One tile in any format.
+enum { TILE_NARROW, TILE_WIDE, TILE_ROW, TILE_LANE };
+template <class P, int COLL, bool KEPT, int TILE>
 __device__ __forceinline__ void step2d_any(const Geom &g, const Phys<typename P::T> &ph, const Ptrs &p,
-                                           void *lds, bool rows, int lbx, int x0, int y0, int *flag)
+                                           void *lds, int lbx, int x0, int y0, int *flag)
 {
     if constexpr (P::F::shifted) {
-        auto *lrec = static_cast<unsigned long long *>(lds);
-        if (rows)
-            step2d_tile16<P, COLL, NbRow, KEPT>(g, ph, p, lrec, lbx, x0, y0, flag);
-        else
-            step2d_tile16<P, COLL, NbLane, KEPT>(g, ph, p, lrec, lbx, x0, y0, flag);
+        using NB = typename std::conditional<TILE == TILE_ROW, NbRow,
+                   typename std::conditional<TILE == TILE_LANE, NbLane, NbFlat>::type>::type;
+        step2d_tile16<P, COLL, NB, KEPT, TILE == TILE_WIDE || TILE == TILE_ROW>(g, ph, p, static_cast<unsigned long long *>(lds),
+                                                              lbx, x0, y0, flag);
     } else {
-        auto *lphi = static_cast<typename P::T *>(lds);
-        if (rows)
-            step2d_tile<P, COLL, true, KEPT>(g, ph, p, lphi, lbx, x0, y0, flag);
-        else
-            step2d_tile<P, COLL, false, KEPT>(g, ph, p, lphi, lbx, x0, y0, flag);
+        step2d_tile<P, COLL, TILE == TILE_WIDE, KEPT>(g, ph, p, static_cast<typename P::T *>(lds), lbx, x0,
+                                                        y0, flag);
     }
 }
-// Tiles of whole wavefronts; in the FP16 formats, whose pulls take the 3-D
-// kernels' forms, also x periodic and 32-bit indices.
+// Narrow tiles, tiles of whole wavefronts, and those whose pulls in the FP16
+// formats take the 3-D kernels' row form (x periodic and 32-bit indices).
+// (TILE_LANE: narrow, with the 3-D kernels' lane form.)
 template <class P>
-__host__ __device__ inline bool step2d_rows(const Geom &g, int lbx)
+__host__ __device__ inline int step2d_form(const Geom &g, int lbx)
 {
-    return lbx == 6 && (!P::F::shifted || (g.bcx == BC_PER && 9 * g.np < (1ll << 31)));
+    if (lbx < 6) return TILE_NARROW;
+    return P::F::shifted && g.bcx == BC_PER && 9 * g.np < (1ll << 31) ? TILE_ROW : TILE_WIDE;
 }
 
 }  // namespace mplb

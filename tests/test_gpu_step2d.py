@@ -88,11 +88,13 @@ def test_fp16_checkpoints_at_either_level(storage, bc):
             assert np.array_equal(a.get_populations(w), b.get_populations(w)), (nx, ny, w)
 
 
+@pytest.mark.parametrize("collision,cac_edf", [(0, 0), (1, 0), (0, 1), (1, 1)])
 @pytest.mark.parametrize("storage", ["fp64", "fp32", "fp16s", "fp16s_all"])
-def test_batch_equals_alone_bitwise(storage):
+def test_batch_equals_alone_bitwise(storage, collision, cac_edf):
     cases = []
     for i, (nx, ny) in enumerate(SIZES):
         params = params_for(2, (nx, ny, 1), BCS[i % len(BCS)] + (0,))
+        params.update(collision=collision, cac_edf=cac_edf)
         cases.append((params,) + tuple(inputs.random_state(params, seed=40 + i)))
     b = mplb.Batch(2, storage, capacity=80, max_tiles=1 << 12)
     solvers, alone = [], []
