@@ -3,7 +3,7 @@
 // (Sec. 2.2) coupled to pressure-based flow populations under the cumulant
 // collision operator (Sec. 2.3).
 //
-// A step is two launches over the lattice:
+// A step of a 3-D lattice is two launches over it:
 //   k_phi      phi(x) = sum_a g_a(x), the g_a pulled from the post-collision
 //              buffer of the previous step (Sec. 2.2, zeroth moment);
 //   k_collide  per cell: isotropic gradient and Laplacian of phi (Sec. 2.2),
@@ -12,9 +12,10 @@
 //              stored at the cell (pull streaming: the next step gathers);
 // or, where the lattice allows it, k_phi_merge (phi from partial sums) and
 // k_collide_nphi (the same update, which also sums the next phi from the
-// values it stores; see "next order parameter" below).  The batched forms
-// (kb_step, kb_collide_nphi) run the same per-cell bodies over a tile list of
-// many independent domains.
+// values it stores; see "next order parameter" below).  A step of a 2-D
+// lattice is one launch (k_step2d, step2d.hpp), and several steps of a small one
+// are (k_multi2d).  The batched forms (kb_step, kb_collide_nphi, kb_step2d) run
+// the same per-cell bodies over many independent domains.
 //
 // Flow collision.  All cumulant rates other than the viscous ones are unity
 // (Sec. 2.3), so every post-collision cumulant above second order is zero and
@@ -339,9 +340,8 @@ constexpr bool is_kept<NbTile<T, true>> = true;
 template <class NB>
 constexpr bool is_kept<NbTile16<NB, true>> = true;
 
-// Stores a post-collision value: non-temporally, or (a form whose kept is set)
-// as an ordinary store, which leaves it in the Infinity Cache for the next
-// step (is_kept).
+// Stores a post-collision value: non-temporally, or (a Kept form) as an ordinary
+// store, which leaves it in the Infinity Cache for the next step.
 template <class NB, typename V, typename E>
 __device__ __forceinline__ void store_out(V v, gptr<E> at)
 {
