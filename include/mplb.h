@@ -169,7 +169,9 @@ int mplb_init(mplb_solver *s, const double *phi, const double *u, const double *
  * Runs of 16 (some small lattices 18) steady-state steps are launched as one
  * captured HIP graph (the same kernels and arguments, the same results; design,
  * not in the paper); small 2-D lattices in plain storage take two to four
- * steps per launch, with the results of single steps:
+ * steps per launch, with the results of single steps (single launches on a
+ * stream that the caller is capturing, where an even number of steps, less
+ * than a run, can be replayed):
  * the graph is captured on a stream of the handle's own at the first such
  * run and again when the level parity, the block or the step form changes.
  * Errors: EINVAL, ESTATE (not initialised, or attached to a batch),

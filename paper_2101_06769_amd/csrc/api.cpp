@@ -612,6 +612,22 @@ int replay_steps(mplb_solver *s)
 
 }  // namespace
 
+namespace {
+
+// Whether the caller captures the stream's launches into a graph.  Its replays
+// read the level that the capture read, so an even number of captured steps must
+// end at that level: a step flips the level, a launch of several flips it
+// once, and captured steps are launched one by one.
+bool capturing(hipStream_t stream)
+{
+    if (!stream) return false;  // the null stream cannot be captured
+    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(stream, &st) != hipSuccess) return true;
+    return st != hipStreamCaptureStatusNone;
+}
+
+}  // namespace
+
 int mplb_step(mplb_solver *s, int64_t nsteps)
 {
     if (!s) return fail(MPLB_EINVAL, "solver is NULL");
@@ -629,7 +645,7 @@ int mplb_step(mplb_solver *s, int64_t nsteps)
             continue;
         }
         const int multi = s->multi_steps();
-        if (multi > 1 && nsteps - i >= multi) {
+        if (multi > 1 && nsteps - i >= multi && !capturing(s->stream)) {
             HIPCHK(mplb::launch_multi2d(c, multi));
             s->cur ^= 1;
             s->steps += multi;
