@@ -165,6 +165,15 @@ __global__ void __launch_bounds__(256) k_set_pop(Geom g, PhysD ph, Ptrs p, int w
     }
 }
 
+// The cell's value of a field.  A 64-bit index: the 32-bit byte offset of
+// lane_ptr holds rows of up to 2^29 doubles, and FP32 lattices have rows of up
+// to 2^30 cells.
+template <class NB>
+__device__ __forceinline__ void put_field(double *dst, const NB &nb, double v)
+{
+    ((gptr<double>)dst)[(long long)nb.row + nb.x] = v;
+}
+
 // phi or rho of the state: no neighbour's phi is needed, so no phi pass.
 template <int D, class P, class NB, int FORM>
 __global__ void __launch_bounds__(256) k_field_phi(Geom g, Phys<typename P::T> ph, Ptrs p, int field,
@@ -175,7 +184,7 @@ __global__ void __launch_bounds__(256) k_field_phi(Geom g, Phys<typename P::T> p
     if (!block_cell<FORM, false>(g, x, y, z)) return;
     const NB nb = make_nb(g, x, y, z, (NB *)nullptr);
     const T phi = phi_value<D, P>(nb, g.np, p);
-    *lane_ptr(dst, nb.row, nb.x) = double(field == 0 ? phi : ph.rho_l + ph.drho * phi);
+    put_field(dst, nb, double(field == 0 ? phi : ph.rho_l + ph.drho * phi));
 }
 
 template <typename T>
@@ -194,7 +203,7 @@ __global__ void __launch_bounds__(256) k_field(Geom g, Phys<typename P::T> ph, P
     Cell<typename P::T> c;
     const NB nb = make_nb(g, x, y, z, (NB *)nullptr);
     eval_cell<D, P>(nb, g.np, ph, p, c);
-    *lane_ptr(dst, nb.row, nb.x) = field_of(c, field);
+    put_field(dst, nb, field_of(c, field));
 }
 
 // The same of a 2-D lattice in plain storage: phi summed in the block, as the
@@ -211,7 +220,7 @@ __global__ void __launch_bounds__(STEP2D_THREADS) k_field2d(Geom g, Phys<typenam
     if (!step2d_load<P, ROWU, false>(g, p, lphi, lbx, (bid % ntx) << lbx, (bid / ntx) * by, nullptr, nb)) return;
     Cell<T> c;
     eval_cell<2, P>(nb, g.np, ph, p, c);
-    *lane_ptr(dst, nb.row, nb.x) = field_of(c, field);
+    put_field(dst, nb, field_of(c, field));
 }
 
 constexpr int RED_BLOCKS = 1024;
