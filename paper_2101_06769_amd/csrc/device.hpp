@@ -1438,6 +1438,17 @@ __device__ __forceinline__ bool pack_cell(const Geom &g, int block, int &x, int 
 }
 
 
+// Launches whose blocks are numbered along one axis.  A launch has fewer than 2^32 threads
+// per axis (the runtime takes a larger size modulo 2^32 without an error), so
+// larger grids lie in rows of GRID_ROW blocks, the last one partly beyond the
+// count that the kernel checks, or are launched GRID_ROW blocks at a time.
+constexpr int GRID_ROW = 1 << 22;  // of at most 512 threads
+__device__ __forceinline__ int flat_block() { return int(blockIdx.x) + int(blockIdx.y) * GRID_ROW; }
+inline dim3 flat_grid(int n)
+{
+    return n <= GRID_ROW ? dim3(unsigned(n)) : dim3(GRID_ROW, unsigned((n - 1) / GRID_ROW + 1));
+}
+
 // Tile of block `block` among nt: in order, or (KEPT) XCD k taking the k-th
 // eighth of them, so that neighbouring tiles share an L2.
 template <bool KEPT>

@@ -20,8 +20,9 @@ __attribute__((amdgpu_waves_per_eu(PHI ? 1 : collide_waves<D, P, COLL>()))) kb_s
     // (status[dom] != 0): a non-finite population of either set reaches phi
     // within a step
     const int nt = PHI ? ntiles[2] : ntiles[1];
-    if (int(blockIdx.x) >= nt) return;
-    const BatchTile tl = tiles[ntiles[0] + tile_of<is_kept<NB>>(int(blockIdx.x), nt)];
+    const int block = flat_block();
+    if (block >= nt) return;
+    const BatchTile tl = tiles[ntiles[0] + tile_of<is_kept<NB>>(block, nt)];
     // the domain's record by value: read once, not re-read after every
     // population store the compiler cannot prove to be elsewhere
     const Geom g = doms[tl.dom].g;
@@ -74,8 +75,9 @@ kb_step2d(const BatchDom *__restrict__ doms, const int *__restrict__ table, int 
     const int pos = table[2 * group], n = table[2 * group + 1];
     const int *ids = table + 2 * BATCH_GROUPS + pos, *tile0 = table + 2 * BATCH_GROUPS + capacity + pos + group;
     const int nt = tile0[n];
-    if (int(blockIdx.x) >= nt) return;
-    const int bid = tile_of<true>(int(blockIdx.x), nt);
+    const int block = flat_block();
+    if (block >= nt) return;
+    const int bid = tile_of<true>(block, nt);
     // the last domain whose tiles begin at or before bid
     int at = -1;
     for (int d0 = 0; d0 < n; d0 += 64) {
@@ -119,7 +121,7 @@ hipError_t launch_batch_step2d(int storage, int collision, bool kept, const Batc
             return with_coll(collision, [&](auto cc) {
                 constexpr int COLL = decltype(cc)::value;
                 auto go = [&](auto kernel) {
-                    hipLaunchKernelGGL(kernel, dim3(grid), dim3(STEP2D_THREADS), 0, stream, doms, table, capacity,
+                    hipLaunchKernelGGL(kernel, flat_grid(grid), dim3(STEP2D_THREADS), 0, stream, doms, table, capacity,
                                        group, tbase, step_off, status);
                     return hipGetLastError();
                 };
@@ -148,7 +150,7 @@ hipError_t launch_batch_step(int storage, int collision, int form, bool kept,
     auto step = [&]<int D, class P, class NB, int FORM>() -> hipError_t {
         auto go = [&](auto k, int nblk, size_t lds) {
             if (nblk == 0) return hipSuccess;
-            hipLaunchKernelGGL(k, dim3(nblk), block, lds, stream, doms, tiles, ntiles, tbase, step_off,
+            hipLaunchKernelGGL(k, flat_grid(nblk), block, lds, stream, doms, tiles, ntiles, tbase, step_off,
                                status);
             return hipGetLastError();
         };

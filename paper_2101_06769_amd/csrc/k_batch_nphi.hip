@@ -30,8 +30,9 @@ kb_collide_nphi(const BatchDom *__restrict__ doms, const BatchTile *__restrict__
     constexpr int k = nphi_group(BX);
     const long long t = *tbase + step_off;
     const int n0 = ntiles[3 + 2 * k], nt = ntiles[4 + 2 * k];
-    if (int(blockIdx.x) >= nt) return;
-    const BatchTile tl = tiles[n0 + int(blockIdx.x)];
+    const int block = flat_block();
+    if (block >= nt) return;
+    const BatchTile tl = tiles[n0 + block];
     const Geom g = doms[tl.dom].g;  // by value, see kb_step
     const long long first = doms[tl.dom].first, last = doms[tl.dom].last;
     if (t < first || t >= last) return;  // the whole block
@@ -63,7 +64,7 @@ hipError_t launch_batch_nphi(int storage, int collision, bool kept, const BatchD
                     if (grid[2 + k] == 0) return hipSuccess;
                     const int threads = nphi_threads(storage, nphi_group_width(k));
                     const size_t lds = size_t(26) * threads * sizeof(typename P::T);
-                    hipLaunchKernelGGL(kernel, dim3(grid[2 + k]), dim3(threads), lds, stream, doms, tiles,
+                    hipLaunchKernelGGL(kernel, flat_grid(grid[2 + k]), dim3(threads), lds, stream, doms, tiles,
                                        ntiles, tbase, step_off);
                     return hipGetLastError();
                 };

@@ -1,5 +1,6 @@
 // Host exchange (initial state, populations in and out, fields) and the
 // deterministic FP64 reductions.
+#include <algorithm>
 #include <map>
 #include <mutex>
 
@@ -210,11 +211,12 @@ __global__ void __launch_bounds__(256) k_field(Geom g, Phys<typename P::T> ph, P
 // one-launch step does.
 template <class P, bool ROWU>
 __global__ void __launch_bounds__(STEP2D_THREADS) k_field2d(Geom g, Phys<typename P::T> ph, Ptrs p, int lbx,
-                                                            int ntx, int field, double *dst)
+                                                            int ntx, int nt, int first, int field,
+                                                            double *dst)
 {
     using T = typename P::T;
     __shared__ T lphi[step2d_slots()];
-    const int bid = tile_of<true>(int(blockIdx.x), int(gridDim.x));
+    const int bid = tile_of<true>(first + int(blockIdx.x), nt);
     const int by = ROWU ? STEP2D_THREADS / 64 : STEP2D_THREADS >> lbx;
     NbTile<T, false> nb;
     if (!step2d_load<P, ROWU, false>(g, p, lphi, lbx, (bid % ntx) << lbx, (bid / ntx) * by, nullptr, nb)) return;
@@ -358,10 +360,15 @@ hipError_t launch_field(const Ctx &c, int field, double *dst)
         }
         if constexpr (D == 2 && !P::F::shifted) {
             const int lbx = step2d_width(c.g.nx), ntx = (c.g.nx + (1 << lbx) - 1) >> lbx;
+            const int nt = step2d_tiles(c.g);
             auto go = [&](auto kernel) {
-                hipLaunchKernelGGL(kernel, dim3(step2d_tiles(c.g)), dim3(STEP2D_THREADS), 0, c.stream, c.g,
-                                   ph, c.p, lbx, ntx, field, dst);
-                return hipGetLastError();
+                hipError_t e = hipSuccess;
+                for (int first = 0; first < nt && e == hipSuccess; first += GRID_ROW) {
+                    hipLaunchKernelGGL(kernel, dim3(std::min(nt - first, GRID_ROW)), dim3(STEP2D_THREADS), 0,
+                                       c.stream, c.g, ph, c.p, lbx, ntx, nt, first, field, dst);
+                    e = hipGetLastError();
+                }
+                return e;
             };
             return lbx == 6 ? go(k_field2d<P, true>) : go(k_field2d<P, false>);
         } else {

@@ -1,4 +1,6 @@
 // The one-launch step of one 2-D domain (see step2d.hpp).
+#include <algorithm>
+
 #include "step2d.hpp"
 
 namespace mplb {
@@ -9,10 +11,10 @@ namespace mplb {
 // form of the kernel).
 template <class P, int COLL, int TILE, bool KEPT>
 __global__ void __launch_bounds__(STEP2D_THREADS)
-k_step2d(Geom g, Phys<typename P::T> ph, Ptrs p, int lbx, int ntx)
+k_step2d(Geom g, Phys<typename P::T> ph, Ptrs p, int lbx, int ntx, int nt, int first)
 {
     __shared__ typename std::conditional<P::F::shifted, unsigned long long, typename P::T>::type lds[step2d_slots()];
-    const int bid = tile_of<true>(int(blockIdx.x), int(gridDim.x));
+    const int bid = tile_of<true>(first + int(blockIdx.x), nt);
     const int x0 = (bid % ntx) << lbx, y0 = (bid / ntx) * (STEP2D_THREADS >> lbx);
     step2d_any<P, COLL, KEPT, TILE>(g, ph, p, lds, lbx, x0, y0, nullptr);
 }
@@ -26,16 +28,20 @@ int step2d_tiles(const Geom &g)
 hipError_t launch_step2d(const Ctx &c)
 {
     const int lbx = step2d_width(c.g.nx);
-    const int ntx = (c.g.nx + (1 << lbx) - 1) >> lbx;
+    const int ntx = (c.g.nx + (1 << lbx) - 1) >> lbx, nt = step2d_tiles(c.g);
     const bool kept = kept_in_cache(2, c.storage, c.g.np);
     return dispatch(c, [&]<int D, class P>() -> hipError_t {
         if constexpr (D != 2) {
             return hipErrorInvalidValue;
         } else {
             auto launch = [&](auto kernel) {
-                hipLaunchKernelGGL(kernel, dim3(step2d_tiles(c.g)), dim3(STEP2D_THREADS), 0,
-                                   c.stream, c.g, to_phys<typename P::T>(c.ph), c.p, lbx, ntx);
-                return hipGetLastError();
+                hipError_t e = hipSuccess;
+                for (int first = 0; first < nt && e == hipSuccess; first += GRID_ROW) {
+                    hipLaunchKernelGGL(kernel, dim3(std::min(nt - first, GRID_ROW)), dim3(STEP2D_THREADS), 0,
+                                       c.stream, c.g, to_phys<typename P::T>(c.ph), c.p, lbx, ntx, nt, first);
+                    e = hipGetLastError();
+                }
+                return e;
             };
             return with_coll(coll_code(c.ph), [&](auto cc) {
                 constexpr int COLL = decltype(cc)::value;

@@ -1,7 +1,8 @@
-"""2-D lattices of one very long row (80 GB): 2^29 cells and more,
-past the 32-bit byte offsets of double fields.  The state repeats with a period
-of 4096 cells, so every field after any number of steps is that of a lattice
-of one period, bit for bit."""
+"""2-D lattices of one very long row or column (80 GB): 2^29 cells and more, past
+the 32-bit byte offsets of double fields and, for tiles of 8 by 32 cells, past
+2^32 threads, alone and in a batch.  The state repeats with a period of 4096
+cells, so every field after any number of steps is that of a lattice of one
+period, bit for bit."""
 import numpy as np
 import pytest
 
@@ -19,7 +20,7 @@ if gpu_available():
 PERIOD, REPEATS = 4096, (1 << 17) + 2
 
 
-def check_repeats(axis):
+def check_repeats(axis, batch=False):
     one = [1, 1, 1]
     one[axis] = PERIOD
     many = list(one)
@@ -28,17 +29,31 @@ def check_repeats(axis):
     phi = inputs.random_state(params, seed=5)[0].reshape(-1)
     s = mplb.Solver(params, storage="fp32")
     s.init(phi, np.zeros((2, PERIOD)))
-    b = mplb.Solver(params_for(2, many, (0, 0, 0)), storage="fp32")
+    shared = None
+    if batch:
+        # 2^27 tiles is what a column is counted as: 64 by 4 cells each
+        shared = mplb.Batch(2, "fp32", capacity=1, max_tiles=1 << 28)
+        shared.set_solo_cells(1 << 31)
+    b = mplb.Solver(params_for(2, many, (0, 0, 0)), storage="fp32", stream=shared and shared.stream)
     b.init(np.tile(phi, REPEATS), np.zeros((2, PERIOD * REPEATS)))
     for steps in (0, 3):
         s.step(steps)
-        b.step(steps)
+        if shared and steps:
+            shared.attach(b, steps)
+            shared.step(steps)
+        else:
+            b.step(steps)
         for field in (mplb.FIELD_PHI, mplb.FIELD_UX + axis):
             want = s.read(field).reshape(-1)
             assert (b.read(field).reshape(REPEATS, PERIOD) == want).all(), (axis, steps, field)
-    del b
+    del b, shared
     torch.cuda.empty_cache()
 
 
 def test_long_row():
     check_repeats(0)
+
+
+@pytest.mark.parametrize("batch", [False, True])
+def test_long_column(batch):
+    check_repeats(1, batch)
