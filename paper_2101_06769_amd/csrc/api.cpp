@@ -22,6 +22,7 @@
 #include <vector>
 
 #include "../../include/mplb.h"
+#include "hostplan.hpp"
 #include "internal.h"
 
 namespace {
@@ -715,23 +716,31 @@ int64_t mplb_steps_done(const mplb_solver *s) { return s ? s->steps : -1; }
 
 namespace {
 
-// The device address of n doubles of page-locked host memory, or null where
-// host_out is not that (pageable or managed memory, or a buffer not locked to
-// its end): the field kernel then writes over the bus itself, without the
-// staging array and the copy's launch.
+// The device address of n doubles of page-locked host memory, or null (see
+// direct_address): the field kernel then writes over the bus itself, without
+// the staging array and the copy's launch.
 double *device_view(double *host_out, long long n)
 {
-    if (reinterpret_cast<uintptr_t>(host_out) % sizeof(double)) return nullptr;
-    hipPointerAttribute_t a{}, z{};
-    if (hipPointerGetAttributes(&a, host_out) != hipSuccess ||
-        hipPointerGetAttributes(&z, host_out + n - 1) != hipSuccess) {
-        (void)hipGetLastError();  // pageable memory: the query's error is not the next launch's
-        return nullptr;
-    }
-    if (a.type != hipMemoryTypeHost || z.type != hipMemoryTypeHost || !a.devicePointer || !z.devicePointer)
-        return nullptr;
-    double *first = static_cast<double *>(a.devicePointer);
-    return static_cast<double *>(z.devicePointer) == first + (n - 1) ? first : nullptr;
+    auto query = [](uintptr_t at, mplb::HostRange &r) {
+        hipPointerAttribute_t a{};
+        hipDeviceptr_t start = nullptr;
+        size_t bytes = 0;
+        if (hipPointerGetAttributes(&a, reinterpret_cast<void *>(at)) != hipSuccess) return false;
+        r.page_locked = a.type == hipMemoryTypeHost;
+        if (!r.page_locked) return true;
+        if (hipMemGetAddressRange(&start, &bytes, a.devicePointer) != hipSuccess) return false;
+        r.device = reinterpret_cast<uintptr_t>(a.devicePointer);
+        r.start = reinterpret_cast<uintptr_t>(start);
+        r.bytes = bytes;
+        return true;
+    };
+    auto known = [&](uintptr_t at, mplb::HostRange &r) {
+        if (query(at, r)) return true;
+        (void)hipGetLastError();  // the query's error is not the next launch's
+        return false;
+    };
+    return reinterpret_cast<double *>(
+        mplb::direct_address(reinterpret_cast<uintptr_t>(host_out), size_t(n) * sizeof(double), known));
 }
 
 }  // namespace

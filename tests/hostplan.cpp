@@ -1,0 +1,24 @@
+// The host decisions of csrc/hostplan.hpp behind C functions, for
+// test_hostplan.py (built with g++, no device).
+#include "hostplan.hpp"
+
+extern "C" {
+
+// n ranges of host memory (host address, device address, bytes, page-locked): the
+// address that a read of `bytes` at `host` writes to, 0 for the staging array.
+uint64_t direct_address(uint64_t host, uint64_t bytes, const uint64_t *ranges, int n)
+{
+    return mplb::direct_address(host, bytes, [&](uintptr_t at, mplb::HostRange &r) {
+        for (int i = 0; i < n; ++i) {
+            const uint64_t *q = ranges + 4 * i;
+            if (at < q[0] || at >= q[0] + q[2]) continue;
+            r.page_locked = q[3] != 0;
+            r.device = q[1] + (at - q[0]);
+            r.start = q[1];
+            r.bytes = q[2];
+            return true;
+        }
+        return false;
+    });
+}
+}

@@ -1,0 +1,51 @@
+"""Decisions of the host code that need no device, built here with g++: when
+mplb_read writes into the caller's memory itself."""
+import ctypes
+import os
+import shutil
+import subprocess
+
+import pytest
+
+from tests.helpers import ROOT
+
+
+@pytest.fixture(scope="module")
+def plan(tmp_path_factory):
+    cxx = shutil.which("g++") or shutil.which("c++")
+    if cxx is None:
+        pytest.skip("no host compiler")
+    out = str(tmp_path_factory.mktemp("plan") / "hostplan.so")
+    subprocess.run([cxx, "-std=c++20", "-O1", "-Wall", "-Werror", "-shared", "-fPIC", "-I",
+                    os.path.join(ROOT, "paper_2101_06769_amd", "csrc"),
+                    os.path.join(ROOT, "tests", "hostplan.cpp"), "-o", out], check=True)
+    return ctypes.CDLL(out)
+
+
+def direct(plan, host, bytes_, ranges):
+    flat = [v for r in ranges for v in r]
+    plan.direct_address.restype = ctypes.c_uint64
+    return plan.direct_address(ctypes.c_uint64(host), ctypes.c_uint64(bytes_),
+                               (ctypes.c_uint64 * len(flat))(*flat), len(ranges))
+
+
+A, B, P = 0x10000, 0x40000, 0x1000  # two ranges, a page
+
+
+@pytest.mark.parametrize("host,bytes_,ranges,want", [
+    (A, 4 * P, [(A, A, 4 * P, 1)], A),                     # the whole range
+    (A + 8, 4 * P - 8, [(A, A, 4 * P, 1)], A + 8),         # to its end
+    (A + 8, 4 * P, [(A, A, 4 * P, 1)], 0),                 # one value beyond it
+    (A, 8, [(A, A, 4 * P, 1)], A),                         # one value
+    (A + 4, 8, [(A, A, 4 * P, 1)], 0),                     # not aligned
+    (A, 4 * P, [(A, B, 4 * P, 1)], B),                     # seen elsewhere by the device
+    (A, 4 * P, [(A, A, 4 * P, 0)], 0),                     # pageable or managed
+    (A, 4 * P, [], 0),                                     # unknown to the runtime
+    # locked at both ends, pageable between them
+    (A, B + P - A, [(A, A, P, 1), (B, B, P, 1)], 0),
+    # two ranges side by side: two registrations, which need not be seen side by side
+    (A, 2 * P, [(A, A, P, 1), (A + P, A + P, P, 1)], 0),
+    (A, 0xffffffffffffff00, [(A, A, 4 * P, 1)], 0),        # no wrap-around
+])
+def test_reads_write_into_one_page_locked_range_only(plan, host, bytes_, ranges, want):
+    assert direct(plan, host, bytes_, ranges) == want
