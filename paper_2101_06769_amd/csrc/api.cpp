@@ -740,7 +740,8 @@ double *device_view(double *host_out, long long n)
         return false;
     };
     return reinterpret_cast<double *>(
-        mplb::direct_address(reinterpret_cast<uintptr_t>(host_out), size_t(n) * sizeof(double), known));
+        mplb::direct_address(reinterpret_cast<uintptr_t>(host_out), size_t(n) * sizeof(double),
+                             hipPeekAtLastError() != hipSuccess, known));
 }
 
 }  // namespace

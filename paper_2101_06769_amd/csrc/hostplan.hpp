@@ -23,11 +23,13 @@ struct HostRange {
 // memory at its host address, so two ranges with pageable memory between them
 // look like one.  query: HostRange of an address, false where the runtime
 // cannot tell.
+// pending: an earlier error that the caller of the library has yet to see; nothing is
+// asked then, since the answer could take that error's place.
 template <class Query>
-uintptr_t direct_address(uintptr_t host, size_t bytes, Query &&query)
+uintptr_t direct_address(uintptr_t host, size_t bytes, bool pending, Query &&query)
 {
     HostRange r;
-    if (host % 8 != 0 || !query(host, r) || !r.page_locked || r.device == 0) return 0;
+    if (pending || host % 8 != 0 || !query(host, r) || !r.page_locked || r.device == 0) return 0;
     if (r.device < r.start) return 0;
     const size_t before = r.device - r.start;
     return before <= r.bytes && bytes <= r.bytes - before ? r.device : 0;

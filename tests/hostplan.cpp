@@ -6,9 +6,11 @@ extern "C" {
 
 // n ranges of host memory (host address, device address, bytes, page-locked): the
 // address that a read of `bytes` at `host` writes to, 0 for the staging array.
-uint64_t direct_address(uint64_t host, uint64_t bytes, const uint64_t *ranges, int n)
+// asked: how often the ranges were looked up.
+uint64_t direct_address(uint64_t host, uint64_t bytes, int pending, const uint64_t *ranges, int n, int *asked)
 {
-    return mplb::direct_address(host, bytes, [&](uintptr_t at, mplb::HostRange &r) {
+    return mplb::direct_address(host, bytes, pending != 0, [&](uintptr_t at, mplb::HostRange &r) {
+        ++*asked;
         for (int i = 0; i < n; ++i) {
             const uint64_t *q = ranges + 4 * i;
             if (at < q[0] || at >= q[0] + q[2]) continue;

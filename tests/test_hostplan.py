@@ -22,11 +22,13 @@ def plan(tmp_path_factory):
     return ctypes.CDLL(out)
 
 
-def direct(plan, host, bytes_, ranges):
+def direct(plan, host, bytes_, ranges, pending=0):
     flat = [v for r in ranges for v in r]
     plan.direct_address.restype = ctypes.c_uint64
-    return plan.direct_address(ctypes.c_uint64(host), ctypes.c_uint64(bytes_),
-                               (ctypes.c_uint64 * len(flat))(*flat), len(ranges))
+    asked = ctypes.c_int(0)
+    got = plan.direct_address(ctypes.c_uint64(host), ctypes.c_uint64(bytes_), pending,
+                              (ctypes.c_uint64 * len(flat))(*flat), len(ranges), ctypes.byref(asked))
+    return got, asked.value
 
 
 A, B, P = 0x10000, 0x40000, 0x1000  # two ranges, a page
@@ -48,4 +50,9 @@ A, B, P = 0x10000, 0x40000, 0x1000  # two ranges, a page
     (A, 0xffffffffffffff00, [(A, A, 4 * P, 1)], 0),        # no wrap-around
 ])
 def test_reads_write_into_one_page_locked_range_only(plan, host, bytes_, ranges, want):
-    assert direct(plan, host, bytes_, ranges) == want
+    assert direct(plan, host, bytes_, ranges)[0] == want
+
+
+def test_a_pending_error_is_left_for_the_launch_to_report(plan):
+    # no query, whose own error would be cleared and the caller's with it
+    assert direct(plan, A, 8, [(A, A, P, 1)], pending=1) == (0, 0)
