@@ -1496,6 +1496,7 @@ int mplb_batch_step(mplb_batch *b, int64_t nsteps)
         if (!s || !b->solo[i]) continue;
         const long long lo = t0 > b->start[i] ? t0 : b->start[i];
         const long long hi = b->t < b->doms[i].last ? b->t : b->doms[i].last;
+        int unchecked = check;  // direct steps since the last check
         for (long long k = lo; k < hi;) {
             const mplb::Ctx c = s->ctx(s->cur);
             const bool steady = s->hist && (!s->use_nphi(c) || s->nphi_valid);
@@ -1507,13 +1508,16 @@ int mplb_batch_step(mplb_batch *b, int64_t nsteps)
                 if (rc != MPLB_OK) return rc;
                 s->steps += graph_steps(s);
                 k += graph_steps(s);
+                unchecked = check;  // the first direct step after a run is checked
                 continue;
             }
             HIPCHK(s->launch_phi_stage(c));
-            if ((k - lo) % check == 0) {
+            if (unchecked >= check) {
                 HIPCHK(s->refresh_phi(c));
                 HIPCHK(mplb::launch_flag_nonfinite(c, b->d_status + i));
+                unchecked = 0;
             }
+            ++unchecked;
             HIPCHK(s->launch_update_stage(c));
             s->cur ^= 1;
             s->steps++;
