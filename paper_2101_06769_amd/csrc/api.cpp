@@ -967,9 +967,7 @@ struct mplb_batch {
         bool kept;  // its populations stay in the Infinity Cache
         int grid[2 + mplb::NPHI_GROUPS];  // blocks of the phi, update and phi-summing update
                                           // launches (0 for none), grid[0] the only one in 2-D:
-                                          // tile counts rounded up by at most an eighth,
-                                          // so that a captured graph survives most changes
-        bool operator==(const Group &) const = default;
+                                          // see launch_blocks
     };
     std::vector<Group> groups;
     std::vector<int> counts;  // the device tile counters, GROUP_INTS per group
@@ -1113,12 +1111,6 @@ int upload_tables(mplb_batch *b)
     const int form = pack && ragged ? mplb::FORM_PACK : row ? mplb::FORM_ROW : mplb::FORM_LANE;
     if (form != b->form) drop_graph(b);  // a captured graph holds the other kernel
     b->form = form;
-    // launch sizes: rounded up by at most an eighth
-    auto bucketed = [](int n) {
-        int step = 1;
-        while (step * 16 <= n) step <<= 1;
-        return (n + step - 1) / step * step;
-    };
     std::vector<mplb_batch::Group> groups;
     std::fill(b->counts.begin(), b->counts.end(), 0);
     std::fill(b->table2d.begin(), b->table2d.end(), 0);
@@ -1141,7 +1133,7 @@ int upload_tables(mplb_batch *b)
             }
             run[cg.slots.size()] = int(n);
             pos += head[1];
-            gr.grid[0] = bucketed(int(n));
+            gr.grid[0] = int(n);
             groups.push_back(gr);
             continue;
         }
@@ -1170,8 +1162,8 @@ int upload_tables(mplb_batch *b)
             }
             cnt[1 + pass] = int(b->tiles.size()) - cnt[0];
         }
-        gr.grid[0] = bucketed(cnt[2]);
-        gr.grid[1] = bucketed(cnt[1]);
+        gr.grid[0] = cnt[2];
+        gr.grid[1] = cnt[1];
         for (int k = 0; k < NPHI_GROUPS; ++k) {
             cnt[3 + 2 * k] = int(b->tiles.size());
             for (int i : cg.slots) {
@@ -1182,12 +1174,23 @@ int upload_tables(mplb_batch *b)
                         b->tiles.push_back(mplb::BatchTile{i, 0, y0, z, z + 1, b->doms[i].g.nx});
             }
             cnt[4 + 2 * k] = int(b->tiles.size()) - cnt[3 + 2 * k];
-            gr.grid[2 + k] = bucketed(cnt[4 + 2 * k]);
+            gr.grid[2 + k] = cnt[4 + 2 * k];
         }
         groups.push_back(gr);
     }
-    if (groups != b->groups) drop_graph(b);
-    b->groups = groups;
+    // the captured graph stays where its launches serve the new tiles
+    bool serves = groups.size() == b->groups.size();
+    for (size_t gi = 0; serves && gi < groups.size(); ++gi) {
+        serves = groups[gi].kept == b->groups[gi].kept;
+        for (int k = 0; serves && k < 2 + NPHI_GROUPS; ++k)
+            serves = mplb::blocks_serve(b->groups[gi].grid[k], groups[gi].grid[k]);
+    }
+    if (!serves) {
+        drop_graph(b);
+        for (mplb_batch::Group &gr : groups)
+            for (int &n : gr.grid) n = mplb::launch_blocks(n);
+        b->groups = groups;
+    }
     HIPCHK(hipStreamSynchronize(b->stream));
     HIPCHK(hipMemcpyAsync(b->d_doms, b->doms.data(), sizeof(mplb::BatchDom) * b->capacity,
                           hipMemcpyHostToDevice, b->stream));

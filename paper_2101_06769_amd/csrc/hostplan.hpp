@@ -35,4 +35,21 @@ uintptr_t direct_address(uintptr_t host, size_t bytes, bool pending, Query &&que
     return before <= r.bytes && bytes <= r.bytes - before ? r.device : 0;
 }
 
+// Launch sizes of the batched kernels (surplus blocks find no tile and exit).
+// A captured graph holds its sizes, so it outlives a change of the domains only
+// where the old size serves the new count of tiles: enough blocks, and
+// at most half more than needed (one of four equal domains or more may go and
+// come; the surplus cost nothing measurable: 24 2-D domains of 64 to 200 a side
+// less 8 of them 12.8 us a step with either size).
+inline int launch_blocks(int tiles)
+{
+    int step = 1;  // up by at most an eighth
+    while (step <= tiles / 16) step <<= 1;
+    return (tiles + step - 1) / step * step;
+}
+inline bool blocks_serve(int blocks, int tiles)
+{
+    return tiles == 0 ? blocks == 0 : blocks >= tiles && blocks - tiles <= tiles / 2 + 32;
+}
+
 }  // namespace mplb

@@ -23,4 +23,7 @@ uint64_t direct_address(uint64_t host, uint64_t bytes, int pending, const uint64
         return false;
     });
 }
+
+int launch_blocks(int tiles) { return mplb::launch_blocks(tiles); }
+int blocks_serve(int blocks, int tiles) { return mplb::blocks_serve(blocks, tiles); }
 }

@@ -1,5 +1,6 @@
 """Decisions of the host code that need no device, built here with g++: when
-mplb_read writes into the caller's memory itself."""
+mplb_read writes into the caller's memory itself, and when a batch's captured graph
+outlives a change of its domains."""
 import ctypes
 import os
 import shutil
@@ -56,3 +57,23 @@ def test_reads_write_into_one_page_locked_range_only(plan, host, bytes_, ranges,
 def test_a_pending_error_is_left_for_the_launch_to_report(plan):
     # no query, whose own error would be cleared and the caller's with it
     assert direct(plan, A, 8, [(A, A, P, 1)], pending=1) == (0, 0)
+
+
+def test_launches_of_a_batch_cover_every_tile(plan):
+    for tiles in list(range(1, 300)) + [4095, 4096, 4097, 99999, (1 << 24) + 1, 0x3fffffff, 0x7fffffff // 2]:
+        n = plan.launch_blocks(tiles)
+        assert tiles <= n <= tiles + tiles // 8 and plan.blocks_serve(n, tiles)
+        assert not plan.blocks_serve(tiles - 1, tiles)
+        assert not plan.blocks_serve(2 * tiles + 33, tiles)
+    # a kernel is launched exactly where it has tiles
+    assert plan.launch_blocks(0) == 0
+    assert plan.blocks_serve(0, 0) and not plan.blocks_serve(16, 0) and not plan.blocks_serve(0, 1)
+
+
+@pytest.mark.parametrize("domains", [4, 5, 8, 12, 20, 60])
+@pytest.mark.parametrize("tiles", [1, 7, 33, 250, 4000])
+def test_one_domain_may_leave_and_come_back(plan, domains, tiles):
+    # the graph captured for all of them serves the others, and all of them again
+    blocks = plan.launch_blocks(domains * tiles)
+    assert plan.blocks_serve(blocks, (domains - 1) * tiles)
+    assert plan.blocks_serve(blocks, domains * tiles)
