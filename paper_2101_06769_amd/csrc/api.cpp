@@ -1020,47 +1020,20 @@ void drop_graph(mplb_batch *b)
     b->have_graph = false;
 }
 
-// The sharing slots in groups whose populations (both levels) fit the Infinity
-// Cache together, as few and as even as the largest-first rule makes them.  A
-// group takes a chunk of steps while its values stay in the cache; stepped all
-// at once, every step would stream all of them from HBM.  Domains too
-// large for it share one more group, and so does everything when the groups
-// would exceed BATCH_GROUPS.  Returns, per group, whether it is kept and its
-// slots.
-struct CacheGroup {
-    bool kept;
-    std::vector<int> slots;
-    long long cells;
-};
-std::vector<CacheGroup> cache_groups(const mplb_batch *b)
+// The sharing slots in cache groups (members: slots).
+std::vector<mplb::CacheGroup> cache_groups(const mplb_batch *b)
 {
-    auto fits = [&](long long cells) { return mplb::kept_in_cache(b->dim, b->storage, cells); };
-    std::vector<int> small, large;
+    std::vector<int> slots;
+    std::vector<long long> cells;
     for (int i = 0; i < b->capacity; ++i)
-        if (b->slot[i] && !b->solo[i]) (fits(b->doms[i].g.np) ? small : large).push_back(i);
-    std::stable_sort(small.begin(), small.end(),
-                     [&](int x, int y) { return b->doms[x].g.np > b->doms[y].g.np; });
-    const size_t most = mplb::BATCH_GROUPS - (large.empty() ? 0 : 1);
-    std::vector<CacheGroup> out;
-    for (size_t n = small.empty() ? 0 : 1; n <= most; ++n) {
-        out.assign(n, CacheGroup{true, {}, 0});
-        bool ok = true;
-        for (int i : small) {
-            CacheGroup *to = &out[0];
-            for (CacheGroup &c : out)
-                if (c.cells < to->cells) to = &c;
-            to->slots.push_back(i);
-            to->cells += b->doms[i].g.np;
-            ok = ok && fits(to->cells);
+        if (b->slot[i] && !b->solo[i]) {
+            slots.push_back(i);
+            cells.push_back(b->doms[i].g.np);
         }
-        if (ok) break;
-        if (n == most) {
-            out.clear();
-            large.insert(large.end(), small.begin(), small.end());
-        }
-    }
-    if (!large.empty()) out.push_back(CacheGroup{false, large, 0});
-    for (CacheGroup &c : out) std::sort(c.slots.begin(), c.slots.end());
+    auto fits = [&](long long n) { return mplb::kept_in_cache(b->dim, b->storage, n); };
+    std::vector<mplb::CacheGroup> out = mplb::cache_groups(cells, mplb::BATCH_GROUPS, fits);
+    for (mplb::CacheGroup &c : out)
+        for (int &m : c.members) m = slots[m];
     return out;
 }
 
@@ -1115,7 +1088,7 @@ int upload_tables(mplb_batch *b)
     std::fill(b->counts.begin(), b->counts.end(), 0);
     std::fill(b->table2d.begin(), b->table2d.end(), 0);
     int pos = 0;
-    for (const CacheGroup &cg : cache_groups(b)) {
+    for (const mplb::CacheGroup &cg : cache_groups(b)) {
         const int gi = int(groups.size());
         mplb_batch::Group gr{};
         gr.kept = cg.kept;
@@ -1123,15 +1096,15 @@ int upload_tables(mplb_batch *b)
             int *head = &b->table2d[2 * gi], *ids = &b->table2d[2 * mplb::BATCH_GROUPS + pos];
             int *run = ids + b->capacity + gi;
             head[0] = pos;
-            head[1] = int(cg.slots.size());
+            head[1] = int(cg.members.size());
             long long n = 0;
-            for (size_t k = 0; k < cg.slots.size(); ++k) {
-                ids[k] = cg.slots[k];
+            for (size_t k = 0; k < cg.members.size(); ++k) {
+                ids[k] = cg.members[k];
                 run[k] = int(n);
-                n += mplb::step2d_tiles(b->doms[cg.slots[k]].g);
+                n += mplb::step2d_tiles(b->doms[cg.members[k]].g);
                 if (n > 0x3fffffffLL) return fail(MPLB_ENOMEM, "batch tile list is full");
             }
-            run[cg.slots.size()] = int(n);
+            run[cg.members.size()] = int(n);
             pos += head[1];
             gr.grid[0] = int(n);
             groups.push_back(gr);
@@ -1144,7 +1117,7 @@ int upload_tables(mplb_batch *b)
         int *cnt = &b->counts[size_t(gi) * mplb::GROUP_INTS];
         cnt[0] = int(b->tiles.size());
         for (int pass = 0; pass < 2; ++pass) {
-            for (int i : cg.slots) {
+            for (int i : cg.members) {
                 const mplb_solver *s = b->slot[i];
                 const int nx = s->prm.n[0], ny = s->prm.n[1], nz = s->prm.n[2];
                 if ((pass == 0) != (b->doms[i].nphi_by == 0)) continue;
@@ -1166,7 +1139,7 @@ int upload_tables(mplb_batch *b)
         gr.grid[1] = cnt[1];
         for (int k = 0; k < NPHI_GROUPS; ++k) {
             cnt[3 + 2 * k] = int(b->tiles.size());
-            for (int i : cg.slots) {
+            for (int i : cg.members) {
                 const int nby = b->doms[i].nphi_by;
                 if (!nby || b->doms[i].g.nx != mplb::nphi_group_width(k)) continue;
                 for (int z = 0; z < b->doms[i].g.nz; ++z)

@@ -2,8 +2,10 @@
 // compiled and tested without one.
 #pragma once
 
+#include <algorithm>
 #include <cstddef>
 #include <cstdint>
+#include <vector>
 
 namespace mplb {
 
@@ -50,6 +52,48 @@ inline int launch_blocks(int tiles)
 inline bool blocks_serve(int blocks, int tiles)
 {
     return tiles == 0 ? blocks == 0 : blocks >= tiles && blocks - tiles <= tiles / 2 + 32;
+}
+
+// The domains that share a batch's launches in groups whose populations (both
+// levels) fit the Infinity Cache together, as few and as even as the
+// largest-first rule makes them.  A group takes a chunk of steps while its
+// values stay in the cache; stepped all at once, every step would stream all of
+// them from HBM.  Domains too large for it share one more group, and so does
+// everything when the groups would exceed max_groups.  cells: per domain;
+// fits: whether a number of cells fits.
+struct CacheGroup {
+    bool kept;                // its populations stay in the cache
+    std::vector<int> members;  // indices of cells, ascending
+    long long cells;
+};
+template <class Fits>
+std::vector<CacheGroup> cache_groups(const std::vector<long long> &cells, size_t max_groups, Fits &&fits)
+{
+    std::vector<int> small, large;
+    for (int i = 0; i < int(cells.size()); ++i) (fits(cells[i]) ? small : large).push_back(i);
+    std::stable_sort(small.begin(), small.end(), [&](int x, int y) { return cells[x] > cells[y]; });
+    const size_t most = max_groups - (large.empty() ? 0 : 1);
+    std::vector<CacheGroup> out;
+    for (size_t n = small.empty() ? 0 : 1; n <= most; ++n) {
+        out.assign(n, CacheGroup{true, {}, 0});
+        bool ok = true;
+        for (int i : small) {
+            CacheGroup *to = &out[0];
+            for (CacheGroup &c : out)
+                if (c.cells < to->cells) to = &c;
+            to->members.push_back(i);
+            to->cells += cells[i];
+            ok = ok && fits(to->cells);
+        }
+        if (ok) break;
+        if (n == most) {
+            out.clear();
+            large.insert(large.end(), small.begin(), small.end());
+        }
+    }
+    if (!large.empty()) out.push_back(CacheGroup{false, large, 0});
+    for (CacheGroup &c : out) std::sort(c.members.begin(), c.members.end());
+    return out;
 }
 
 }  // namespace mplb

@@ -26,4 +26,21 @@ uint64_t direct_address(uint64_t host, uint64_t bytes, int pending, const uint64
 
 int launch_blocks(int tiles) { return mplb::launch_blocks(tiles); }
 int blocks_serve(int blocks, int tiles) { return mplb::blocks_serve(blocks, tiles); }
+
+// The cache groups of n domains where `limit` cells fit: per domain its group in
+// group[], per group whether it is kept in kept[]; the number of groups.
+int cache_groups(const int64_t *cells, int n, int64_t limit, int max_groups, int *group, int *kept)
+{
+    const auto out = mplb::cache_groups(std::vector<long long>(cells, cells + n), size_t(max_groups),
+                                        [&](long long c) { return c <= limit; });
+    for (size_t k = 0; k < out.size(); ++k) {
+        kept[k] = out[k].kept;
+        for (size_t j = 0; j < out[k].members.size(); ++j) {
+            const int i = out[k].members[j];
+            if (group[i] >= 0 || (j > 0 && i <= out[k].members[j - 1])) return -1;
+            group[i] = int(k);
+        }
+    }
+    return int(out.size());
+}
 }

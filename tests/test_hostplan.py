@@ -1,8 +1,9 @@
 """Decisions of the host code that need no device, built here with g++: when
-mplb_read writes into the caller's memory itself, and when a batch's captured graph
-outlives a change of its domains."""
+mplb_read writes into the caller's memory itself, when a batch's captured graph
+outlives a change of its domains, and which domains of a batch advance together."""
 import ctypes
 import os
+import random
 import shutil
 import subprocess
 
@@ -77,3 +78,43 @@ def test_one_domain_may_leave_and_come_back(plan, domains, tiles):
     blocks = plan.launch_blocks(domains * tiles)
     assert plan.blocks_serve(blocks, (domains - 1) * tiles)
     assert plan.blocks_serve(blocks, domains * tiles)
+
+
+def groups_of(plan, cells, limit, most=32):
+    group, kept = (ctypes.c_int * len(cells))(*[-1] * len(cells)), (ctypes.c_int * (most + 1))()
+    n = plan.cache_groups((ctypes.c_int64 * len(cells))(*cells), len(cells), ctypes.c_int64(limit), most,
+                          group, kept)
+    return n, list(group), list(kept)
+
+
+def check_groups(plan, cells, limit, most=32):
+    n, group, kept = groups_of(plan, cells, limit, most)
+    assert 0 <= n <= most
+    load = [sum(c for c, k in zip(cells, group) if k == j) for j in range(n)]
+    assert all(0 <= k < n for k in group) and all(x > 0 for x in load)
+    for j in range(n):
+        assert load[j] <= limit if kept[j] else j == n - 1, (j, load)
+    return n, load, kept
+
+
+def test_cache_groups_of_a_batch(plan):
+    assert groups_of(plan, [], 100)[0] == 0
+    assert check_groups(plan, [100], 100)[0] == 1
+    n, load, kept = check_groups(plan, [101], 100)
+    assert n == 1 and not kept[0]
+    # as few and as even as the largest-first rule makes them
+    n, load, kept = check_groups(plan, [60, 50, 40, 30, 10], 100)
+    assert n == 2 and sorted(load) == [90, 100]
+    # a domain beyond the cache in a group of its own, the last one
+    n, load, kept = check_groups(plan, [30, 500, 60, 40], 100)
+    assert n == 3 and load[2] == 500 and kept[:3] == [1, 1, 0]
+    # as many groups as there may be, and one too many: all of them together
+    n, load, kept = check_groups(plan, [90] * 32, 100)
+    assert n == 32 and all(kept[:32])
+    for cells in ([90] * 33, [90] * 32 + [500]):
+        n, load, kept = check_groups(plan, cells, 100)
+        assert n == 1 and not kept[0] and load == [sum(cells)]
+    rng = random.Random(3)
+    for _ in range(300):
+        cells = [rng.randint(1, rng.choice([20, 100, 150])) for _ in range(rng.randint(1, 70))]
+        check_groups(plan, cells, 100, rng.choice([2, 5, 32]))
