@@ -438,6 +438,14 @@ __host__ __device__ static Phys<T> to_phys(const PhysD &d)
 // P, high half F) to a reference array; the next step's order-parameter stage
 // copies it into the cell's 8-byte record (phi, reference), which is what
 // the stencil loads.
+// The multiply-adds of the codes are written out, and a code is rounded once:
+// the compiler folds the last multiply or multiply-add and the conversion into
+// v_fma_mixlo_f16, which rounds the exact product (or sum) to FP16, where
+// v_cvt_f16_f32 of the FP32 result rounds twice (619 000 of 4.2 million
+// products, a third of them set near a tie, came out different).  It does so where
+// both stand in one basic block, in every form of the update alike (26 codes of
+// f', 26 of g and the reference P per 3-D cell): a form whose control flow came between them
+// would store other bits than the others, which the tests compare.
 struct Ref16 {
     float P, F;
 };
@@ -461,7 +469,7 @@ __device__ __forceinline__ float flow_scale16(const Phys<float> &ph, float F)
 }
 __device__ __forceinline__ float dec_f16(float w, const Ref16 &r, float s, float q)
 {
-    return w * (r.P + s * q);
+    return w * __builtin_fmaf(s, q, r.P);
 }
 // w (F + q) as w q + w F: a reader decodes all its values against one F, so
 // w F is formed once per weight and each value takes one mixed-precision
@@ -1162,7 +1170,7 @@ __device__ __forceinline__ void collide_body(const NB &nb, const Geom &g,
         auto emit = [&](int a, T dev) {
             if constexpr (P::F::shifted) {
                 const float w = weight<D, float>(a);
-                const __half h = __float2half((dev * (1.0f / w) + (c.pstar - W.P)) * isw);
+                const __half h = __float2half(__builtin_fmaf(dev, 1.0f / w, c.pstar - W.P) * isw);
                 fsum += dec_f16(w, W, sw, __half2float(h));
                 store_code<P::G::shifted>(nb, p.Fout, (long long)a * g.np, row, xl, __half_as_ushort(h));
             } else {
@@ -1293,7 +1301,7 @@ __device__ __forceinline__ void collide_body(const NB &nb, const Geom &g,
         auto gemit = [&](int a, T gout, float F) {
             if constexpr (P::G::shifted) {
                 const float w = weight<D, float>(a);
-                const __half h = __float2half(gout * (1.0f / w) - F);
+                const __half h = __float2half(__builtin_fmaf(gout, 1.0f / w, -F));
                 const float dec = dec_g16(w, F, __half2float(h));
                 gsum += dec;
                 store_code<P::G::shifted>(nb, p.Gout, (long long)a * g.np, row, xl, __half_as_ushort(h));
