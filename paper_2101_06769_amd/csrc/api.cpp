@@ -1125,12 +1125,12 @@ int upload_tables(mplb_batch *b)
                 for (int z0 = 0; z0 < nz; ++z0) {
                     if (form == mplb::FORM_PACK) {
                         for (int c0 = 0; c0 < nx * ny; c0 += threads)
-                            b->tiles.push_back(mplb::BatchTile{i, c0, 0, z0, z0 + 1, 0});
+                            b->tiles.push_back(mplb::BatchTile{i, c0, 0, z0, 0});
                         continue;
                     }
                     for (int y0 = 0; y0 < ny; y0 += rows)
                         for (int x0 = 0; x0 < nx; x0 += w)
-                            b->tiles.push_back(mplb::BatchTile{i, x0, y0, z0, z0 + 1, w});
+                            b->tiles.push_back(mplb::BatchTile{i, x0, y0, z0, w});
                 }
             }
             cnt[1 + pass] = int(b->tiles.size()) - cnt[0];
@@ -1144,7 +1144,7 @@ int upload_tables(mplb_batch *b)
                 if (!nby || b->doms[i].g.nx != mplb::nphi_group_width(k)) continue;
                 for (int z = 0; z < b->doms[i].g.nz; ++z)
                     for (int y0 = 0; y0 < b->doms[i].g.ny; y0 += nby)
-                        b->tiles.push_back(mplb::BatchTile{i, 0, y0, z, z + 1, b->doms[i].g.nx});
+                        b->tiles.push_back(mplb::BatchTile{i, 0, y0, z, b->doms[i].g.nx});
             }
             cnt[4 + 2 * k] = int(b->tiles.size()) - cnt[3 + 2 * k];
             gr.grid[2 + k] = cnt[4 + 2 * k];

@@ -1,5 +1,5 @@
 // Host-side interface between the C ABI (api.cpp) and the kernel launchers
-// (kernels.hip).  Not part of the public ABI.
+// (the k_*.hip files).  Not part of the public ABI.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -148,12 +148,11 @@ struct BatchDom {
     long long nphi_from;
 };
 
-// A tile of a batch: domain index, origin cell (x0, y0, z0), end of its
-// plane range z1 and width w: w cells in x by (threads per block) / w rows,
-// one plane; w = 0: consecutive cells of plane z0 from in-plane index x0 (see
+// A tile of a batch: domain index, origin cell (x0, y0, z0) and width w: w
+// cells in x by (threads per block) / w rows, one plane; w = 0: consecutive cells of plane z0 from in-plane index x0 (see
 // NbPack).
 struct BatchTile {
-    int dom, x0, y0, z0, z1, w;
+    int dom, x0, y0, z0, w;
 };
 
 // The domains that share launches are advanced in cache groups: a group's
@@ -203,8 +202,6 @@ hipError_t launch_batch_step(int storage, int collision, int form, bool kept,
 hipError_t launch_batch_nphi(int storage, int collision, bool kept, const BatchDom *doms,
                              const BatchTile *tiles, const int *ntiles, const long long *tbase,
                              int step_off, const int *grid, hipStream_t stream);
-// Threads per block of the phi-summing update for a storage format and row length.
-int nphi_block_threads(int storage, int nx);
 hipError_t launch_set_i64(long long *ptr, long long v, hipStream_t stream);
 // *flag |= 1 if the order parameter of the context's current level (phi
 // array, as the phi stage left it) holds a non-finite value.

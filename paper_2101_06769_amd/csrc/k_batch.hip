@@ -4,11 +4,12 @@
 
 namespace mplb {
 
-// NB: the form of the block kernels (a Kept form: the group stays in the
-// Infinity Cache).
-template <int D, class P, int COLL, bool PHI, class NB, int FORM>
+// The phi stage or the update of one step of a group of 3-D domains.  NB: the
+// form of the block kernels (a Kept form: the group stays in the Infinity
+// Cache).
+template <class P, int COLL, bool PHI, class NB, int FORM>
 __global__ void __launch_bounds__(256)
-__attribute__((amdgpu_waves_per_eu(PHI ? 1 : collide_waves<D, P, COLL>()))) kb_step(const BatchDom *__restrict__ doms,
+__attribute__((amdgpu_waves_per_eu(PHI ? 1 : collide_waves<3, P, COLL>()))) kb_step(const BatchDom *__restrict__ doms,
                                                const BatchTile *__restrict__ tiles,
                                                const int *ntiles, const long long *tbase,
                                                int step_off, int *status)
@@ -44,20 +45,20 @@ __attribute__((amdgpu_waves_per_eu(PHI ? 1 : collide_waves<D, P, COLL>()))) kb_s
         x = tl.x0 + tid % tl.w;
         y = tl.y0 + tid / tl.w;
         if constexpr (FORM == FORM_ROW) y = __builtin_amdgcn_readfirstlane(y);
-        if (x >= g.nx || y >= g.ny || z >= tl.z1) return;
+        if (x >= g.nx || y >= g.ny) return;
     }
     const int nby = doms[tl.dom].nphi_by;
     if constexpr (PHI) {
         // (packed: the rows of a phi-summing domain are whole wavefronts)
         const int yw = FORM == FORM_PACK ? __builtin_amdgcn_readfirstlane(y) : y;
-        const T ph = (D == 3 && nby && t >= doms[tl.dom].nphi_from)
+        const T ph = (nby && t >= doms[tl.dom].nphi_from)
                          ? nphi_merge_cell<P, NB>(g, p, NextPhi{doms[tl.dom].npart, doms[tl.dom].nedge, nby}, x,
                                                   yw, z)
-                         : phi_cell<D, P, NB>(g, p, x, y, z);
+                         : phi_cell<3, P, NB>(g, p, x, y, z);
         if (!__builtin_isfinite(ph)) atomicOr(status + tl.dom, 1);
     } else {
         const Phys<T> ph = to_phys<T>(doms[tl.dom].ph);
-        collide_cell<D, P, COLL, NB>(g, ph, p, x, y, z);
+        collide_cell<3, P, COLL, NB>(g, ph, p, x, y, z);
     }
 }
 
@@ -147,20 +148,20 @@ hipError_t launch_batch_step(int storage, int collision, int form, bool kept,
     Ctx c{};
     c.dim = 3;
     c.storage = storage;
-    auto step = [&]<int D, class P, class NB, int FORM>() -> hipError_t {
+    auto step = [&]<class P, class NB, int FORM>() -> hipError_t {
         auto go = [&](auto k, int nblk, size_t lds) {
             if (nblk == 0) return hipSuccess;
             hipLaunchKernelGGL(k, flat_grid(nblk), block, lds, stream, doms, tiles, ntiles, tbase, step_off,
                                status);
             return hipGetLastError();
         };
-        hipError_t e = go(kb_step<D, P, 0, true, NB, FORM>, grid[0], 0);
+        hipError_t e = go(kb_step<P, 0, true, NB, FORM>, grid[0], 0);
         if (e != hipSuccess) return e;
         return with_coll(collision, [&](auto cc) -> hipError_t {
             constexpr int COLL = decltype(cc)::value;
             // dynamic LDS: single relaxation time's flow values (3-D)
-            return go(kb_step<D, P, COLL, false, NB, FORM>, grid[1],
-                      srt_lds_bytes<D, P, COLL>(block.x * block.y * block.z));
+            return go(kb_step<P, COLL, false, NB, FORM>, grid[1],
+                      srt_lds_bytes<3, P, COLL>(block.x * block.y * block.z));
         });
     };
     return dispatch(c, [&]<int D, class P>() -> hipError_t {
@@ -170,9 +171,9 @@ hipError_t launch_batch_step(int storage, int collision, int form, bool kept,
             auto by_form = [&]<int FORM>() -> hipError_t {
                 using NB = NbOf<FORM>;
                 if constexpr (!P::F::shifted) {
-                    if (kept) return step.template operator()<D, P, Kept<NB>, FORM>();
+                    if (kept) return step.template operator()<P, Kept<NB>, FORM>();
                 }
-                return step.template operator()<D, P, NB, FORM>();
+                return step.template operator()<P, NB, FORM>();
             };
             hipError_t e = hipErrorInvalidValue;
             if (form == FORM_LANE) {

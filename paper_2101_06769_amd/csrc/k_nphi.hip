@@ -154,7 +154,4 @@ hipError_t launch_phi_merge(const Ctx &c, const NextPhi &q)
     });
 }
 
-int nphi_block_threads(int storage, int nx) { return nphi_threads(storage, nx); }
-
-
 }  // namespace mplb
