@@ -167,13 +167,13 @@ int mplb_init(mplb_solver *s, const double *phi, const double *u, const double *
  * phase_source_post_discretization), and streaming with the boundary rules
  * of Sec. 3 (half-way bounce-back walls, symmetry planes, periodic axes).
  * Runs of 16 (some small lattices 18) steady-state steps are launched as one
- * captured HIP graph (the same kernels and arguments, the same results; design,
- * not in the paper); small 2-D lattices in plain storage take two to four
- * steps per launch, with the results of single steps (single launches on a
- * stream that the caller is capturing, where an even number of steps, less
- * than a run, can be replayed):
- * the graph is captured on a stream of the handle's own at the first such
- * run and again when the level parity, the block or the step form changes.
+ * HIP graph (the same kernels and arguments, the same results; design, not in
+ * the paper), captured on a stream of the handle's own at the first such run
+ * and again when the level parity, the block or the step form changes.
+ * Small 2-D lattices in plain storage take two to four steps per launch, with
+ * the results of single steps.  On a stream that the caller is capturing every
+ * launch is one step, so that a graph of an even number of steps, fewer than
+ * a run, advances the state by as many at every replay.
  * Errors: EINVAL, ESTATE (not initialised, or attached to a batch),
  * EDEVICE. */
 int mplb_step(mplb_solver *s, int64_t nsteps);
@@ -183,9 +183,11 @@ int mplb_step(mplb_solver *s, int64_t nsteps);
  * each step (ms_phi: order-parameter stage; ms_collide: cell update) in
  * milliseconds (2-D lattices step in one launch, counted
  * in ms_collide: ms_phi is then 0 or a few microseconds of event overhead a
- * step).  Synchronises the stream.  For profiling; the events add a
- * few microseconds per step.  Design, not in the paper.  Errors: as
- * mplb_step. */
+ * step).  Every launch timed is one step, also on the small 2-D lattices of
+ * which mplb_step takes several per launch: there mplb_step is faster than
+ * the times returned here.  Synchronises the stream.  For profiling; the
+ * events add a few microseconds per step.  Design, not in the paper.  Errors:
+ * as mplb_step. */
 int mplb_step_timed(mplb_solver *s, int64_t nsteps, double *ms_phi, double *ms_collide);
 
 /* Block until all queued work on the solver's stream has finished. */
@@ -255,11 +257,16 @@ int mplb_save(mplb_solver *s, void *host_blob, size_t bytes);
 int mplb_load(mplb_solver *s, const void *host_blob, size_t bytes);
 
 /* Threads per block of the cell update (x, y, z); (0, 0, 0) = library
- * default (as wide in x as the lattice, up to 256).  2-D lattices step
- * in one launch on tiles of the library's own.  Between 1 and 256
+ * default (as wide in x as the lattice, up to 256).  Between 1 and 256
  * threads; bz = 1 in 2-D.  Blocks a multiple of 64 wide in x on lattices
  * periodic in x take wavefront-uniform (row-form) addressing; results do not
- * depend on the shape.  Errors: EINVAL.  Design, not in the paper. */
+ * depend on the shape.  The library sets the shape aside where it has a
+ * better one: 2-D steps take tiles of its own; 3-D lattices periodic in x and
+ * y whose rows would leave lanes of the block idle (any block not a multiple
+ * of 64 wide among them) take 256 consecutive cells of a plane; other 3-D
+ * lattices whose rows fill less than 3/4 of the block's width take blocks 64
+ * wide where those fill more; the update that sums phi takes its own tiles
+ * (mplb_set_phi_partials).  Errors: EINVAL.  Design, not in the paper. */
 int mplb_set_block(mplb_solver *s, int32_t bx, int32_t by, int32_t bz);
 
 /* Next order parameter from partial sums.  phi at a cell is the zeroth
@@ -286,9 +293,12 @@ int mplb_uses_phi_partials(const mplb_solver *s);
 
 /* Autotuner: time candidate block shapes for the step kernels (each over
  * `steps` steps after two warm-up steps, device time from HIP events), select
- * the fastest, and write it to best[3].  The solver is advanced by the timed
- * steps, so tune on a scratch solver of representative size.  candidates is
- * an array of ncand (bx, by, bz) triples, or NULL for the built-in list.
+ * the fastest, and write it to best[3].  Every candidate is timed, also where
+ * the library sets the shape aside (mplb_set_block): the candidates then run
+ * the same kernels, 2-D ones all of them, and differ by noise.  The solver is
+ * advanced by the timed steps, so tune on a scratch solver of representative
+ * size.  candidates is an array of ncand (bx, by, bz) triples, or NULL for the
+ * built-in list.
  * Errors: EINVAL, ESTATE (attached to a batch), EDEVICE.  Design, not in
  * the paper. */
 int mplb_tune_block(mplb_solver *s, int32_t steps, const int32_t *candidates, int32_t ncand,
@@ -329,7 +339,11 @@ int mplb_batch_create(int32_t dim, int32_t storage, int32_t capacity, int64_t ma
                       void *dev_table, size_t table_bytes, void *hip_stream, mplb_batch **out);
 
 /* Block (= tile) shape of the batched kernels; at most 256 threads.
- * Rebuilds the tile list.  Errors: EINVAL, ENOMEM (tile list full). */
+ * Rebuilds the tile list.  2-D batches take tiles of the library's own and
+ * 3-D ones of x- and y-periodic domains, one of them ragged, consecutive cells
+ * of a plane, as many as the block has threads (whole wavefronts); max_tiles is compared with
+ * the tiles of this shape in any case.  Errors: EINVAL, ENOMEM (tile list
+ * full). */
 int mplb_batch_set_block(mplb_batch *b, int32_t bx, int32_t by, int32_t bz);
 
 /* Graph chunk in steps (>= 1), or 0 to launch every step directly. */
@@ -338,7 +352,7 @@ int mplb_batch_set_graph_chunk(mplb_batch *b, int32_t chunk);
 /* Autotuner: time `steps` batch steps (after one warm-up step) for each
  * candidate block shape (candidates = ncand triples bx, by, bz; NULL = a
  * built-in list), keep the fastest and report it in best[3] and its time per
- * step.  Timing needs real work, so every attached domain whose window is
+ * step (2-D batches run the same kernel for every shape).  Timing needs real work, so every attached domain whose window is
  * open advances by up to ncand * (steps + 1) steps: tune on a copy of the
  * workload.  Errors: EINVAL (steps < 1, no valid candidate, no attached
  * domain), EDEVICE. */
@@ -378,8 +392,10 @@ int mplb_batch_remaining(const mplb_batch *b, int32_t slot, int64_t *remaining);
 /* Health of every slot, status[capacity]: MPLB_OK for an attached solver
  * whose order parameter has stayed finite, MPLB_EUNSTABLE for one whose
  * order parameter held a non-finite value at some batch step (checked by
- * the batch's phi stage at every step, inside the captured graph; a
- * non-finite population of either set reaches phi within a step),
+ * the batch's phi stage at every step, inside the captured graph, or, for a
+ * solver that steps alone, before every run of steps and every chunk of
+ * direct ones; a non-finite population of either set reaches phi within a
+ * step),
  * MPLB_ESTATE for an empty slot.  An unstable solver is retired by this call:
  * its window closes, so it takes no further batch steps; detach it to free
  * the slot.  Synchronises the batch stream.  Errors: EINVAL, EDEVICE. */
