@@ -1450,7 +1450,7 @@ __device__ __forceinline__ bool pack_cell(const Geom &g, int block, int &x, int 
 // per axis (the runtime takes a larger size modulo 2^32 without an error), so
 // larger grids lie in rows of GRID_ROW blocks, the last one partly beyond the
 // count that the kernel checks, or are launched GRID_ROW blocks at a time.
-constexpr int GRID_ROW = 1 << 22;  // of at most 512 threads
+constexpr int GRID_ROW = 1 << 20;  // of at most 512 threads
 __device__ __forceinline__ int flat_block() { return int(blockIdx.x) + int(blockIdx.y) * GRID_ROW; }
 inline dim3 flat_grid(int n)
 {

@@ -215,7 +215,7 @@ __global__ void __launch_bounds__(STEP2D_THREADS) k_field2d(Geom g, Phys<typenam
                                                             double *dst)
 {
     using T = typename P::T;
-    __shared__ T lphi[step2d_slots()];
+    __shared__ T lphi[step2d_slots(ROWU)];
     const int bid = tile_of<true>(first + int(blockIdx.x), nt);
     const int by = ROWU ? STEP2D_THREADS / 64 : STEP2D_THREADS >> lbx;
     NbTile<T, false> nb;
@@ -359,7 +359,7 @@ hipError_t launch_field(const Ctx &c, int field, double *dst)
             });
         }
         if constexpr (D == 2 && !P::F::shifted) {
-            const int lbx = step2d_width(c.g.nx), ntx = (c.g.nx + (1 << lbx) - 1) >> lbx;
+            const int lbx = step2d_width(c.g), ntx = (c.g.nx + (1 << lbx) - 1) >> lbx;
             const int nt = step2d_tiles(c.g);
             auto go = [&](auto kernel) {
                 hipError_t e = hipSuccess;

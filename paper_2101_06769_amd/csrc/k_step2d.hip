@@ -13,7 +13,7 @@ template <class P, int COLL, int TILE, bool KEPT>
 __global__ void __launch_bounds__(STEP2D_THREADS)
 k_step2d(Geom g, Phys<typename P::T> ph, Ptrs p, int lbx, int ntx, int nt, int first)
 {
-    __shared__ typename std::conditional<P::F::shifted, unsigned long long, typename P::T>::type lds[step2d_slots()];
+    __shared__ typename std::conditional<P::F::shifted, unsigned long long, typename P::T>::type lds[step2d_slots(TILE == TILE_WIDE || TILE == TILE_ROW)];
     const int bid = tile_of<true>(first + int(blockIdx.x), nt);
     const int x0 = (bid % ntx) << lbx, y0 = (bid / ntx) * (STEP2D_THREADS >> lbx);
     step2d_any<P, COLL, KEPT, TILE>(g, ph, p, lds, lbx, x0, y0, nullptr);
@@ -21,13 +21,13 @@ k_step2d(Geom g, Phys<typename P::T> ph, Ptrs p, int lbx, int ntx, int nt, int f
 
 int step2d_tiles(const Geom &g)
 {
-    const int lbx = step2d_width(g.nx), by = STEP2D_THREADS >> lbx;
+    const int lbx = step2d_width(g), by = STEP2D_THREADS >> lbx;
     return ((g.nx + (1 << lbx) - 1) >> lbx) * ((g.ny + by - 1) / by);
 }
 
 hipError_t launch_step2d(const Ctx &c)
 {
-    const int lbx = step2d_width(c.g.nx);
+    const int lbx = step2d_width(c.g);
     const int ntx = (c.g.nx + (1 << lbx) - 1) >> lbx, nt = step2d_tiles(c.g);
     const bool kept = kept_in_cache(2, c.storage, c.g.np);
     return dispatch(c, [&]<int D, class P>() -> hipError_t {

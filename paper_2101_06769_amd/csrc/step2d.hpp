@@ -104,24 +104,75 @@ __device__ __forceinline__ T phi_sum9(const T (&v)[9])
     return s;
 }
 
-// Tile: 256 threads, as wide as the lattice up to a wavefront (2^3 .. 2^6
-// cells); its slots in LDS with the ring.
+// Tile: 256 threads, 64 x 4 cells; narrower and taller on lattices of less than
+// 64 columns (down to one); on long ones of few rows 256 x 1, 128 x 2 and 32 x 8
+// (5 or 6 rows), so that few threads are without a cell.  With tiles of at least
+// 8 columns and 4 rows, and with these, a step in us: 3 million cells in one
+// column FP32 310 and 87, FP16S_ALL 546 and 91; 300 000 in one row 14.7 and 10.9,
+// 17.8 and 12.7; 600 000 x 5 FP64 221 and 177.  Shorter rows leave CUs idle in any case and
+// are faster as whole wavefronts (20 000 cells FP16S 5.3 and 5.7), as are 7 and 8
+// rows (428 571 x 7 FP32 119 and 139).
 constexpr int STEP2D_THREADS = 256;
-__host__ __device__ inline int step2d_width(int nx)
+__host__ __device__ inline int step2d_width(const Geom &g)
 {
-    int l = 3;
-    while (l < 6 && (1 << l) < nx) ++l;
+    if (g.nx > 65536) return g.ny == 1 ? 8 : g.ny == 2 ? 7 : g.ny == 5 || g.ny == 6 ? 5 : 6;
+    if (g.nx > 64) return 6;
+    int l = 0;
+    while ((1 << l) < g.nx) ++l;
     return l;
 }
-constexpr int step2d_slots()
+// Slots of a tile in LDS with the ring around it.
+constexpr int step2d_slots(bool wide)
 {
     int most = 0;
-    for (int bx = 8; bx <= 64; bx *= 2) {
+    for (int bx = wide ? 64 : 1; bx <= (wide ? 64 : 256); bx *= 2) {
         const int n = (bx + 2) * (STEP2D_THREADS / bx + 2);
         most = n > most ? n : most;
     }
     return most;
 }
+
+// The ring around a tile in the forms without whole wavefronts per row.  A tile
+// that spans the lattice along an axis is its own neighbour there: the ring's
+// cells are images of the tile's, written by the threads that hold those, and
+// nothing is summed twice.
+struct Ring2d {
+    int w, h;
+    bool whole_x, whole_y, px, py;
+    __device__ __forceinline__ Ring2d(const Geom &g, int w_, int h_)
+        : w(w_), h(h_), whole_x(w_ == g.nx), whole_y(h_ == g.ny), px(g.bcx == BC_PER), py(g.bcy == BC_PER)
+    {
+    }
+    // cells of the ring to sum: the k-th in (i, j), false beyond the last
+    __device__ __forceinline__ bool cell(int k, int &i, int &j) const
+    {
+        const int row = whole_x ? w : w + 2, rows = whole_y ? 0 : 2 * row;
+        if (k < rows) {
+            i = (k < row ? k : k - row) - (whole_x ? 0 : 1);
+            j = k < row ? -1 : h;
+            return true;
+        }
+        k -= rows;
+        i = k < h ? -1 : w;
+        j = k < h ? k : k - h;
+        return !whole_x && k < 2 * h;
+    }
+    // stores v for cell (i, j) of the tile or its ring, and for its images
+    template <class Slot, typename V>
+    __device__ __forceinline__ void put(const Slot &slot, int i, int j, V v) const
+    {
+        const bool lo = whole_x && i == (px ? w - 1 : 0), hi = whole_x && i == (px ? 0 : w - 1);
+        const bool bot = whole_y && j == (py ? h - 1 : 0), top = whole_y && j == (py ? 0 : h - 1);
+        auto row = [&](int jj) {
+            *slot(i, jj) = v;
+            if (lo) *slot(-1, jj) = v;
+            if (hi) *slot(w, jj) = v;
+        };
+        row(j);
+        if (bot) row(-1);
+        if (top) row(h);
+    }
+};
 
 // The first half of a tile from (x0, y0), bx = 2^lbx cells wide, 256 / bx rows
 // high: the thread's cell with its pulled populations, and phi of the tile and
@@ -157,27 +208,26 @@ __device__ __forceinline__ bool step2d_load(const Geom &g, const Ptrs &p, typena
         const Pull2d<decltype(rowu)::value> c(g, stencil_coord(x0 + i, g.nx, g.bcx),
                                               stencil_coord(y0 + j, g.ny, g.bcy));
         c.load(G, g.np, v);
-        *slot(i, j) = phi_sum9(v);
+        return phi_sum9(v);
     };
+    const Ring2d rim(g, w, h);
     if constexpr (ROWU) {
         if (ty < 2) {
-            if (tx < w) ring(std::true_type{}, tx, ty == 0 ? -1 : h);
+            if (tx < w) *slot(tx, ty == 0 ? -1 : h) = ring(std::true_type{}, tx, ty == 0 ? -1 : h);
         } else if (ty == 2) {
-            const int n = h + 2;
-            if (tx < 2 * n) ring(std::false_type{}, tx < n ? -1 : w, (tx < n ? tx : tx - n) - 1);
+            const int n = h + 2, i = tx < n ? -1 : w, j = (tx < n ? tx : tx - n) - 1;
+            if (tx < 2 * n) *slot(i, j) = ring(std::false_type{}, i, j);
         }
     } else {
-        if (tid < 2 * (w + 2 + h)) {
-            const int k = tid - 2 * (w + 2);
-            if (k < 0)
-                ring(std::false_type{}, (tid < w + 2 ? tid : tid - (w + 2)) - 1, tid < w + 2 ? -1 : h);
-            else
-                ring(std::false_type{}, k < h ? -1 : w, k < h ? k : k - h);
-        }
+        int i, j;
+        if (rim.cell(tid, i, j)) rim.put(slot, i, j, ring(std::false_type{}, i, j));
     }
     if (active) {
         const T s = phi_sum9(nb.gp);
-        *slot(tx, ty) = s;
+        if constexpr (ROWU)
+            *slot(tx, ty) = s;
+        else
+            rim.put(slot, tx, ty, s);
         if (flag && !__builtin_isfinite(s)) atomicOr(flag, 1);
     }
     __syncthreads();
@@ -274,15 +324,19 @@ __device__ __forceinline__ void step2d_tile16(const Geom &g, const Phys<float> &
     const int ty = WIDE ? __builtin_amdgcn_readfirstlane(tid >> 6) : tid >> lbx;
     const int w = min(bx, g.nx - x0), h = min(by, g.ny - y0);
     auto slot = [&](int i, int j) { return lrec + (j + 1) * ls + i + 1; };
-    auto record = [&](const auto &nb, unsigned long long *to) {
+    const Ring2d rim(g, w, h);
+    auto record = [&](const auto &nb, int i, int j, unsigned long long *to) {
         const float s = phi_value<2, P>(nb, g.np, p);
-        *to = make_rec(s, own_at(nb, p.ref_in));
+        if constexpr (WIDE)
+            *to = make_rec(s, own_at(nb, p.ref_in));
+        else
+            rim.put(slot, i, j, make_rec(s, own_at(nb, p.ref_in)));
         return s;
     };
     // the ring: beyond walls and symmetry planes the mirrored cell's record
     auto ring = [&](auto *form, int i, int j) {
-        record(make_nb(g, stencil_coord(x0 + i, g.nx, g.bcx), stencil_coord(y0 + j, g.ny, g.bcy), 0, form),
-               slot(i, j));
+        record(make_nb(g, stencil_coord(x0 + i, g.nx, g.bcx), stencil_coord(y0 + j, g.ny, g.bcy), 0, form), i,
+               j, slot(i, j));
     };
     const bool active = tx < w && ty < h;
     NbTile16<NB, KEPT> nb;
@@ -290,7 +344,7 @@ __device__ __forceinline__ void step2d_tile16(const Geom &g, const Phys<float> &
         static_cast<NB &>(nb) = make_nb(g, x0 + tx, y0 + ty, 0, (NB *)nullptr);
         nb.lrec = slot(tx, ty);
         nb.ls = ls;
-        const float s = record(nb, slot(tx, ty));
+        const float s = record(nb, tx, ty, slot(tx, ty));
         if (flag && !__builtin_isfinite(s)) atomicOr(flag, 1);
     }
     if constexpr (WIDE) {
@@ -300,12 +354,9 @@ __device__ __forceinline__ void step2d_tile16(const Geom &g, const Phys<float> &
             const int n = h + 2;
             if (tx < 2 * n) ring((Kept<NbFlat> *)nullptr, tx < n ? -1 : w, (tx < n ? tx : tx - n) - 1);
         }
-    } else if (tid < 2 * (w + 2 + h)) {
-        const int k = tid - 2 * (w + 2);
-        if (k < 0)
-            ring((Kept<NbFlat> *)nullptr, (tid < w + 2 ? tid : tid - (w + 2)) - 1, tid < w + 2 ? -1 : h);
-        else
-            ring((Kept<NbFlat> *)nullptr, k < h ? -1 : w, k < h ? k : k - h);
+    } else {
+        int i, j;
+        if (rim.cell(tid, i, j)) ring((Kept<NbFlat> *)nullptr, i, j);
     }
     __syncthreads();
     if (active) collide_body<2, P, COLL>(nb, g, ph, p);
@@ -333,7 +384,7 @@ __device__ __forceinline__ void step2d_any(const Geom &g, const Phys<typename P:
 template <class P>
 __host__ __device__ inline int step2d_form(const Geom &g, int lbx)
 {
-    if (lbx < 6) return TILE_NARROW;
+    if (lbx != 6) return TILE_NARROW;
     return P::F::shifted && g.bcx == BC_PER && 9 * g.np < (1ll << 31) ? TILE_ROW : TILE_WIDE;
 }
 
