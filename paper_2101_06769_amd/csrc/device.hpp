@@ -39,6 +39,7 @@
 
 #include <type_traits>
 
+#include "hostplan.hpp"
 #include "internal.h"
 
 namespace mplb {
@@ -1419,7 +1420,7 @@ using NbOf = typename std::conditional<FORM == FORM_PACK, NbPack,
 
 // Packed form: thread -> cell, PACK_THREADS consecutive cells of a plane per
 // block.  False where the block reaches past the plane.
-constexpr int PACK_THREADS = 256;
+constexpr int PACK_THREADS = int(PACK_BLOCK);
 __device__ __forceinline__ bool pack_cell(const Geom &g, int block, int &x, int &y, int &z)
 {
     const int plane = g.nx * g.ny, per = (plane + PACK_THREADS - 1) / PACK_THREADS;
@@ -1742,20 +1743,17 @@ inline hipError_t dispatch(const Ctx &c, Fn &&fn)
     return hipErrorInvalidValue;
 }
 
-// Packed planes on 3-D lattices periodic in x and y, the arrays within 32-bit
-// indices, where rows would leave lanes idle.  Per step, rows and packed: FP32
-// 97 x 96 x 200 282 and 201 us, 200 x 100 x 150 409 and 326, 300 x 100 x 100 541 and
-// 350, 320 x 128 x 160 850 and 694; FP64 96 x 96 x 200 405 and 386; FP16S_ALL
-// 96 x 96 x 384 334 and 282.  Rows stay where they fill 3/4 of their blocks and
-// start at cache lines in FP32, which a packed wavefront's would straddle
-// (96 x 96 x 384 364 and 374, 576 x 100 x 100 586 and 594).
+// The launch's shape as the rules of hostplan.hpp take it.
+inline Shape3 shape_of(const Ctx &c)
+{
+    return Shape3{c.g.nx, c.g.ny, c.g.nz, c.block.x, c.block.y, c.block.z, c.storage == ST_FP64 || c.storage == ST_FP32,
+                  c.storage == ST_FP32, kept_in_cache(3, c.storage, c.g.np)};
+}
+// Whether a launch takes packed planes (packs_planes has the rule).
 inline bool pack_form(const Ctx &c)
 {
-    if (c.dim != 3 || c.g.bcx != BC_PER || c.g.bcy != BC_PER || 27 * c.g.np >= (1ll << 31)) return false;
-    const long long nx = c.g.nx, bx = c.block.x, wide = (nx + bx - 1) / bx * bx;
-    if (bx % 64 != 0) return true;
-    if (kept_in_cache(3, c.storage, c.g.np)) return nx % 64 != 0;
-    return wide != nx && !(c.storage == ST_FP32 && nx % 32 == 0 && 4 * nx >= 3 * wide);
+    return c.dim == 3 && c.g.bcx == BC_PER && c.g.bcy == BC_PER && 27 * c.g.np < (1ll << 31) &&
+           packs_planes(shape_of(c));
 }
 inline unsigned pack_blocks(const Geom &g)
 {

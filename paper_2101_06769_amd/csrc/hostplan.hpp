@@ -96,4 +96,43 @@ std::vector<CacheGroup> cache_groups(const std::vector<long long> &cells, size_t
     return out;
 }
 
+// Packed planes on 3-D lattices periodic in x and y, the arrays within 32-bit
+// indices, where rows would leave lanes idle.  Per step, rows and packed: FP32
+// 97 x 96 x 200 282 and 201 us, 200 x 100 x 150 409 and 326, 300 x 100 x 100 541 and
+// 350, 320 x 128 x 160 850 and 694; FP64 96 x 96 x 200 405 and 386; FP16S_ALL
+// 96 x 96 x 384 334 and 282.  Rows stay where they fill 3/4 of their blocks and
+// start at cache lines in FP32, which a packed wavefront's would straddle
+// (96 x 96 x 384 364 and 374, 576 x 100 x 100 586 and 594).
+// A plane of few cells fills little of its block: the block's own form stays where
+// packed planes would take more lanes than pack_lanes_ratio times its own.
+constexpr long long PACK_BLOCK = 256;
+struct Shape3 {
+    long long nx, ny, nz, bx, by, bz;  // lattice and block
+    bool plain, fp32, kept;            // storage FP64 or FP32; FP32; populations in the cache
+};
+inline long long up_to(long long n, long long b) { return (n + b - 1) / b * b; }
+inline long long block_lanes(const Shape3 &s)
+{
+    return up_to(s.nx, s.bx) * up_to(s.ny, s.by) * up_to(s.nz, s.bz);
+}
+inline long long pack_lanes(const Shape3 &s) { return up_to(s.nx * s.ny, PACK_BLOCK) * s.nz; }
+// Rows: 4 in plain storage and 1 in the FP16 formats (100 x 1 x 3000, twice the
+// lanes, FP32 39 and 33 us a step, FP16S_ALL 40 and 48; 63 x 3 x 1587, as many,
+// FP16S_ALL 42 and 43).  Per-lane blocks (not whole wavefronts wide), of more
+// integer work a lane: 8 and 4 (32 x 1 x 9375, 8 times, FP32 48 and 43, FP16S_ALL
+// 54 and 64; 9 x 3 x 11111, 4 times, FP16S_ALL 102 and 80; 16 x 1 x 18750, 16 times,
+// FP32 48 and 75; 1 x 1 x 300000, 256 times, FP32 48 and 1017).
+inline long long pack_lanes_ratio(const Shape3 &s)
+{
+    return s.bx % 64 == 0 ? (s.plain ? 4 : 1) : (s.plain ? 8 : 4);
+}
+inline bool packs_planes(const Shape3 &s)
+{
+    if (pack_lanes(s) > pack_lanes_ratio(s) * block_lanes(s)) return false;
+    if (s.bx % 64 != 0) return true;
+    if (s.kept) return s.nx % 64 != 0;
+    const long long wide = up_to(s.nx, s.bx);
+    return wide != s.nx && !(s.fp32 && s.nx % 32 == 0 && 4 * s.nx >= 3 * wide);
+}
+
 }  // namespace mplb

@@ -1,6 +1,7 @@
 """Decisions of the host code that need no device, built here with g++: when
 mplb_read writes into the caller's memory itself, when a batch's captured graph
-outlives a change of its domains, and which domains of a batch advance together."""
+outlives a change of its domains, which domains of a batch advance together, and
+which lattices take which launch shapes."""
 import ctypes
 import os
 import random
@@ -118,3 +119,41 @@ def test_cache_groups_of_a_batch(plan):
     for _ in range(300):
         cells = [rng.randint(1, rng.choice([20, 100, 150])) for _ in range(rng.randint(1, 70))]
         check_groups(plan, cells, 100, rng.choice([2, 5, 32]))
+
+
+def pow2(v, cap):
+    b = 1
+    while b < v and b < cap:
+        b *= 2
+    return b
+
+
+def default_block(nx, ny, nz):
+    bx = pow2(nx, 256)
+    by = pow2(ny, 256 // bx)
+    return bx, by, pow2(nz, 256 // (bx * by))
+
+
+def packs(plan, n, storage, kept=1, block=None):
+    a = (ctypes.c_int * 6)(*n, *(block or default_block(*n)))
+    plan.lanes.restype = ctypes.c_int64
+    return bool(plan.packs_planes(a, storage, kept)), plan.lanes(a, 1), plan.lanes(a, 0)
+
+
+def test_packed_planes_do_not_multiply_the_lanes(plan):
+    # planes of few cells: a block of 256 threads each
+    for n in [(1, 1, 300000), (2, 1, 150000), (3, 1, 100000), (1, 10, 30000), (16, 1, 18750), (3, 3, 33333)]:
+        for storage in range(4):
+            assert not packs(plan, n, storage)[0], (n, storage)
+    for nx in [1, 2, 3, 5, 9, 16, 20, 24, 33, 48, 63, 65, 100, 127, 129, 200, 300]:
+        for ny in [1, 2, 3, 7, 10, 50]:
+            for nz in [1, 7, 1000]:
+                for storage in range(4):
+                    took, packed, blocks = packs(plan, (nx, ny, nz), storage)
+                    assert not took or packed <= (8 if storage < 2 else 4) * blocks
+    # what packed planes are for
+    for n in [(97, 96, 200), (48, 48, 192), (32, 32, 128), (100, 3, 1000), (9, 10, 3333), (20, 10, 1500)]:
+        for storage in range(4):
+            assert packs(plan, n, storage)[0], (n, storage)
+    assert not packs(plan, (128, 64, 64), 1)[0] and not packs(plan, (96, 96, 384), 1, kept=0)[0]
+    assert packs(plan, (128, 64, 64), 1, block=(8, 4, 1))[0]  # not whole wavefronts wide
