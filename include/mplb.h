@@ -263,10 +263,10 @@ int mplb_load(mplb_solver *s, const void *host_blob, size_t bytes);
  * depend on the shape.  The library sets the shape aside where it has a
  * better one: 2-D steps take tiles of its own; 3-D lattices periodic in x and
  * y whose rows would leave lanes of the block idle (any block not a multiple
- * of 64 wide among them) take 256 consecutive cells of a plane; other 3-D
- * lattices whose rows fill less than 3/4 of the block's width take blocks 64
- * wide where those fill more; the update that sums phi takes its own tiles
- * (mplb_set_phi_partials).  Errors: EINVAL.  Design, not in the paper. */
+ * of 64 wide among them) take 256 consecutive cells of a plane, unless a
+ * plane has too few; other 3-D lattices whose rows fill less than 3/4 of the
+ * block's width take blocks 64 wide where those are fuller; the update that
+ * sums phi takes its own tiles (mplb_set_phi_partials).  Errors: EINVAL.  Design, not in the paper. */
 int mplb_set_block(mplb_solver *s, int32_t bx, int32_t by, int32_t bz);
 
 /* Next order parameter from partial sums.  phi at a cell is the zeroth

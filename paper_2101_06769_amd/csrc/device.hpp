@@ -1762,15 +1762,10 @@ inline unsigned pack_blocks(const Geom &g)
 }
 inline bool row_form(const Ctx &c) { return row_form_ok(c.dim, c.g, c.block); }
 
-// The context's block, or one a wavefront wide where its rows would fill less
-// than 3/4 of it and a wavefront's width fills more (320 cells take two blocks
-// of 256).  Lattices with walls or symmetry planes in x or y: the others are
-// packed (320 x 128 x 160, measured periodic: FP64 1759 -> 1336 us a step).
+// The context's block, or one a wavefront wide (takes_narrow_blocks has the rule).
 inline dim3 filled_block(const Ctx &c)
 {
-    const long long nx = c.g.nx, bx = c.block.x;
-    const long long wide = (nx + bx - 1) / bx * bx, waves = (nx + 63) / 64 * 64;
-    if (4 * nx >= 3 * wide || waves >= wide) return c.block;
+    if (!takes_narrow_blocks(shape_of(c))) return c.block;
     const unsigned by = c.g.ny >= 4 ? 4 : c.g.ny >= 2 ? 2 : 1;
     return dim3(64, by, c.g.nz >= int(4 / by) ? 4 / by : 1);
 }

@@ -135,4 +135,22 @@ inline bool packs_planes(const Shape3 &s)
     return wide != s.nx && !(s.fp32 && s.nx % 32 == 0 && 4 * s.nx >= 3 * wide);
 }
 
+// Whether blocks a wavefront wide take the place of a lattice's own, whose rows
+// would fill less than 3/4 of it: from 50 000 cells (less do not fill the chip
+// either way; 300 x 10 x 10 FP16S_ALL 13.3 us a step and 14.2 with them) where
+// whole wavefronts are at least 4/5 full (320 cells take two blocks of 256), and
+// on plain lattices of 200 000 cells and more in the Infinity Cache.  Lattices with walls or symmetry planes in x or y:
+// the others are packed.  Per step, wide and narrow: 320 x 79 x 79 FP32 257 and
+// 207 us, FP16S_ALL 219 and 177; 160 x 111 x 111 FP64 460 and 427; 129 x 48 x 48 FP32
+// 53 and 47; but 129 x 124 x 124 FP32 331 and 395, FP16S_ALL 294 and 361, 129 x 48 x
+// 48 49 and 59, FP32 129 x 27 x 27 20 and 24, 129 x 7 x 7 12 and 18 (a third
+// wavefront of one cell, and rows that are cut inside cache lines).
+inline bool takes_narrow_blocks(const Shape3 &s)
+{
+    const long long wide = up_to(s.nx, s.bx), waves = up_to(s.nx, 64);
+    const long long cells = s.nx * s.ny * s.nz;
+    if (4 * s.nx >= 3 * wide || waves >= wide || cells < 50000) return false;
+    return 5 * s.nx >= 4 * waves || (s.plain && s.kept && cells >= 200000);
+}
+
 }  // namespace mplb

@@ -55,4 +55,8 @@ int64_t lanes(const int *n, int packed)
     const mplb::Shape3 s = shape_of(n, 0, 1);
     return packed ? mplb::pack_lanes(s) : mplb::block_lanes(s);
 }
+int narrow_blocks(const int *n, int storage, int kept)
+{
+    return mplb::takes_narrow_blocks(shape_of(n, storage, kept));
+}
 }

@@ -157,3 +157,18 @@ def test_packed_planes_do_not_multiply_the_lanes(plan):
             assert packs(plan, n, storage)[0], (n, storage)
     assert not packs(plan, (128, 64, 64), 1)[0] and not packs(plan, (96, 96, 384), 1, kept=0)[0]
     assert packs(plan, (128, 64, 64), 1, block=(8, 4, 1))[0]  # not whole wavefronts wide
+
+
+def test_narrow_blocks_only_where_they_fill(plan):
+    def narrow(n, storage, kept):
+        return bool(plan.narrow_blocks((ctypes.c_int * 6)(*n, *default_block(*n)), storage, kept))
+
+    for storage in range(4):
+        for kept in (0, 1):
+            assert narrow((320, 79, 79), storage, kept) and narrow((160, 111, 111), storage, kept)
+            assert not narrow((200, 50, 50), storage, kept) and not narrow((64, 50, 50), storage, kept)
+            assert not narrow((40, 40, 40), storage, kept) and not narrow((65, 40, 40), storage, kept)
+            assert not narrow((300, 10, 10), storage, kept) and not narrow((320, 9, 9), storage, kept)
+        # a third wavefront of one cell
+        assert not narrow((129, 124, 124), storage, 0) and not narrow((129, 27, 27), storage, 1)
+        assert narrow((129, 48, 48), storage, 1) == (storage < 2)
