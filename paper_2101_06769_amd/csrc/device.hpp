@@ -1785,7 +1785,12 @@ inline hipError_t with_form(const Ctx &ctx, Fn &&fn)
     auto go = [&]<int FORM>(dim3 grid, dim3 block) {
         using NB = NbOf<FORM>;
         if constexpr (KEEP && !P::F::shifted && D == 3) {
-            if (kept_in_cache(3, c.storage, c.g.np)) return fn.template operator()<Kept<NB>, FORM>(grid, block);
+            // FP32 rows of less than 80 000 cells, about a wavefront per SIMD, are
+            // faster without (33 x 34 x 34 between walls 14.9 us a step and 17.5
+            // with Kept forms, 40 x 40 x 40 16.7 and 18.4; 40 x 50 x 50 21.1 and 20.4)
+            const bool few = FORM == FORM_ROW && sizeof(typename P::T) == 4 && c.g.np < 80000;
+            if (kept_in_cache(3, c.storage, c.g.np) && !few)
+                return fn.template operator()<Kept<NB>, FORM>(grid, block);
         }
         return fn.template operator()<NB, FORM>(grid, block);
     };
