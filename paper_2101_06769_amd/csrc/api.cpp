@@ -1101,7 +1101,7 @@ int upload_tables(mplb_batch *b)
             for (size_t k = 0; k < cg.members.size(); ++k) {
                 ids[k] = cg.members[k];
                 run[k] = int(n);
-                n += mplb::step2d_tiles(b->doms[cg.members[k]].g);
+                n += mplb::step2d_tiles(b->doms[cg.members[k]].g, b->storage);
                 if (n > 0x3fffffffLL) return fail(MPLB_ENOMEM, "batch tile list is full");
             }
             run[cg.members.size()] = int(n);

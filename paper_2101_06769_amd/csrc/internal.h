@@ -72,7 +72,7 @@ hipError_t launch_collide(const Ctx &c);
 // tile and the ring of cells around it into LDS, then updates its cells; the
 // phi array is not written.  Its tiles (step2d_tiles of them) do not depend on
 // the context's block.
-int step2d_tiles(const Geom &g);
+int step2d_tiles(const Geom &g, int storage);
 hipError_t launch_step2d(const Ctx &c);
 // Several steps of a small such lattice in plain storage in one launch, from the Fin/Gin to the
 // Fout/Gout buffers: the number of steps multi2d_steps gives (1: none; single

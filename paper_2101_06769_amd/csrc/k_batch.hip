@@ -95,7 +95,7 @@ kb_step2d(const BatchDom *__restrict__ doms, const int *__restrict__ table, int 
     const Geom g = doms[dom].g;  // by value, see kb_step
     const Ptrs p = batch_ptrs(doms[dom], int((t - first) & 1), t >= doms[dom].hist_from);
     const Phys<T> ph = to_phys<T>(doms[dom].ph);
-    const int lbx = step2d_width(g), by = STEP2D_THREADS >> lbx;
+    const int lbx = step2d_width(g, P::F::shifted), by = STEP2D_THREADS >> lbx;
     const int ntx = (g.nx + (1 << lbx) - 1) >> lbx, k = bid - tile0[at];
     const int x0 = (k % ntx) << lbx, y0 = (k / ntx) * by;
     // the fast tile form of the format, and one for all other domains: in the

@@ -359,8 +359,8 @@ hipError_t launch_field(const Ctx &c, int field, double *dst)
             });
         }
         if constexpr (D == 2 && !P::F::shifted) {
-            const int lbx = step2d_width(c.g), ntx = (c.g.nx + (1 << lbx) - 1) >> lbx;
-            const int nt = step2d_tiles(c.g);
+            const int lbx = step2d_width(c.g, false), ntx = (c.g.nx + (1 << lbx) - 1) >> lbx;
+            const int nt = step2d_tiles(c.g, c.storage);
             auto go = [&](auto kernel) {
                 hipError_t e = hipSuccess;
                 for (int first = 0; first < nt && e == hipSuccess; first += GRID_ROW) {

@@ -19,16 +19,16 @@ k_step2d(Geom g, Phys<typename P::T> ph, Ptrs p, int lbx, int ntx, int nt, int f
     step2d_any<P, COLL, KEPT, TILE>(g, ph, p, lds, lbx, x0, y0, nullptr);
 }
 
-int step2d_tiles(const Geom &g)
+int step2d_tiles(const Geom &g, int storage)
 {
-    const int lbx = step2d_width(g), by = STEP2D_THREADS >> lbx;
+    const int lbx = step2d_width(g, storage == ST_FP16S || storage == ST_FP16S_ALL), by = STEP2D_THREADS >> lbx;
     return ((g.nx + (1 << lbx) - 1) >> lbx) * ((g.ny + by - 1) / by);
 }
 
 hipError_t launch_step2d(const Ctx &c)
 {
-    const int lbx = step2d_width(c.g);
-    const int ntx = (c.g.nx + (1 << lbx) - 1) >> lbx, nt = step2d_tiles(c.g);
+    const int lbx = step2d_width(c.g, c.storage == ST_FP16S || c.storage == ST_FP16S_ALL);
+    const int ntx = (c.g.nx + (1 << lbx) - 1) >> lbx, nt = step2d_tiles(c.g, c.storage);
     const bool kept = kept_in_cache(2, c.storage, c.g.np);
     return dispatch(c, [&]<int D, class P>() -> hipError_t {
         if constexpr (D != 2) {

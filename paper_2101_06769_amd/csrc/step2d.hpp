@@ -105,17 +105,18 @@ __device__ __forceinline__ T phi_sum9(const T (&v)[9])
 }
 
 // Tile: 256 threads, 64 x 4 cells; narrower and taller on lattices of less than
-// 64 columns (down to one); on long ones of few rows 256 x 1, 128 x 2 and 32 x 8
-// (5 or 6 rows), so that few threads are without a cell.  With tiles of at least
+// 64 columns (down to one); on long ones of few rows 256 x 1, 128 x 2 and, in
+// plain storage, 32 x 8 (5 or 6 rows), so that few threads are without a cell.  With tiles of at least
 // 8 columns and 4 rows, and with these, a step in us: 3 million cells in one
 // column FP32 310 and 87, FP16S_ALL 546 and 91; 300 000 in one row 14.7 and 10.9,
 // 17.8 and 12.7; 600 000 x 5 FP64 221 and 177.  Shorter rows leave CUs idle in any case and
 // are faster as whole wavefronts (20 000 cells FP16S 5.3 and 5.7), as are 7 and 8
-// rows (428 571 x 7 FP32 119 and 139).
+// rows (428 571 x 7 FP32 119 and 139) and the FP16 formats' row form (600 000 x 5
+// FP16S_ALL 102 and 114).
 constexpr int STEP2D_THREADS = 256;
-__host__ __device__ inline int step2d_width(const Geom &g)
+__host__ __device__ inline int step2d_width(const Geom &g, bool fp16)
 {
-    if (g.nx > 65536) return g.ny == 1 ? 8 : g.ny == 2 ? 7 : g.ny == 5 || g.ny == 6 ? 5 : 6;
+    if (g.nx > 65536) return g.ny == 1 ? 8 : g.ny == 2 ? 7 : (g.ny == 5 || g.ny == 6) && !fp16 ? 5 : 6;
     if (g.nx > 64) return 6;
     int l = 0;
     while ((1 << l) < g.nx) ++l;
