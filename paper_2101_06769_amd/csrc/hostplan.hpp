@@ -153,4 +153,26 @@ inline bool takes_narrow_blocks(const Shape3 &s)
     return 5 * s.nx >= 4 * waves || (s.plain && s.kept && cells >= 200000);
 }
 
+// Whether the 2-D step stores its populations with ordinary stores: where they
+// stay in the Infinity Cache (kept), and where rows do not start at 64-byte
+// boundaries.  Lines that two rows or tiles share are then completed in L2;
+// stored non-temporally, their parts went to HBM one by one.  elem: bytes of a value
+// of g.  Beyond the cache, per step, non-temporal and ordinary: 129 x 46511 FP32
+// 311 and 224 us, FP64 488 and 404, FP16S 291 and 228, FP16S_ALL 244 and 203; with
+// 64-byte rows 400 x 7500 FP32 101 and 103, 96 x 31250 101 and 105, 200 x 15000
+// FP64 194 and 206.
+inline bool stores_stay2d(int nx, int elem, bool kept) { return kept || (long long)nx * elem % 64 != 0; }
+// Columns of a tile of whole wavefronts.  An even number of tiles per row, with
+// ordinary stores, shares the row evenly where the last one would otherwise be
+// narrow, and beyond the cache in any case: with tiles of 64 and 1 column a step
+// of 65 x 307 FP16S took 8.3 us, of 33 and 32 5.4; 65 x 92307 FP32 298 and 249,
+// 100 x 60000 271 and 264, 200 x 1500 13.8 and 11.8.  Not an odd number (129 x
+// 46511 FP32 224 and 238), nor with non-temporal stores (120 x 25000 FP64 183 and
+// 201).
+inline int tile_columns2d(int nx, bool stay, bool kept)
+{
+    const int tiles = (nx - 1) / 64 + 1, last = nx - (tiles - 1) * 64;
+    return tiles % 2 == 0 && stay && (last < 32 || !kept) ? (nx - 1) / tiles + 1 : 64;
+}
+
 }  // namespace mplb

@@ -219,7 +219,8 @@ __global__ void __launch_bounds__(STEP2D_THREADS) k_field2d(Geom g, Phys<typenam
     const int bid = tile_of<true>(first + int(blockIdx.x), nt);
     const int by = ROWU ? STEP2D_THREADS / 64 : STEP2D_THREADS >> lbx;
     NbTile<T, false> nb;
-    if (!step2d_load<P, ROWU, false>(g, p, lphi, lbx, (bid % ntx) << lbx, (bid / ntx) * by, nullptr, nb)) return;
+    const int x0 = (bid % ntx) << lbx, y0 = (bid / ntx) * by;
+    if (!step2d_load<P, ROWU, false>(g, p, lphi, lbx, 1 << lbx, x0, y0, nullptr, nb)) return;
     Cell<T> c;
     eval_cell<2, P>(nb, g.np, ph, p, c);
     put_field(dst, nb, field_of(c, field));

@@ -175,8 +175,8 @@ struct Ring2d {
     }
 };
 
-// The first half of a tile from (x0, y0), bx = 2^lbx cells wide, 256 / bx rows
-// high: the thread's cell with its pulled populations, and phi of the tile and
+// The first half of a tile from (x0, y0), bx = 2^lbx threads wide (cols of them
+// with cells), 256 / bx rows high: the thread's cell with its pulled populations, and phi of the tile and
 // its ring in lphi.  False for threads without a cell.
 // KEPT: the populations are stored to stay in the Infinity Cache (kept_in_cache).
 // flag, if given: or-ed with 1 where phi is not finite.
@@ -185,14 +185,14 @@ struct Ring2d {
 // first two wavefronts in row form, the columns beside it by the third.
 template <class P, bool ROWU, bool KEPT>
 __device__ __forceinline__ bool step2d_load(const Geom &g, const Ptrs &p, typename P::T *lphi, int lbx,
-                                            int x0, int y0, int *flag, NbTile<typename P::T, KEPT> &nb)
+                                            int cols, int x0, int y0, int *flag, NbTile<typename P::T, KEPT> &nb)
 {
     using T = typename P::T;
     const int bx = ROWU ? 64 : 1 << lbx, by = STEP2D_THREADS / bx, ls = bx + 2;
     const int tid = int(threadIdx.x);
     const int tx = tid & (bx - 1);
     const int ty = ROWU ? __builtin_amdgcn_readfirstlane(tid >> 6) : tid >> lbx;
-    const int w = min(bx, g.nx - x0), h = min(by, g.ny - y0);
+    const int w = min(cols, g.nx - x0), h = min(by, g.ny - y0);
     const T *F = static_cast<const T *>(p.Fin), *G = static_cast<const T *>(p.Gin);
     // slot (i, j) of the tile, i, j from -1
     auto slot = [&](int i, int j) { return lphi + (j + 1) * ls + i + 1; };
@@ -242,11 +242,11 @@ __device__ __forceinline__ bool step2d_load(const Geom &g, const Ptrs &p, typena
 // One tile of the step.
 template <class P, int COLL, bool ROWU, bool KEPT>
 __device__ __forceinline__ void step2d_tile(const Geom &g, const Phys<typename P::T> &ph, const Ptrs &p,
-                                            typename P::T *lphi, int lbx, int x0, int y0,
+                                            typename P::T *lphi, int lbx, int cols, int x0, int y0,
                                             int *flag = nullptr)
 {
     NbTile<typename P::T, KEPT> nb;
-    if (step2d_load<P, ROWU, KEPT>(g, p, lphi, lbx, x0, y0, flag, nb)) collide_body<2, P, COLL>(nb, g, ph, p);
+    if (step2d_load<P, ROWU, KEPT>(g, p, lphi, lbx, cols, x0, y0, flag, nb)) collide_body<2, P, COLL>(nb, g, ph, p);
 }
 
 // Lane form of the FP16 formats' pulls: the rules of both axes as per-lane selects
@@ -316,14 +316,14 @@ __device__ __forceinline__ R own_at(const NbFlat &n, const R *base)
 // level's to another array, since neighbouring blocks still read these.
 template <class P, int COLL, class NB, bool KEPT, bool WIDE>
 __device__ __forceinline__ void step2d_tile16(const Geom &g, const Phys<float> &ph, const Ptrs &p,
-                                              unsigned long long *lrec, int lbx, int x0, int y0,
+                                              unsigned long long *lrec, int lbx, int cols, int x0, int y0,
                                               int *flag = nullptr)
 {
     const int bx = WIDE ? 64 : 1 << lbx, by = STEP2D_THREADS / bx, ls = bx + 2;
     const int tid = int(threadIdx.x);
     const int tx = tid & (bx - 1);
     const int ty = WIDE ? __builtin_amdgcn_readfirstlane(tid >> 6) : tid >> lbx;
-    const int w = min(bx, g.nx - x0), h = min(by, g.ny - y0);
+    const int w = min(cols, g.nx - x0), h = min(by, g.ny - y0);
     auto slot = [&](int i, int j) { return lrec + (j + 1) * ls + i + 1; };
     const Ring2d rim(g, w, h);
     auto record = [&](const auto &nb, int i, int j, unsigned long long *to) {
@@ -367,15 +367,15 @@ __device__ __forceinline__ void step2d_tile16(const Geom &g, const Phys<float> &
 enum { TILE_NARROW, TILE_WIDE, TILE_ROW, TILE_LANE };
 template <class P, int COLL, bool KEPT, int TILE>
 __device__ __forceinline__ void step2d_any(const Geom &g, const Phys<typename P::T> &ph, const Ptrs &p,
-                                           void *lds, int lbx, int x0, int y0, int *flag)
+                                           void *lds, int lbx, int cols, int x0, int y0, int *flag)
 {
     if constexpr (P::F::shifted) {
         using NB = typename std::conditional<TILE == TILE_ROW, NbRow,
                    typename std::conditional<TILE == TILE_LANE, NbLane, NbFlat>::type>::type;
         step2d_tile16<P, COLL, NB, KEPT, TILE == TILE_WIDE || TILE == TILE_ROW>(g, ph, p, static_cast<unsigned long long *>(lds),
-                                                              lbx, x0, y0, flag);
+                                                              lbx, cols, x0, y0, flag);
     } else {
-        step2d_tile<P, COLL, TILE == TILE_WIDE, KEPT>(g, ph, p, static_cast<typename P::T *>(lds), lbx, x0,
+        step2d_tile<P, COLL, TILE == TILE_WIDE, KEPT>(g, ph, p, static_cast<typename P::T *>(lds), lbx, cols, x0,
                                                         y0, flag);
     }
 }

@@ -59,4 +59,6 @@ int narrow_blocks(const int *n, int storage, int kept)
 {
     return mplb::takes_narrow_blocks(shape_of(n, storage, kept));
 }
+int stores_stay2d(int nx, int elem, int kept) { return mplb::stores_stay2d(nx, elem, kept != 0); }
+int tile_columns2d(int nx, int stay, int kept) { return mplb::tile_columns2d(nx, stay != 0, kept != 0); }
 }

@@ -103,6 +103,8 @@ def test_phi_summing_domains_beside_a_packed_one(storage, collision):
 LARGE = [(2, (24, 500, 1), (0, 0, 0), 1, 320), (2, (24, 500, 1), (1, 0, 0), 1, 320),
          (2, (100, 500, 1), (2, 0, 0), 1, 80), (2, (128, 500, 1), (0, 0, 0), 1, 64),
          (2, (100, 500, 1), (0, 0, 0), 1, 80),
+         (2, (65, 500, 1), (1, 0, 0), 1, 130), (2, (193, 300, 1), (0, 0, 0), 1, 70),
+         (2, (75, 400, 1), (2, 0, 0), 1, 130), (2, (129, 300, 1), (0, 0, 0), 1, 100),
          (3, (36, 10, 31), (0, 0, 0), 2, 120), (3, (36, 10, 31), (0, 1, 0), 2, 120),
          (3, (64, 8, 31), (0, 0, 0), 2, 80), (3, (128, 6, 31), (0, 1, 0), 2, 60)]
 

@@ -172,3 +172,17 @@ def test_narrow_blocks_only_where_they_fill(plan):
         # a third wavefront of one cell
         assert not narrow((129, 124, 124), storage, 0) and not narrow((129, 27, 27), storage, 1)
         assert narrow((129, 48, 48), storage, 1) == (storage < 2)
+
+
+def test_2d_rows_are_covered_by_their_tiles(plan):
+    for nx in list(range(33, 1100)) + [65537, 100000, 1 << 29, 2 ** 31 - 65]:
+        tiles = (nx - 1) // 64 + 1
+        for kept in (0, 1):
+            for stay in ((1,) if kept else (0, 1)):
+                cols = plan.tile_columns2d(nx, stay, kept)
+                assert 1 <= cols <= 64 and (tiles - 1) * cols < nx <= tiles * cols, (nx, kept, stay, cols)
+                assert stay or cols == 64
+    assert plan.tile_columns2d(65, 1, 1) == 33 and plan.tile_columns2d(129, 1, 1) == 64
+    assert plan.tile_columns2d(100, 1, 0) == 50 and plan.tile_columns2d(100, 1, 1) == 64
+    for nx, elem, want in [(65, 4, 1), (80, 4, 0), (72, 4, 1), (72, 8, 0), (64, 2, 0), (80, 2, 1), (2 ** 31 - 65, 8, 1)]:
+        assert plan.stores_stay2d(nx, elem, 0) == want and plan.stores_stay2d(nx, elem, 1) == 1
