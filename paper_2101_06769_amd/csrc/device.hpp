@@ -1785,10 +1785,14 @@ inline hipError_t with_form(const Ctx &ctx, Fn &&fn)
     auto go = [&]<int FORM>(dim3 grid, dim3 block) {
         using NB = NbOf<FORM>;
         if constexpr (KEEP && !P::F::shifted && D == 3) {
-            // FP32 rows of less than 80 000 cells, about a wavefront per SIMD, are
-            // faster without (33 x 34 x 34 between walls 14.9 us a step and 17.5
-            // with Kept forms, 40 x 40 x 40 16.7 and 18.4; 40 x 50 x 50 21.1 and 20.4)
-            const bool few = FORM == FORM_ROW && sizeof(typename P::T) == 4 && c.g.np < 80000;
+            // FP32 rows of less than 80 000 cells and FP64 lattices of 12 000 to 36 000
+            // outside packed planes, about a wavefront per SIMD, are faster without
+            // (33 x 34 x 34 FP32 between walls 14.9 us a step and 17.5 with Kept forms,
+            // 40 x 40 x 40 16.7 and 18.4; 40 x 50 x 50 21.1 and 20.4; FP64 72 x 20 x 20
+            // 14.6 and 15.7, 9 x 57 x 57 23.3 and 24.9; 33 x 34 x 34 21.8 and 20.0)
+            const bool few = sizeof(typename P::T) == 4
+                                 ? FORM == FORM_ROW && c.g.np < 80000
+                                 : FORM != FORM_PACK && c.g.np >= 12000 && c.g.np < 36000;
             if (kept_in_cache(3, c.storage, c.g.np) && !few)
                 return fn.template operator()<Kept<NB>, FORM>(grid, block);
         }
