@@ -1746,8 +1746,9 @@ inline hipError_t dispatch(const Ctx &c, Fn &&fn)
 // The launch's shape as the rules of hostplan.hpp take it.
 inline Shape3 shape_of(const Ctx &c)
 {
-    return Shape3{c.g.nx, c.g.ny, c.g.nz, c.block.x, c.block.y, c.block.z, c.storage == ST_FP64 || c.storage == ST_FP32,
-                  c.storage == ST_FP32, kept_in_cache(3, c.storage, c.g.np)};
+    const bool plain = c.storage == ST_FP64 || c.storage == ST_FP32;
+    return Shape3{c.g.nx, c.g.ny, c.g.nz, c.block.x, c.block.y, c.block.z, plain, c.storage == ST_FP32,
+                  kept_in_cache(3, c.storage, c.g.np), c.storage == ST_FP16S_ALL && c.ph.collision != 0};
 }
 // Whether a launch takes packed planes (packs_planes has the rule).
 inline bool pack_form(const Ctx &c)

@@ -104,11 +104,12 @@ std::vector<CacheGroup> cache_groups(const std::vector<long long> &cells, size_t
 // start at cache lines in FP32, which a packed wavefront's would straddle
 // (96 x 96 x 384 364 and 374, 576 x 100 x 100 586 and 594).
 // A plane of few cells fills little of its block: the block's own form stays where
-// packed planes would take more lanes than pack_lanes_ratio times its own.
+// packed planes would take more lanes than pack_fifths / 5 times its own.
 constexpr long long PACK_BLOCK = 256;
 struct Shape3 {
     long long nx, ny, nz, bx, by, bz;  // lattice and block
     bool plain, fp32, kept;            // storage FP64 or FP32; FP32; populations in the cache
+    bool pulls_twice;                  // FP16S_ALL with a single relaxation time
 };
 inline long long up_to(long long n, long long b) { return (n + b - 1) / b * b; }
 inline long long block_lanes(const Shape3 &s)
@@ -116,19 +117,22 @@ inline long long block_lanes(const Shape3 &s)
     return up_to(s.nx, s.bx) * up_to(s.ny, s.by) * up_to(s.nz, s.bz);
 }
 inline long long pack_lanes(const Shape3 &s) { return up_to(s.nx * s.ny, PACK_BLOCK) * s.nz; }
-// Rows: 4 in plain storage and 1 in the FP16 formats (100 x 1 x 3000, twice the
-// lanes, FP32 39 and 33 us a step, FP16S_ALL 40 and 48; 63 x 3 x 1587, as many,
-// FP16S_ALL 42 and 43).  Per-lane blocks (not whole wavefronts wide), of more
-// integer work a lane: 8 and 4 (32 x 1 x 9375, 8 times, FP32 48 and 43, FP16S_ALL
-// 54 and 64; 9 x 3 x 11111, 4 times, FP16S_ALL 102 and 80; 16 x 1 x 18750, 16 times,
+// Rows: 4 times in plain storage and as many in the FP16 formats (100 x 1 x 3000,
+// twice the lanes, FP32 39 and 33 us a step, FP16S_ALL 40 and 48; 33 x 3 x 3030, as
+// many, FP16S_ALL 57 and 50), four fifths where the update pulls its FP16 codes
+// twice (single relaxation time, as many lanes: 63 x 178 x 178 276 and 308, 100 x 3
+// x 1000 67 and 79).  Per-lane blocks (not whole wavefronts wide), of more integer
+// work a lane: 8 and 4 times (32 x 1 x 9375, 8 times, FP32 48 and 43, FP16S_ALL 54
+// and 64; 9 x 3 x 11111, 4 times, FP16S_ALL 102 and 80; 16 x 1 x 18750, 16 times,
 // FP32 48 and 75; 1 x 1 x 300000, 256 times, FP32 48 and 1017).
-inline long long pack_lanes_ratio(const Shape3 &s)
+inline long long pack_fifths(const Shape3 &s)
 {
-    return s.bx % 64 == 0 ? (s.plain ? 4 : 1) : (s.plain ? 8 : 4);
+    if (s.bx % 64 != 0) return s.plain ? 40 : 20;
+    return s.plain ? 20 : s.pulls_twice ? 4 : 5;
 }
 inline bool packs_planes(const Shape3 &s)
 {
-    if (pack_lanes(s) > pack_lanes_ratio(s) * block_lanes(s)) return false;
+    if (5 * pack_lanes(s) > pack_fifths(s) * block_lanes(s)) return false;
     if (s.bx % 64 != 0) return true;
     if (s.kept) return s.nx % 64 != 0;
     const long long wide = up_to(s.nx, s.bx);

@@ -44,10 +44,12 @@ int cache_groups(const int64_t *cells, int n, int64_t limit, int max_groups, int
     return int(out.size());
 }
 
-// shape: nx, ny, nz, bx, by, bz; storage 0 FP64, 1 FP32, 2 FP16S, 3 FP16S_ALL.
+// shape: nx, ny, nz, bx, by, bz; storage 0 FP64, 1 FP32, 2 FP16S, 3 FP16S_ALL, 4 the
+// last with a single relaxation time.
 static mplb::Shape3 shape_of(const int *n, int storage, int kept)
 {
-    return mplb::Shape3{n[0], n[1], n[2], n[3], n[4], n[5], storage < 2, storage == 1, kept != 0};
+    return mplb::Shape3{n[0], n[1], n[2], n[3], n[4], n[5], storage < 2, storage == 1, kept != 0,
+                        storage == 4};
 }
 int packs_planes(const int *n, int storage, int kept) { return mplb::packs_planes(shape_of(n, storage, kept)); }
 int64_t lanes(const int *n, int packed)

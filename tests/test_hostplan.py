@@ -155,6 +155,10 @@ def test_packed_planes_do_not_multiply_the_lanes(plan):
     for n in [(97, 96, 200), (48, 48, 192), (32, 32, 128), (100, 3, 1000), (9, 10, 3333), (20, 10, 1500)]:
         for storage in range(4):
             assert packs(plan, n, storage)[0], (n, storage)
+    # FP16S_ALL with a single relaxation time: where they save a fifth of the lanes
+    for n in [(63, 178, 178), (100, 3, 1000), (129, 1, 2325), (127, 125, 125)]:
+        assert not packs(plan, n, 4, kept=0)[0] and not packs(plan, n, 4)[0], n
+    assert packs(plan, (96, 96, 384), 4, kept=0)[0] and packs(plan, (200, 100, 50), 4)[0]
     assert not packs(plan, (128, 64, 64), 1)[0] and not packs(plan, (96, 96, 384), 1, kept=0)[0]
     assert packs(plan, (128, 64, 64), 1, block=(8, 4, 1))[0]  # not whole wavefronts wide
 
