@@ -103,7 +103,7 @@ kb_step2d(const BatchDom *__restrict__ doms, const int *__restrict__ table, int 
     // kernel's (NbLane 64, NbFlat 98; 24 domains FP16S 42 and 47 us a step)
     constexpr int FAST = P::F::shifted ? TILE_ROW : TILE_WIDE, OTHER = P::F::shifted ? TILE_LANE : TILE_NARROW;
     if (step2d_form<P>(g, lbx) == FAST)
-        step2d_any<P, COLL, KEPT, FAST>(g, ph, p, lds, lbx, 1 << lbx, x0, y0, status + dom);
+        step2d_any<P, COLL, KEPT, FAST>(g, ph, p, lds, 6, 64, x0, y0, status + dom);
     else
         step2d_any<P, COLL, KEPT, OTHER>(g, ph, p, lds, lbx, 1 << lbx, x0, y0, status + dom);
 }
