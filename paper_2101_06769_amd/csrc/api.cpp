@@ -1030,7 +1030,12 @@ std::vector<mplb::CacheGroup> cache_groups(const mplb_batch *b)
             slots.push_back(i);
             cells.push_back(b->doms[i].g.np);
         }
-    auto fits = [&](long long n) { return mplb::kept_in_cache(b->dim, b->storage, n); };
+    // 3-D FP16 formats: one group of all; their kernels do not store to the cache,
+    // and several groups cost launches (five each of edge 48 and 64, FP16S 208 us a
+    // step in three groups and 172, FP16S_ALL 182 and 161; four of 128 x 64 x 100
+    // FP16S 317 and 272; four of edge 80 to 100 between walls 463 and 569)
+    const bool streams = b->dim == 3 && (b->storage == mplb::ST_FP16S || b->storage == mplb::ST_FP16S_ALL);
+    auto fits = [&](long long n) { return !streams && mplb::kept_in_cache(b->dim, b->storage, n); };
     std::vector<mplb::CacheGroup> out = mplb::cache_groups(cells, mplb::BATCH_GROUPS, fits);
     for (mplb::CacheGroup &c : out)
         for (int &m : c.members) m = slots[m];
