@@ -65,8 +65,9 @@ __attribute__((amdgpu_waves_per_eu(PHI ? 1 : collide_waves<3, P, COLL>()))) kb_s
 // Batched form of the one-launch 2-D step over one cache group (see
 // launch_batch_step2d): block b takes tile b of the group's running counts (in
 // eighths per XCD, as k_step2d); every wavefront finds the domain with one load
-// of 64 counts at a time.
-template <class P, int COLL, bool KEPT>
+// of 64 counts at a time.  FEW: all blocks of the launch are resident at once
+// (FP16 formats only, see below).
+template <class P, int COLL, bool KEPT, bool FEW>
 __global__ void __launch_bounds__(STEP2D_THREADS)
 kb_step2d(const BatchDom *__restrict__ doms, const int *__restrict__ table, int capacity, int group,
           const long long *tbase, int step_off, int *status)
@@ -100,8 +101,11 @@ kb_step2d(const BatchDom *__restrict__ doms, const int *__restrict__ table, int 
     const int x0 = (k % ntx) << lbx, y0 = (k / ntx) * by;
     // the fast tile form of the format, and one for all other domains: in the
     // FP16 formats the one of fewest registers, since both bodies share the
-    // kernel's (NbLane 64, NbFlat 98; 24 domains FP16S 42 and 47 us a step)
-    constexpr int FAST = P::F::shifted ? TILE_ROW : TILE_WIDE, OTHER = P::F::shifted ? TILE_LANE : TILE_NARROW;
+    // kernel's (NbLane 64, NbFlat 98; 24 domains FP16S 42 and 47 us a step), but
+    // the one of fewest instructions where occupancy does not matter (FEW: one
+    // domain of 20 to 60 cells a side 9.6 and 7.0, forty 12.0 and 9.6)
+    constexpr int FAST = P::F::shifted ? TILE_ROW : TILE_WIDE;
+    constexpr int OTHER = P::F::shifted && !FEW ? TILE_LANE : TILE_NARROW;
     if (step2d_form<P>(g, lbx) == FAST)
         step2d_any<P, COLL, KEPT, FAST>(g, ph, p, lds, 6, 64, x0, y0, status + dom);
     else
@@ -126,7 +130,11 @@ hipError_t launch_batch_step2d(int storage, int collision, bool kept, const Batc
                                        group, tbase, step_off, status);
                     return hipGetLastError();
                 };
-                return kept ? go(kb_step2d<P, COLL, true>) : go(kb_step2d<P, COLL, false>);
+                if constexpr (P::F::shifted) {
+                    // four blocks a CU: five fit with NbFlat's registers
+                    if (kept && grid <= 1024) return go(kb_step2d<P, COLL, true, true>);
+                }
+                return kept ? go(kb_step2d<P, COLL, true, false>) : go(kb_step2d<P, COLL, false, false>);
             });
         }
     });
