@@ -65,7 +65,8 @@ def nphi_bytes(storage, rows):
 
 
 KERNEL_SOURCES = ("device.hpp", "k_step.hip", "k_nphi.hip", "k_host.hip", "k_batch.hip",
-                  "k_batch_nphi.hip", "k_step2d.hip", "k_multi2d.hip", "step2d.hpp", "lattice.hpp", "internal.h")
+                  "k_batch_nphi.hip", "k_step2d.hip", "k_multi2d.hip", "step2d.hpp", "lattice.hpp", "hostplan.hpp",
+                  "internal.h")
 PROFILE_KERNELS = {"k_collide_nphi": "k_phi_merge", "k_collide": "k_phi", "k_step2d": None}
 PROFILES_DIR = os.path.join(ROOT, "profiles")
 

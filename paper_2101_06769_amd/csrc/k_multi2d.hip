@@ -4,9 +4,12 @@
 namespace mplb {
 
 // A step of a lattice of some 10^4 cells is a launch, a round trip to memory
-// and about 1.5 us of instruction issue at a wavefront per SIMD.  This kernel pays
+// and about 1.5 us of a wavefront's own chain of instructions.  This kernel pays
 // the first two once for K steps (64 x 256 FP64 4.85 -> 3.26 us a step, 97 x 113
-// FP32 4.44 -> 2.94), and is bound by that issue: a block loads a tile of MULTI_EDGE^2 cells
+// FP32 4.44 -> 2.94), and is bound by the chain: two wavefronts a SIMD keep the VALU
+// 38 % (64 x 256 FP64) to 41 % busy (128 x 512 FP32, single relaxation time); the
+// rest is dependent instructions and barriers, more so as the region shrinks to a
+// wavefront or two.  A block loads a tile of MULTI_EDGE^2 cells
 // into LDS and steps it there, the region it can still compute shrinking by two
 // cells a side and step (a cell's update reaches the phase-field values two
 // cells away), and stores the MULTI_EDGE - 4 K cells square that are left.  The

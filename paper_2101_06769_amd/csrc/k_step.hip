@@ -35,7 +35,8 @@ bool row_form_ok(int dim, const Geom &g, dim3 block)
 // it back from there (1024 x 1024 FP32, 151 MB: 35.3 against 24.9 us a step;
 // 1792 x 1024, 264 MB: 57.0 against 41.5).  Beyond that size cached stores only
 // displace what the step has yet to read (2048 x 1024, 302 MB: 64.1 against
-// 65.0 us; 2048 x 2048: 124 against 130).
+// 65.0 us; 2048 x 2048: 124 against 130), but for 2-D rows that do not start at
+// cache lines (stores_stay2d).
 bool kept_in_cache(int dim, int storage, long long np)
 {
     const long long f = storage == ST_FP64 ? 8 : storage == ST_FP32 ? 4 : 2;

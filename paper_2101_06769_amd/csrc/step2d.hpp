@@ -5,15 +5,16 @@
 // stencil and the update are those of k_phi and k_collide in the same order,
 // so the results are the same bits.
 //
-// Bound: launch and load latency up to about 10^5 cells, then the Infinity
-// Cache (6 TB/s of the 144 B/cell at 1024 x 1024 FP32), beyond it HBM.  Tiles
-// of 256 threads: 512 and 1024 sum fewer ring cells (148 and 164 a tile
-// against 140, for two and four times the cells) but leave a small lattice
-// fewer blocks: 4.9, 6.1 and 8.8 us on 64 x 256 FP64, 24.9, 25.4 and 26+ us on
-// 1024 x 1024 FP32.  Measured per step, before (two launches) and now:
-// 64 x 256 FP64 7.0 -> 4.9 us, 128 x 512 FP32 (single relaxation time)
-// 7.2 -> 4.8, 800 x 400 FP32 between symmetry planes 18.0 -> 10.7,
-// 1024 x 1024 FP32 38.8 -> 24.9, 4096 x 2048 FP32 272 -> 252 us.
+// Bound: launch and load latency up to about 10^5 cells (800 x 400 FP32 runs one
+// round of blocks, 3.9 wavefronts a SIMD, the VALU 75 % busy), then instruction
+// issue and the Infinity Cache together (1024 x 1024 FP32 90 % busy at 5.9 TB/s of
+// its 144 B/cell, FP16S 90 %, FP16S_ALL 98 %), beyond the cache HBM.  Tiles of 256
+// threads: 512 and 1024 sum fewer ring cells (148 and 164 a tile against 140, for
+// two and four times the cells) but leave a small lattice fewer blocks: 4.9, 6.1
+// and 8.8 us on 64 x 256 FP64, 24.9, 25.4 and 26+ us on 1024 x 1024 FP32.  Measured
+// per step, before (two launches) and now: 64 x 256 FP64 7.0 -> 4.9 us, 128 x 512
+// FP32 (single relaxation time) 7.2 -> 4.8, 800 x 400 FP32 between symmetry planes
+// 18.0 -> 10.7, 1024 x 1024 FP32 38.8 -> 24.9, 4096 x 2048 FP32 272 -> 252 us.
 #pragma once
 
 #include "device.hpp"
